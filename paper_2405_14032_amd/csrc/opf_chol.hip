@@ -42,6 +42,7 @@ constexpr int kNB = 64;      // panel width of the blocked fronts
 constexpr int kTile = 128;   // trailing-update tile (8 x 8 outputs per thread)
 constexpr int kChainCols = 128;  // column chunk of the chain's L21 z
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
+constexpr int kWide = 256;       // columns whose panels update each other within their launches
 // Trailing updates of at least this many rows below the panel and panel
 // columns go to the library's strided-batched GEMM (plain dense products);
 // smaller ones stay on k_update.
@@ -75,8 +76,19 @@ struct FrontArg {
   double* U;
   int64_t Ustride;
   int32_t ldU;
+  double* D;  // the factored diagonal blocks (see diag_size)
+  int64_t Dstride;
   const int32_t* stop;  // as CDev::stop
 };
+
+// The factored 64 x 64 diagonal blocks of a blocked front live apart from
+// its factor block, one after the other, the last one kb x kb (column-major,
+// leading dimension kb): every block of a panel launch reads the unfactored
+// block from the front while one of them stores the factored one.
+__host__ __device__ __forceinline__ int64_t diag_size(int p) {
+  const int64_t np = (p + kNB - 1) / kNB, kb = p - (np - 1) * kNB;
+  return (np - 1) * kNB * kNB + kb * kb;
+}
 
 // Whether the factorization stops at its first static pivot and one has
 // been counted: the count read once per block by its first thread and
@@ -278,57 +290,179 @@ __global__ void __launch_bounds__(64) k_factor_small(CDev D, const int32_t* __re
     }
 }
 
-// Blocked front, one panel [k0, k0+kb), step 1: the kb x kb diagonal block
-// factored in place by one wavefront per period (pivots counted here).
-__global__ void __launch_bounds__(64) k_diag(FrontArg A, int32_t k0, int32_t kb, double tol, double repl,
-                                             int32_t* __restrict__ npert) {
-  if (stopped(A.stop)) return;
-  double* L = A.L + (int64_t)blockIdx.x * A.Lstride;
-  const int64_t ld = A.ld;
-  const int i = (int)threadIdx.x;
-  double a[64];
-#pragma unroll
-  for (int j = 0; j < 64; ++j) a[j] = (j < kb && i >= j && i < kb) ? L[(int64_t)(k0 + j) * ld + k0 + i] : 0.0;
-  chol_rows64(a, kb, kb, tol, repl, npert);
-#pragma unroll
-  for (int j = 0; j < 64; ++j)
-    if (j < kb && i >= j && i < kb) L[(int64_t)(k0 + j) * ld + k0 + i] = a[j];
+// sqrt(d) and the reciprocal of that square root, both rounded as sqrt() and
+// the division round them: one hardware estimate refined by two coupled
+// (Goldschmidt) steps and a last correction each, where the two functions one
+// after the other are a dependent chain about three times as long -- and a
+// front's pivots are one serial chain.  d outside [2^-500, 2^500] is scaled
+// by a power of four first; an infinite pivot keeps inf and 0.
+__device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
+  const bool lo = d < 0x1p-500, hi = d > 0x1p500;
+  const double x = d * (lo ? 0x1p400 : (hi ? 0x1p-400 : 1.0));
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  g = fma(fma(-g, g, x), h, g);
+  h = h + h;
+  h = fma(fma(-g, h, 1.0), h, h);
+  const bool inf = d == INFINITY;
+  s = inf ? d : g * (lo ? 0x1p-200 : (hi ? 0x1p200 : 1.0));
+  r = inf ? 0.0 : h * (lo ? 0x1p200 : (hi ? 0x1p-200 : 1.0));
 }
 
-// Step 2: the rows below the panel, L21 = A21 L11^-T, 256 rows per block
-// against the factored diagonal block (read-only here).
-__global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t k0, int32_t kb) {
-  __shared__ double Dg[kNB * (kNB + 1)];
-  __shared__ double rdg[kNB];
-  constexpr int S = kNB + 1;
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+// Blocked front, one panel of kb <= 64 columns [k0, k0+kb): its update by the
+// columns [kbeg, k0) before it, its diagonal block's factorization and the
+// solve of the kTR rows of each block against it, in one launch.  Grid (row
+// blocks below the panel, at least one; periods).
+//
+// What bounds it is latency: a front's panels follow one another, 64 serial
+// pivots each.  So every block repeats the diagonal block's work (64 rows
+// beside its own kTR) instead of waiting for another launch, the pivot chain
+// runs in registers, one row per lane, 16 columns at a time: lanes 0-15 of
+// every wavefront hold the 16 diagonal rows, lanes 16-63 another 48 of the
+// rows below, so the pivot and column entries are broadcast within the
+// wavefront and the rows' solve costs no steps of its own; the columns to the
+// right take their 16-column update from the matrix cores.
+// (Before: one wavefront per diagonal block, 19 us, one launch for the rows,
+// 31 us, and one matrix-core update launch per 64 columns, 16 us at least.)
+constexpr int kTR = 64;
+__global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t kbeg, int32_t k0, int32_t kb, double tol,
+                                               double repl, int32_t* __restrict__ npert) {
+  constexpr int NG = (kNB + kTR) / 16;      // 16-row groups: 4 of the diagonal block, then the block's own rows
+  constexpr int GW = NG / 4;                // of which per wavefront
+  constexpr int S = kNB + kTR + 16;         // column stride: the 4 columns an operand load touches fall on distinct banks
+  __shared__ double P[kNB * S];
   if (stopped(A.stop)) return;
-  double* L = A.L + (int64_t)blockIdx.y * A.Lstride;
+  double* __restrict__ L = A.L + (int64_t)blockIdx.y * A.Lstride;
   const int64_t ld = A.ld;
   const int rows = A.p + A.u;
-  const int tid = (int)threadIdx.x;
-  for (int e = tid; e < kb * kb; e += (int)blockDim.x) {
-    const int j = e / kb, i = e % kb;
-    if (i >= j) Dg[j * S + i] = L[(int64_t)(k0 + j) * ld + k0 + i];
+  const int r0 = k0 + kb + (int)blockIdx.x * kTR;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  // rows and columns past the front are clamped onto its last ones: what is
+  // computed for them is never stored
+  const int last = rows - 1;
+  int64_t ra[4], rb[GW];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) ra[c] = min(k0 + c * 16 + lr, last);
+#pragma unroll
+  for (int i = 0; i < GW; ++i) {
+    const int g = wv + 4 * i;
+    rb[i] = min(g < 4 ? k0 + g * 16 + lr : r0 + (g - 4) * 16 + lr, last);
   }
-  if (tid < kb) rdg[tid] = 1.0 / L[(int64_t)(k0 + tid) * ld + k0 + tid];
-  __syncthreads();
-  const int r = k0 + kb + (int)blockIdx.x * (int)blockDim.x + tid;
-  if (r >= rows) return;
-  double x[kNB];
+  dbl4 x[4][GW];
 #pragma unroll
-  for (int j = 0; j < kNB; ++j) x[j] = j < kb ? L[(int64_t)(k0 + j) * ld + r] : 0.0;
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
-  for (int j = 0; j < kNB; ++j) {
-    if (j < kb) {
-      double sacc = x[j];
+    for (int e = 0; e < 4; ++e) {
+      const int64_t col = (int64_t)min(k0 + c * 16 + lk + 4 * e, A.p - 1) * ld;
 #pragma unroll
-      for (int l = 0; l < j; ++l) sacc -= x[l] * Dg[l * S + j];
-      x[j] = sacc * rdg[j];
+      for (int i = 0; i < GW; ++i) x[c][i][e] = L[col + rb[i]];
     }
+  // the columns before, in the blocks of the recursive elimination order (the
+  // 128 first ones, then 64), each block's product summed by itself and then
+  // subtracted; formed transposed (see k_update)
+  for (int k = kbeg; k < k0;) {
+    const int ke = k + ((k0 - k) & ~127 ? 128 : 64);  // k0 - kbeg is 0, 64, 128 or 192
+    dbl4 acc[4][GW];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < GW; ++i) acc[c][i] = (dbl4){0.0, 0.0, 0.0, 0.0};
+    for (; k < ke; k += 16) {
+      double a[4][4], b[4][GW];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t col = (int64_t)(k + 4 * q + lk) * ld;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a[q][c] = L[col + ra[c]];
+#pragma unroll
+        for (int i = 0; i < GW; ++i) b[q][i] = L[col + rb[i]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int i = 0; i < GW; ++i)
+            acc[c][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q][c], b[q][i], acc[c][i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < GW; ++i) x[c][i] -= acc[c][i];
   }
 #pragma unroll
-  for (int j = 0; j < kNB; ++j)
-    if (j < kb) L[(int64_t)(k0 + j) * ld + r] = x[j];
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int i = 0; i < GW; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + (wv + 4 * i) * 16 + lr] = x[c][i][e];
+  __syncthreads();
+  double* Dq = A.D + (int64_t)blockIdx.y * A.Dstride + (int64_t)(k0 / kNB) * kNB * kNB;
+  for (int jb = 0; jb * 16 < kb; ++jb) {
+    // this lane's row of the tile: a diagonal row, or one of the rows below
+    const int row = lane < 16 ? jb * 16 + lane : (jb + 1) * 16 + wv * 48 + lane - 16;
+    const bool in = row < kNB + kTR;
+    double a[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a[j] = in ? P[(jb * 16 + j) * S + row] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if (jb * 16 + k < kb) {
+        double d = lane_bcast(a[k], k);
+        if (!(d > tol)) {
+          d = repl;
+          if (tid == 0 && blockIdx.x == 0) atomicAdd(npert, 1);
+        }
+        double s, r;
+        sqrt_recip(d, s, r);
+        a[k] = lane == k ? s : a[k] * r;
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) a[j] = fma(-a[k], lane_bcast(a[k], j), a[j]);
+      }
+    }
+    // the rows below the 16 to LDS for the columns to the right.  What is
+    // done with goes to memory: the rows' solution to the front, the 16
+    // diagonal rows (the same in every block and wavefront; LDS keeps the
+    // unfactored ones, which a slower wavefront may not have read yet) and
+    // the diagonal block's rows below them once
+    const int gi = r0 + row - kNB;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int c = jb * 16 + j;
+      if (in && lane >= 16) P[c * S + row] = a[j];
+      if (c < kb) {
+        if (in && row >= kNB && gi < rows) L[(int64_t)(k0 + c) * ld + gi] = a[j];
+        if (blockIdx.x == 0 && row < kb && row >= c && (lane >= 16 || wv == 0)) Dq[(int64_t)c * kb + row] = a[j];
+      }
+    }
+    __syncthreads();
+    // the columns to the right: 16 x 16 tiles on and below the diagonal
+    const int nc = 3 - jb;  // column groups left
+    for (int t = wv; t < nc * (NG - 1 - jb); t += 4) {
+      const int c = jb + 1 + t % nc, g = jb + 1 + t / nc;
+      if (g < c) continue;
+      dbl4 x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = -P[(c * 16 + lk + 4 * e) * S + g * 16 + lr];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double* col = P + (jb * 16 + 4 * q + lk) * S;
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(col[c * 16 + lr], col[g * 16 + lr], x, 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + g * 16 + lr] = -x[e];
+    }
+    __syncthreads();
+  }
 }
 
 // Trailing update after a panel: C -= P P^T on the lower part of rows and
@@ -340,16 +474,12 @@ __global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t k0, int32_t k
 // group writes 16 consecutive rows of a column of the column-major front.
 // The panel is staged through LDS 16 columns at a time.  Columns < p live
 // in the factor block, the others in the update block.
-typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 // Region: rows [r0, p+u) x columns [r0, min(cmax, p+u)), lower part, in
 // 128 x 128 tiles enumerated column by column; panel columns [k0, k0+kb),
-// kb <= 1024.  With dnext > 0, block 0 (the tile holding rows and columns
-// [r0, r0+128)) then factors the next diagonal block [r0, r0+dnext) in
-// place, which the next panel needs.
+// kb <= 1024.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax, int32_t dnext, double tol, double repl,
-         int32_t* __restrict__ npert) {
+k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
   constexpr int KC = 16;
   constexpr int NLD = KC * kTile / 256;  // panel values per thread per chunk and side
   // two LDS buffers: the next chunk is loaded into registers while the
@@ -447,19 +577,6 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax, int32_t d
           else U[(int64_t)(j - A.p) * A.ldU + (i - A.p)] -= acc[c][r][e];
         }
       }
-  }
-  if (dnext > 0 && x == 0 && tj == 0) {
-    __syncthreads();
-    if (wv == 0) {
-      double a[64];
-#pragma unroll
-      for (int j = 0; j < 64; ++j)
-        a[j] = (j < dnext && lane >= j && lane < dnext) ? L[(int64_t)(r0 + j) * ld + r0 + lane] : 0.0;
-      chol_rows64(a, dnext, dnext, tol, repl, npert);
-#pragma unroll
-      for (int j = 0; j < 64; ++j)
-        if (j < dnext && lane >= j && lane < dnext) L[(int64_t)(r0 + j) * ld + r0 + lane] = a[j];
-    }
   }
 }
 
@@ -587,7 +704,8 @@ __global__ void __launch_bounds__(256) k_fwd_root_pull(CDev D, const int32_t* __
 // below the panel.  y's panel entries are only read here and z is only
 // written, so the blocks of one launch never touch an entry another block
 // writes.
-__global__ void __launch_bounds__(256) k_fwd_panel(const double* __restrict__ Lb, int64_t Lstride, int32_t ld,
+__global__ void __launch_bounds__(256) k_fwd_panel(const double* __restrict__ Lb, int64_t Lstride,
+                                                   const double* __restrict__ Db, int64_t Dstride, int32_t ld,
                                                    int32_t p, int32_t k0, double* __restrict__ yb,
                                                    double* __restrict__ zb, int64_t ystride) {
   __shared__ double Tr[64 * 65];
@@ -604,9 +722,10 @@ __global__ void __launch_bounds__(256) k_fwd_panel(const double* __restrict__ Lb
   double rv[64];
 #pragma unroll
   for (int l = 0; l < 64; ++l) rv[l] = (row && l < kb) ? L[(int64_t)(k0 + l) * ld + i] : 0.0;
+  const double* D = Db + (int64_t)blockIdx.y * Dstride + (int64_t)k0 * 64;
   for (int e = tid; e < 64 * 64; e += (int)blockDim.x) {
     const int c = e >> 6, r = e & 63;
-    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = L[(int64_t)(k0 + c) * ld + k0 + r];
+    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = D[c * kb + r];
   }
   __syncthreads();
   if (tid < 64) {
@@ -693,7 +812,8 @@ __global__ void __launch_bounds__(256) k_bwd_gemv(const double* __restrict__ Lb,
 // in y, and each block's 4 wavefronts subtract the panel's contribution
 // from their columns j < k0 of z (one wavefront per column, lanes over the
 // panel's rows).  Grid (column blocks of kBwdCols, periods).
-__global__ void __launch_bounds__(256) k_bwd_panel(const double* __restrict__ Lb, int64_t Lstride, int32_t ld,
+__global__ void __launch_bounds__(256) k_bwd_panel(const double* __restrict__ Lb, int64_t Lstride,
+                                                   const double* __restrict__ Db, int64_t Dstride, int32_t ld,
                                                    int32_t p, int32_t k0, double* __restrict__ yb,
                                                    double* __restrict__ zb, int64_t ystride) {
   __shared__ double Tr[64 * 65];
@@ -713,9 +833,10 @@ __global__ void __launch_bounds__(256) k_bwd_panel(const double* __restrict__ Lb
     const int j = jb + wv + 4 * q;
     cv[q] = (j < je && lane < kb) ? L[(int64_t)j * ld + k0 + lane] : 0.0;
   }
+  const double* D = Db + (int64_t)blockIdx.y * Dstride + (int64_t)k0 * 64;
   for (int e = tid; e < 64 * 64; e += (int)blockDim.x) {
     const int c = e >> 6, r = e & 63;
-    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = L[(int64_t)(k0 + c) * ld + k0 + r];
+    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = D[c * kb + r];
   }
   __syncthreads();
   if (tid < 64) {
@@ -792,10 +913,11 @@ struct CholInst {
           *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr;
   int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
           *d_slot = nullptr;
-  double *Lf = nullptr, *Cf = nullptr, *Ar = nullptr, *W = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
+  double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
   double* Gp = nullptr;  // column-chunk partials of the chain's L21 z
   std::vector<int64_t> woff;  // per-front offsets of the forward update vectors
-  int64_t csize = 0, wsize = 0;
+  std::vector<int64_t> doff;  // per-front offsets of the diagonal blocks (large fronts)
+  int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
 };
 
@@ -900,6 +1022,12 @@ int setup_device(opf_chol* F, CholInst& C) {
     w += P.node_u[s];
   }
   C.wsize = std::max<int64_t>(w, 1);
+  C.doff.assign(P.nnodes, 0);
+  for (int32_t s : P.lvl_large) {
+    C.doff[s] = C.dsize;
+    C.dsize += diag_size(P.node_p[s]);
+  }
+  C.dcsize = diag_size(P.G);
   std::vector<int32_t> items = P.items;
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
@@ -925,6 +1053,8 @@ int setup_device(opf_chol* F, CholInst& C) {
   C.chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>(T, arena_budget() / (P.usize * 8)));
   CHK(dalloc(F, P.lsize * T, &C.Lf));
   CHK(dalloc(F, C.csize * T, &C.Cf));
+  CHK(dalloc(F, C.dsize * T, &C.Df));
+  CHK(dalloc(F, C.dcsize * T, &C.Dc));
   CHK(dalloc(F, P.usize * C.chunk, &C.Ar));
   CHK(dalloc(F, C.wsize * T, &C.W));
   CHK(dalloc(F, G * T, &C.Wc));
@@ -952,22 +1082,15 @@ int setup_device(opf_chol* F, CholInst& C) {
   return OPF_OK;
 }
 
-// Blocked factorization of one front over nt periods: 128-column steps of
-// two 64-column sub-panels (diagonal block, rows below; the first
-// sub-panel's update of the second's columns in between), then one
-// trailing update with the 128-wide panel.  Each update launch also factors
-// the next diagonal block.
-// The same update through the library's strided-batched GEMM, every call
+// A trailing update through the library's strided-batched GEMM, every call
 // batched over the nt periods by their strides.  The lower part of the
 // target columns is covered by column blocks of kBlasCols: block [j, j+w)
 // takes rows [j, end) in one product, so it also writes the upper part of
 // its w x w diagonal block (no kernel reads above the diagonal of a factor
 // or update block).  The library's SYRK measured 2-12 TFLOP/s on these
 // shapes against 40-70 for GEMM.  Columns in the factor block first, then
-// those in the update block; the next diagonal block is factored by a
-// launch of its own afterwards.
-int blas_update(rocblas_handle h, const FrontArg& A, int nt, int k0, int kb, int r0, int cend, int dnext,
-                double tol, double repl, int32_t* npert, hipStream_t st) {
+// those in the update block.
+int blas_update(rocblas_handle h, const FrontArg& A, int nt, int k0, int kb, int r0, int cend, hipStream_t st) {
   const int rows = A.p + A.u;
   const int64_t ld = A.ld;
   if (rocblas_set_stream(h, st) != rocblas_status_success) return api_fail(OPF_EHIP, "chol: rocblas_set_stream failed");
@@ -990,49 +1113,36 @@ int blas_update(rocblas_handle h, const FrontArg& A, int nt, int k0, int kb, int
   const int c0 = std::max(r0, A.p);
   const int n3 = cend - c0;  // target columns in the update block
   if (n3 > 0) CHK(lower(c0, n3, A.U + (int64_t)(c0 - A.p) * A.ldU + (c0 - A.p), A.ldU, A.Ustride));
-  if (dnext > 0) {
-    hipLaunchKernelGGL(k_diag, dim3(nt), dim3(64), 0, st, A, r0, dnext, tol, repl, npert);
-    LAUNCH_OK("chol diagonal block");
-  }
   return OPF_OK;
 }
 
-int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, int dnext, double tol, double repl,
-                  int32_t* npert, hipStream_t st, rocblas_handle h) {
+int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, hipStream_t st, rocblas_handle h) {
   const int rows = A.p + A.u;
   const int cend = std::min(cmax, rows);
-  if (r0 >= rows || cend <= r0) {
-    if (dnext > 0) {
-      hipLaunchKernelGGL(k_diag, dim3(nt), dim3(64), 0, st, A, r0, dnext, tol, repl, npert);
-      LAUNCH_OK("chol diagonal block");
-    }
-    return OPF_OK;
-  }
-  if (h && kb >= kBlasMinCols && rows - r0 >= kBlasMinRows)
-    return blas_update(h, A, nt, k0, kb, r0, cend, dnext, tol, repl, npert, st);
+  if (r0 >= rows || cend <= r0) return OPF_OK;
+  if (h && kb >= kBlasMinCols && rows - r0 >= kBlasMinRows) return blas_update(h, A, nt, k0, kb, r0, cend, st);
   const int64_t R = (rows - r0 + kTile - 1) / kTile, Cn = (cend - r0 + kTile - 1) / kTile;
   const int64_t ntiles = Cn * R - Cn * (Cn - 1) / 2;
   if (ntiles > 0x7fffffff) return api_fail(OPF_EINVAL, "chol: front too large");
-  hipLaunchKernelGGL(k_update, dim3((unsigned)ntiles, nt), dim3(256), 0, st, A, k0, kb, r0, cmax, dnext, tol, repl,
-                     npert);
+  hipLaunchKernelGGL(k_update, dim3((unsigned)ntiles, nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
   LAUNCH_OK("chol update");
   return OPF_OK;
 }
 
-// Columns [k, k+w) of a front whose diagonal block [k, k+64) is factored
-// already, w a power of two >= 64: recursively the first half, the first
-// half's update of the second half's columns (which also factors the second
-// half's first diagonal block), the second half.  The rows below the block
-// get their share of the panel through the panel kernels; the trailing
-// columns are left to the caller.
+// Columns [k, k+w) of a front, w a power of two >= kWide: up to kWide columns
+// by panels that each take their update from the block's columns before them;
+// wider blocks recursively: the first half, the first half's update of the
+// second half's columns, the second half.  The trailing columns are left to
+// the caller.
 int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl, int32_t* npert, hipStream_t st,
                 rocblas_handle bh) {
   const int rows = A.p + A.u;
   if (k >= A.p) return OPF_OK;
-  if (w == 64) {
-    const int kb = std::min(64, A.p - k);
-    if (rows > k + kb) {
-      hipLaunchKernelGGL(k_panel, dim3((rows - k - kb + 255) / 256, nt), dim3(256), 0, st, A, k, kb);
+  if (w == kWide) {
+    for (int k0 = k; k0 < std::min(k + kWide, A.p); k0 += kNB) {
+      const int kb = std::min(kNB, A.p - k0);
+      hipLaunchKernelGGL(k_panel, dim3(std::max(1, (rows - k0 - kb + kTR - 1) / kTR), nt), dim3(256), 0, st, A, k, k0,
+                         kb, tol, repl, npert);
       LAUNCH_OK("chol panel");
     }
     return OPF_OK;
@@ -1043,7 +1153,7 @@ int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl
   const int k2 = std::min(h, A.p - k - kh);
   if (k2 > 0) {
     const int r1 = k + kh;
-    CHK(launch_update(A, nt, k, kh, r1, r1 + k2, std::min(64, k2), tol, repl, npert, st, bh));
+    CHK(launch_update(A, nt, k, kh, r1, r1 + k2, st, bh));
     CHK(factor_cols(A, nt, r1, h, tol, repl, npert, st, bh));
   }
   return OPF_OK;
@@ -1052,16 +1162,12 @@ int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl
 int factor_front(const FrontArg& A, int nt, double tol, double repl, int32_t* npert, hipStream_t st,
                  rocblas_handle bh) {
   const int rows = A.p + A.u;
-  hipLaunchKernelGGL(k_diag, dim3(nt), dim3(64), 0, st, A, 0, std::min(64, A.p), tol, repl, npert);
-  LAUNCH_OK("chol diagonal block");
   // kStep-column steps, each factored recursively, then one trailing update
-  // with the kStep-wide panel; every update launch also factors the next
-  // diagonal block
+  // with the kStep-wide panel
   for (int k0 = 0; k0 < A.p; k0 += kStep) {
     CHK(factor_cols(A, nt, k0, kStep, tol, repl, npert, st, bh));
-    const int kb = std::min(kStep, A.p - k0), r0 = k0 + kb;
-    const int dnext = r0 < A.p ? std::min(64, A.p - r0) : 0;
-    CHK(launch_update(A, nt, k0, kb, r0, rows, dnext, tol, repl, npert, st, bh));
+    const int kb = std::min(kStep, A.p - k0);
+    CHK(launch_update(A, nt, k0, kb, k0 + kb, rows, st, bh));
   }
   return OPF_OK;
 }
@@ -1136,6 +1242,8 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
     A.U = Ub;
     A.Ustride = nt > 1 ? gg : 0;
     A.ldU = G;
+    A.D = C.Dc + (int64_t)t * C.dcsize;
+    A.Dstride = nt > 1 ? (int64_t)(t2 - t) * C.dcsize : 0;
     A.stop = C.dev.stop;
     return factor_front(A, nt, tol, repl, npert, F->cs, F->blas);
   };
@@ -1205,6 +1313,8 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
         A.U = C.Ar + P.node_uoff[s];
         A.Ustride = P.usize;
         A.ldU = std::max(1, P.node_u[s]);
+        A.D = C.Df + (int64_t)t0 * C.dsize + C.doff[s];
+        A.Dstride = C.dsize;
         A.stop = C.dev.stop;
         CHK(factor_front(A, nt, tol, repl, npert, fst, nullptr));
       }
@@ -1237,22 +1347,22 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
 // Forward / backward triangle of one front's pivot block by panels (see
 // k_fwd_panel / k_bwd_panel): y is the right-hand side in, z the forward
 // solution; the backward pass reads z and leaves x in y.
-int fwd_tri(const double* L, int64_t Ls, int ld, int p, double* y, double* z, int64_t ys, int nper,
+int fwd_tri(const double* L, int64_t Ls, const double* D, int64_t Ds, int ld, int p, double* y, double* z, int64_t ys, int nper,
             hipStream_t st) {
   for (int k0 = 0; k0 < p; k0 += 64) {
     const int below = p - k0 - std::min(64, p - k0);
-    hipLaunchKernelGGL(k_fwd_panel, dim3(std::max(1, (below + 255) / 256), nper), dim3(256), 0, st, L, Ls, ld, p,
-                       k0, y, z, ys);
+    hipLaunchKernelGGL(k_fwd_panel, dim3(std::max(1, (below + 255) / 256), nper), dim3(256), 0, st, L, Ls, D, Ds,
+                       ld, p, k0, y, z, ys);
   }
   LAUNCH_OK("chol forward triangle");
   return OPF_OK;
 }
 
-int bwd_tri(const double* L, int64_t Ls, int ld, int p, double* y, double* z, int64_t ys, int nper,
+int bwd_tri(const double* L, int64_t Ls, const double* D, int64_t Ds, int ld, int p, double* y, double* z, int64_t ys, int nper,
             hipStream_t st) {
   for (int k0 = ((p - 1) / 64) * 64; k0 >= 0; k0 -= 64)
     hipLaunchKernelGGL(k_bwd_panel, dim3(std::max(1, (k0 + kBwdCols - 1) / kBwdCols), nper), dim3(256), 0, st, L,
-                       Ls, ld, p, k0, y, z, ys);
+                       Ls, D, Ds, ld, p, k0, y, z, ys);
   LAUNCH_OK("chol backward triangle");
   return OPF_OK;
 }
@@ -1278,7 +1388,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
       const int p = P.node_p[s], u = P.node_u[s], fs = P.node_f[s];
       const double* L = C.Lf + P.node_loff[s];
       hipLaunchKernelGGL(k_fwd_pull, dim3(T), dim3(256), 0, st, C.dev, s, C.Y, C.W);
-      CHK(fwd_tri(L, P.lsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
+      CHK(fwd_tri(L, P.lsize, C.Df + C.doff[s], C.dsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
       if (u > 0)
         hipLaunchKernelGGL(k_fwd_gemv, dim3((u + 255) / 256, T), dim3(256), 0, st, L, P.lsize, p + u, p, u,
                            (const double*)(C.Z + fs), np, C.W + C.woff[s], C.wsize, 1);
@@ -1294,6 +1404,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   const int m = (T - 1) / 2;
   auto off = [&](int t) { return (int64_t)t * np + P.n_int; };
   auto front = [&](int t) { return (const double*)(C.Cf + (int64_t)t * C.csize); };
+  auto diag = [&](int t) { return (const double*)(C.Dc + (int64_t)t * C.dcsize); };
   // y_t -= L21_s z_s of its chain neighbour s (held in Wc[s])
   auto pull = [&](int t, int s) -> int {
     hipLaunchKernelGGL(k_sub, dim3((G + 255) / 256), dim3(256), 0, st, C.Y + off(t),
@@ -1318,10 +1429,11 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
       if (l && kl >= 1) CHK(pull(kl, kl - 1));
       if (r && kr <= T - 2) CHK(pull(kr, kr + 1));
       if (l && r)
-        CHK(fwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
+        CHK(fwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, diag(kl), (int64_t)(kr - kl) * C.dcsize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
                     (int64_t)(kr - kl) * np, 2, st));
       else
-        CHK(fwd_tri(front(l ? kl : kr), 0, 2 * G, G, C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
+        CHK(fwd_tri(front(l ? kl : kr), 0, diag(l ? kl : kr), 0, 2 * G, G,
+                    C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
       if (l) CHK(push(kl));
       if (r) CHK(push(kr));
       if (l) ++kl;
@@ -1329,12 +1441,12 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     }
     if (m >= 1) CHK(pull(m, m - 1));
     if (m + 1 <= T - 1) CHK(pull(m, m + 1));
-    CHK(fwd_tri(front(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
+    CHK(fwd_tri(front(m), 0, diag(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
   }
   // backward along the pg chain: front m, then outwards (each front reads
   // its chain neighbour's solution, held in Y)
   {
-    CHK(bwd_tri(front(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
+    CHK(bwd_tri(front(m), 0, diag(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
     int kl = m - 1, kr = m + 1;
     while (kl >= 0 || kr <= T - 1) {
       const bool l = kl >= 0, r = kr <= T - 1;
@@ -1348,10 +1460,11 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
                            (int64_t)0);
       LAUNCH_OK("chol backward chain");
       if (l && r)
-        CHK(bwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
+        CHK(bwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, diag(kl), (int64_t)(kr - kl) * C.dcsize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
                     (int64_t)(kr - kl) * np, 2, st));
       else
-        CHK(bwd_tri(front(l ? kl : kr), 0, 2 * G, G, C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
+        CHK(bwd_tri(front(l ? kl : kr), 0, diag(l ? kl : kr), 0, 2 * G, G,
+                    C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
       if (l) --kl;
       if (r) ++kr;
     }
@@ -1365,7 +1478,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
       if (u > 0)
         hipLaunchKernelGGL(k_bwd_gemv, dim3((p + 3) / 4, T), dim3(256), 0, st, L, P.lsize, p + u, p, u,
                            (const int32_t*)(C.d_rows + P.row_ptr[s]), (const double*)C.Y, np, C.Z + fs, np);
-      CHK(bwd_tri(L, P.lsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
+      CHK(bwd_tri(L, P.lsize, C.Df + C.doff[s], C.dsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
       LAUNCH_OK("chol backward large");
     }
     const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1];
