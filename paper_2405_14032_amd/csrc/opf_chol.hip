@@ -39,7 +39,7 @@ namespace {
 
 constexpr int kSmall = 64;   // largest front factored in LDS by one wavefront
 constexpr int kNB = 64;      // panel width of the blocked fronts
-constexpr int kTile = 128;   // trailing-update tile (8 x 8 outputs per thread)
+constexpr int kTile = 64;    // trailing-update tile
 constexpr int kChainCols = 128;  // column chunk of the chain's L21 z
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
 constexpr int kWide = 256;       // columns whose panels update each other within their launches
@@ -465,76 +465,108 @@ __global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t kbeg, int32_t
   }
 }
 
-// Trailing update after a panel: C -= P P^T on the lower part of rows and
-// columns [k0+kb, p+u), 128 x 128 tiles on the FP64 matrix cores: each of
-// the 4 wavefronts accumulates a 64 x 64 quarter as 4 x 4 products of
-// 16 x 16 x 4 (v_mfma_f64_16x16x4: lane l supplies A(l%16, l/16) and
-// B(l/16, l%16) and holds D(l/16 + 4r, l%16), r < 4).  The product is
-// formed transposed (rows of the tile along the lanes) so that each lane
-// group writes 16 consecutive rows of a column of the column-major front.
-// The panel is staged through LDS 16 columns at a time.  Columns < p live
-// in the factor block, the others in the update block.
-
-// Region: rows [r0, p+u) x columns [r0, min(cmax, p+u)), lower part, in
-// 128 x 128 tiles enumerated column by column; panel columns [k0, k0+kb),
-// kb <= 1024.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
-  constexpr int KC = 16;
-  constexpr int NLD = KC * kTile / 256;  // panel values per thread per chunk and side
-  // two LDS buffers: the next chunk is loaded into registers while the
+// Trailing update after a panel: C -= P P^T on the lower part of rows
+// [r0, p+u) x columns [r0, min(cmax, p+u)), P the panel columns [k0, k0+kb).
+// Columns < p live in the factor block, the others in the update block.
+//
+// FP64 matrix cores: v_mfma_f64_16x16x4, lane l supplies A(l%16, l/16) and
+// B(l/16, l%16) and holds D(l/16 + 4r, l%16), r < 4.  The product is formed
+// transposed (rows of the tile along the lanes) so that each lane group writes
+// 16 consecutive rows of a column of the column-major front; every entry is
+// one ascending chain over the panel's columns, whatever the tile.
+//
+// What bounds it is keeping the matrix cores issued: one wavefront per SIMD
+// reaches half their rate, so a block in its first loads or its last
+// read-modify-write has to leave others running.  64 x 64 tiles of 4
+// wavefronts (32 x 32 each, 63 VGPRs) with 8 panel columns per LDS round (20 KB
+// for both buffers) leave 7 blocks on a CU: 58 TFLOP/s at 4323 columns x 1024
+// panel columns x 8 periods, 47 at 4114 x 204 x 8, 55 at 2976 x 1024 x 2; 128 x
+// 128 tiles of 4 wavefronts (2 blocks on a CU) reached 51, 33 and 37, of 8
+// wavefronts 60, 45 and 43, and twice the time on launches of few tiles.
+// Tiles are taken in column groups of kGroup, row by row, and each XCD gets a
+// contiguous run of (period, tile) items, so that the tiles running side by
+// side share panel slices in its L2.
+constexpr int kGroup = 8;
+__global__ void __launch_bounds__(256, 6) k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
+  constexpr int KC = 8;              // panel columns per LDS round
+  constexpr int S = kTile + 16;      // column stride: an operand load's 4 columns fall on distinct banks
+  constexpr int CS = 256 / kTile;    // columns a load of the block covers
+  constexpr int NLD = KC / CS;       // loads per thread and side
+  // two LDS buffers: the next round is loaded into registers while the
   // matrix cores work on the current one
-  __shared__ double Pi[2][KC][kTile], Pj[2][KC][kTile];
+  __shared__ double Pi[2][KC * S], Pj[2][KC * S];
   if (stopped(A.stop)) return;
-  const int rows = A.p + A.u;
-  const int R = (rows - r0 + kTile - 1) / kTile;
-  // blocks are dealt round-robin to the 8 XCDs in launch order; give each
-  // XCD a contiguous run of (period, tile) items so that neighbouring tiles,
-  // which share panel slices, meet in the same L2
+  const int rows = A.p + A.u, cend = min(cmax, rows);
+  const int R = (rows - r0 + kTile - 1) / kTile, Cn = (cend - r0 + kTile - 1) / kTile;
+  // blocks are dealt round-robin to the 8 XCDs in launch order
   const int ntl = (int)gridDim.x, total = ntl * (int)gridDim.y;
   int item = (int)(blockIdx.y * gridDim.x + blockIdx.x);
   const int q8 = total >> 3;
   if (item < (q8 << 3)) item = (item & 7) * q8 + (item >> 3);
   const int per = item / ntl;
-  int x = item % ntl, tj = 0;
-  while (x >= R - tj) {
-    x -= R - tj;
-    ++tj;
+  int x = item % ntl, ti = 0, tj = 0;
+  for (int g = 0;; g += kGroup) {
+    // column group [g, g + w): a triangle of w rows, then full rows
+    const int w = min(kGroup, Cn - g), tri = w * (w + 1) / 2, cnt = tri + (R - g - w) * w;
+    if (x >= cnt) {
+      x -= cnt;
+      continue;
+    }
+    if (x < tri) {
+      int i = 0;
+      while (x > i) x -= ++i;
+      ti = g + i;
+      tj = g + x;
+    } else {
+      ti = g + w + (x - tri) / w;
+      tj = g + (x - tri) % w;
+    }
+    break;
   }
-  const int ti = tj + x;
-  const int cend = min(cmax, rows);
   double* L = A.L + (int64_t)per * A.Lstride;
   double* U = A.U + (int64_t)per * A.Ustride;
   const int64_t ld = A.ld;
   const int i0 = r0 + ti * kTile, j0 = r0 + tj * kTile;
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wr = wv & 1, wc = wv >> 1;  // the wavefront's 64-row / 64-column quarter
+  const int wr = wv & 1, wc = wv >> 1;  // the wavefront's 32-row / 32-column quarter
   // a quarter wholly above the diagonal or right of the region contributes nothing
-  const bool skip = i0 + wr * 64 + 63 < j0 + wc * 64 || j0 + wc * 64 >= cend;
-  dbl4 acc[4][4];
+  const bool skip = i0 + wr * 32 + 31 < j0 + wc * 32 || j0 + wc * 32 >= cend;
+  dbl4 acc[2][2];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[c][r] = (dbl4){0.0, 0.0, 0.0, 0.0};
+    for (int r = 0; r < 2; ++r) acc[c][r] = (dbl4){0.0, 0.0, 0.0, 0.0};
   const int lr = lane & 15, lk = lane >> 4;
+  // this thread's row of both slices (rows past the front are clamped onto
+  // its last one: what is computed for them is never stored)
+  const int rr = tid % kTile, lc = tid / kTile;
+  const double* pi = L + (int64_t)(k0 + lc) * ld + min(i0 + rr, rows - 1);
+  const double* pj = L + (int64_t)(k0 + lc) * ld + min(j0 + rr, rows - 1);
+  const int64_t step = CS * ld;
   double ri[NLD], rj[NLD];
   auto fetch = [&](int l0) {
-    const int lb = min(KC, kb - l0);
+    if (l0 + KC <= kb) {
 #pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-      const int e = tid + q * 256;
-      const int l = e / kTile, rr = e % kTile;
-      const int64_t col = (int64_t)(k0 + l0 + l) * ld;
-      ri[q] = (l < lb && i0 + rr < rows) ? L[col + i0 + rr] : 0.0;
-      rj[q] = (l < lb && j0 + rr < cend) ? L[col + j0 + rr] : 0.0;
+      for (int q = 0; q < NLD; ++q) {
+        ri[q] = pi[q * step];
+        rj[q] = pj[q * step];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NLD; ++q) {
+        const bool in = l0 + lc + CS * q < kb;
+        ri[q] = in ? pi[q * step] : 0.0;
+        rj[q] = in ? pj[q * step] : 0.0;
+      }
     }
+    pi += KC * ld;
+    pj += KC * ld;
   };
   auto park = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
-      const int e = tid + q * 256;
-      Pi[buf][e / kTile][e % kTile] = ri[q];
-      Pj[buf][e / kTile][e % kTile] = rj[q];
+      Pi[buf][(lc + CS * q) * S + rr] = ri[q];
+      Pj[buf][(lc + CS * q) * S + rr] = rj[q];
     }
   };
   fetch(0);
@@ -542,42 +574,41 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
   __syncthreads();
   int buf = 0;
   for (int l0 = 0; l0 < kb; l0 += KC) {
-    const int lb = min(KC, kb - l0);
     const bool more = l0 + KC < kb;
     if (more) fetch(l0 + KC);
     if (!skip) {
-      for (int k4 = 0; k4 < lb; k4 += 4) {
-        double aj[4], bi[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          aj[q] = Pj[buf][k4 + lk][wc * 64 + q * 16 + lr];
-          bi[q] = Pi[buf][k4 + lk][wr * 64 + q * 16 + lr];
+      for (int k4 = 0; k4 < KC; k4 += 4) {
+        double aj[2], bi[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          aj[q] = Pj[buf][(k4 + lk) * S + wc * 32 + q * 16 + lr];
+          bi[q] = Pi[buf][(k4 + lk) * S + wr * 32 + q * 16 + lr];
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(aj[c], bi[r], acc[c][r], 0, 0, 0);
+          for (int r = 0; r < 2; ++r) acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(aj[c], bi[r], acc[c][r], 0, 0, 0);
       }
     }
     if (more) park(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
-  if (!skip) {
+  if (skip) return;
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = i0 + wr * 64 + r * 16 + lr;
+    for (int r = 0; r < 2; ++r) {
+      const int i = i0 + wr * 32 + r * 16 + lr;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = j0 + wc * 64 + c * 16 + lk + 4 * e;
-          if (i >= rows || j >= cend || i < j) continue;
-          if (j < A.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
-          else U[(int64_t)(j - A.p) * A.ldU + (i - A.p)] -= acc[c][r][e];
-        }
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + wc * 32 + c * 16 + lk + 4 * e;
+        if (i >= rows || j >= cend || i < j) continue;
+        if (j < A.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
+        else U[(int64_t)(j - A.p) * A.ldU + (i - A.p)] -= acc[c][r][e];
       }
-  }
+    }
 }
 
 // G x G lower update block of pg front t-1 into the pivot block of front t.
