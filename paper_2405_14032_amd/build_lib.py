@@ -28,10 +28,7 @@ def build(verbose: bool = False) -> str:
         "-ffp-contract=on",
         "-Wall", "-Wno-unused-result",
         "-o", LIB + ".tmp",
-    ] + [os.path.join(HERE, s) for s in SOURCES] + [
-        # the dense trailing updates of the pg chain's fronts in the sparse Cholesky
-        "-L/opt/rocm/lib", "-lrocblas",
-    ]
+    ] + [os.path.join(HERE, s) for s in SOURCES]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, cwd=HERE, capture_output=True, text=True)

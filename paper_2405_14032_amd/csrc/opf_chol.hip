@@ -15,12 +15,10 @@
 //     and its chain neighbour's update: a chain over t, eliminated from both
 //     ends at once (fronts t < m carry update rows pg_{t+1}, fronts t > m
 //     update rows pg_{t-1}, front m closes it; m = (T - 1) / 2), one front of
-//     each side per launch, its large trailing updates as library GEMMs (see
-//     blas_update).
+//     each side per launch.
 // Solves run the same tree forward (update vectors pulled by the parent)
 // and backward (gathers of the ancestors' solution), batched over periods.
 #include <hip/hip_runtime.h>
-#include <rocblas/rocblas.h>
 
 #include <algorithm>
 #include <cmath>
@@ -28,6 +26,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/opf.h"
@@ -43,19 +42,7 @@ constexpr int kTile = 64;    // trailing-update tile
 constexpr int kChainCols = 128;  // column chunk of the chain's L21 z
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
 constexpr int kWide = 256;       // columns whose panels update each other within their launches
-// Trailing updates of at least this many rows below the panel and panel
-// columns go to the library's strided-batched GEMM (plain dense products);
-// smaller ones stay on k_update.
-constexpr int kBlasMinRows = 512;
-constexpr int kBlasMinCols = 64;
-constexpr int kBlasCols = 512;  // target columns per library product
-// Only the pg chain's fronts (one or two periods per launch) go to the
-// library: so few periods give k_update too few tiles to fill the GPU, and
-// the chain runs its steps in sequence (measured at paper scale on the
-// one-ended chain: 1.132 -> 1.065 s per factorization from 128 panel
-// columns, 1.000 s from 64; the library on the batched interior fronts as
-// well was slower, its long-running blocks holding the CUs the chain's short
-// launches wait for).  The interior passes no library handle.
+constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 ones (one block per CU)
 constexpr int kBwdCols = 16;     // earlier columns updated per block of a backward panel (a multiple of 4)
 
 // Device view of one instance's plan.
@@ -295,7 +282,7 @@ __global__ void __launch_bounds__(64) k_factor_small(CDev D, const int32_t* __re
 // (Goldschmidt) steps and a last correction each, where the two functions one
 // after the other are a dependent chain about three times as long -- and a
 // front's pivots are one serial chain.  d outside [2^-500, 2^500] is scaled
-// by a power of four first; an infinite pivot keeps inf and 0.
+// by a power of four first; an infinite d keeps inf and 0.
 __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   const bool lo = d < 0x1p-500, hi = d > 0x1p500;
   const double x = d * (lo ? 0x1p400 : (hi ? 0x1p-400 : 1.0));
@@ -310,9 +297,98 @@ __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   g = fma(fma(-g, g, x), h, g);
   h = h + h;
   h = fma(fma(-g, h, 1.0), h, h);
+  g *= lo ? 0x1p-200 : (hi ? 0x1p200 : 1.0);
+  h *= lo ? 0x1p200 : (hi ? 0x1p-200 : 1.0);
+  asm("" : "+v"(g), "+v"(h));  // selects, not a branch around the above
   const bool inf = d == INFINITY;
-  s = inf ? d : g * (lo ? 0x1p-200 : (hi ? 0x1p200 : 1.0));
-  r = inf ? 0.0 : h * (lo ? 0x1p200 : (hi ? 0x1p-200 : 1.0));
+  s = inf ? d : g;
+  r = inf ? 0.0 : h;
+}
+
+// The static pivot rule as the elimination uses it: the threshold, the square
+// root of the replacement and its reciprocal.
+struct PivotRule {
+  double tol, s_repl, r_repl;
+};
+
+// Square root and reciprocal of a pivot that is static, infinite, NaN or far
+// from 1 in size: rare, kept out of the pivot chain.
+__device__ __forceinline__ void odd_pivot(double d, const PivotRule& R, bool count, double& s, double& r, int& low) {
+  const bool bad = !(d > R.tol);
+  sqrt_recip(d, s, r);
+  s = bad ? R.s_repl : s;
+  r = bad ? R.r_repl : r;
+  low += bad && count;
+}
+
+// Whether a pivot takes that way: not above the threshold, or outside about
+// [2^-500, 2^500] (a negative one, a NaN or an infinity lies outside too, by
+// its leading word as an unsigned number).
+__device__ __forceinline__ bool is_odd(double d, double tol) {
+  const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, d) >> 32);
+  return hi - 0x20c00000u > 0x5f200000u - 0x20c00000u || !(d > tol);
+}
+
+// Right-looking elimination of 16 columns, one row per lane, lanes 0-15 the
+// diagonal rows; low counts the static pivots among the first n columns.
+// Column k updates column k + 1 first; then that column's pivot is taken
+// (sqrt_recip without its scaling, step by step, some 15 dependent operations)
+// with the updates of the columns further right in between, one after each
+// step: one wavefront issues an instruction every 4 cycles at best, so the
+// chain's waits are where the updates belong, and every instruction counts.
+// The empty asm statements hold that order; left to itself the compiler
+// collects a column's updates in front of its pivot, one dependent chain, and
+// spills the broadcast entries.
+__device__ __forceinline__ void eliminate16(double (&a)[16], int lane, int n, const PivotRule& R, int& low) {
+  double s, r;
+  odd_pivot(lane_bcast(a[0], 0), R, 0 < n, s, r, low);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    a[k] = lane == k ? s : a[k] * r;
+    if (k + 1 == 16) break;
+    a[k + 1] = fma(-a[k], lane_bcast(a[k], k + 1), a[k + 1]);
+    const double d = lane_bcast(a[k + 1], k + 1);
+    int j = k + 2, left = 8;
+    auto fill = [&]() {
+      const int c = (16 - j + left - 1) / left;
+      --left;
+#pragma unroll
+      for (int q = 0; q < c; ++q, ++j) {
+        a[j] = fma(-a[k], lane_bcast(a[k], j), a[j]);
+        asm volatile("" : "+v"(a[j]));
+      }
+    };
+    double y = __builtin_amdgcn_rsq(d);
+    asm volatile("" : "+v"(y));
+    fill();
+    double g = d * y, h = 0.5 * y;
+    asm volatile("" : "+v"(g), "+v"(h));
+    fill();
+    double e = fma(-h, g, 0.5);
+    asm volatile("" : "+v"(e));
+    fill();
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    asm volatile("" : "+v"(g), "+v"(h));
+    fill();
+    e = fma(-g, g, d);
+    asm volatile("" : "+v"(e));
+    fill();
+    g = fma(e, h, g);
+    asm volatile("" : "+v"(g));
+    fill();
+    e = fma(-g, g, d);
+    asm volatile("" : "+v"(e));
+    fill();
+    g = fma(e, h, g);
+    h = h + h;
+    asm volatile("" : "+v"(g), "+v"(h));
+    fill();
+    e = fma(-g, h, 1.0);
+    s = g;
+    r = fma(e, h, h);
+    if (is_odd(d, R.tol)) odd_pivot(d, R, k + 1 < n, s, r, low);
+  }
 }
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
@@ -329,15 +405,18 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // every wavefront hold the 16 diagonal rows, lanes 16-63 another 48 of the
 // rows below, so the pivot and column entries are broadcast within the
 // wavefront and the rows' solve costs no steps of its own; the columns to the
-// right take their 16-column update from the matrix cores.
+// right take their 16-column update from the matrix cores.  8 wavefronts: the update by the columns
+// before needs two per SIMD to fill the matrix cores.
 // (Before: one wavefront per diagonal block, 19 us, one launch for the rows,
 // 31 us, and one matrix-core update launch per 64 columns, 16 us at least.)
 constexpr int kTR = 64;
-__global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t kbeg, int32_t k0, int32_t kb, double tol,
+constexpr int kPT = 512;  // threads
+__global__ void __launch_bounds__(kPT) k_panel(FrontArg A, int32_t kbeg, int32_t k0, int32_t kb, double tol,
                                                double repl, int32_t* __restrict__ npert) {
-  constexpr int NG = (kNB + kTR) / 16;      // 16-row groups: 4 of the diagonal block, then the block's own rows
-  constexpr int GW = NG / 4;                // of which per wavefront
+  constexpr int NG = (kNB + kTR) / 16;      // 16-row groups, one per wavefront: 4 of the diagonal block, then the block's own rows
   constexpr int S = kNB + kTR + 16;         // column stride: the 4 columns an operand load touches fall on distinct banks
+  constexpr int NWV = kPT / 64;
+  static_assert(NG == NWV && kTR == 64, "one row group per wavefront, one own row per lane");
   __shared__ double P[kNB * S];
   if (stopped(A.stop)) return;
   double* __restrict__ L = A.L + (int64_t)blockIdx.y * A.Lstride;
@@ -349,120 +428,131 @@ __global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t kbeg, int32_t
   // rows and columns past the front are clamped onto its last ones: what is
   // computed for them is never stored
   const int last = rows - 1;
-  int64_t ra[4], rb[GW];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) ra[c] = min(k0 + c * 16 + lr, last);
-#pragma unroll
-  for (int i = 0; i < GW; ++i) {
-    const int g = wv + 4 * i;
-    rb[i] = min(g < 4 ? k0 + g * 16 + lr : r0 + (g - 4) * 16 + lr, last);
-  }
-  dbl4 x[4][GW];
+  const int row = min(wv < 4 ? k0 + wv * 16 + lr : r0 + (wv - 4) * 16 + lr, last);
+  dbl4 x[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t col = (int64_t)min(k0 + c * 16 + lk + 4 * e, A.p - 1) * ld;
+    for (int e = 0; e < 4; ++e) x[c][e] = L[(int64_t)min(k0 + c * 16 + lk + 4 * e, A.p - 1) * ld + row];
+  // the columns before, 64 at a time through LDS, the next 64 loaded while the
+  // matrix cores work on these; in the blocks of the recursive elimination
+  // order (the 128 first ones, then 64: k0 - kbeg is 0, 64, 128 or 192), each
+  // block's product summed by itself and then subtracted; formed transposed
+  // (see k_update)
+  if (k0 > kbeg) {
+    // thread: row tid % 128 of the 64 + 64 rows, columns tid / 128 + 4 i
+    const int sr = tid & 127, sc = tid >> 7;
+    const double* ps = L + (int64_t)(kbeg + sc) * ld + min(sr < kNB ? k0 + sr : r0 + sr - kNB, last);
+    double v[16];
+    auto fetch = [&]() {
 #pragma unroll
-      for (int i = 0; i < GW; ++i) x[c][i][e] = L[col + rb[i]];
-    }
-  // the columns before, in the blocks of the recursive elimination order (the
-  // 128 first ones, then 64), each block's product summed by itself and then
-  // subtracted; formed transposed (see k_update)
-  for (int k = kbeg; k < k0;) {
-    const int ke = k + ((k0 - k) & ~127 ? 128 : 64);  // k0 - kbeg is 0, 64, 128 or 192
-    dbl4 acc[4][GW];
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int i = 0; i < GW; ++i) acc[c][i] = (dbl4){0.0, 0.0, 0.0, 0.0};
-    for (; k < ke; k += 16) {
-      double a[4][4], b[4][GW];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t col = (int64_t)(k + 4 * q + lk) * ld;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) a[q][c] = L[col + ra[c]];
-#pragma unroll
-        for (int i = 0; i < GW; ++i) b[q][i] = L[col + rb[i]];
+      for (int i = 0; i < 16; ++i) {
+        v[i] = *ps;
+        ps += 4 * ld;
       }
+    };
+    dbl4 acc[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+    for (int c = 0; c < 4; ++c) acc[c] = (dbl4){0.0, 0.0, 0.0, 0.0};
+    auto mul = [&](auto nc) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+      for (int k4 = 0; k4 < 16; ++k4) {
+        const double* col = P + (4 * k4 + lk) * S + lr;
+        const double bw = col[wv * 16];
 #pragma unroll
-          for (int i = 0; i < GW; ++i)
-            acc[c][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q][c], b[q][i], acc[c][i], 0, 0, 0);
-    }
+        for (int c = 0; c < nc(); ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(col[c * 16], bw, acc[c], 0, 0, 0);
+      }
+    };
+    fetch();
+    for (int k = kbeg; k < k0; k += 64) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+      for (int i = 0; i < 16; ++i) P[(sc + 4 * i) * S + sr] = v[i];
+      __syncthreads();
+      if (k + 64 < k0) fetch();
+      // the diagonal block's groups above its diagonal are not needed
+      if (wv == 0) mul(std::integral_constant<int, 1>());
+      else if (wv == 1) mul(std::integral_constant<int, 2>());
+      else if (wv == 2) mul(std::integral_constant<int, 3>());
+      else mul(std::integral_constant<int, 4>());
+      __syncthreads();
+      if (k + 64 == k0 || k + 64 - kbeg == 128) {
 #pragma unroll
-      for (int i = 0; i < GW; ++i) x[c][i] -= acc[c][i];
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int i = 0; i < GW; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + (wv + 4 * i) * 16 + lr] = x[c][i][e];
-  __syncthreads();
-  double* Dq = A.D + (int64_t)blockIdx.y * A.Dstride + (int64_t)(k0 / kNB) * kNB * kNB;
-  for (int jb = 0; jb * 16 < kb; ++jb) {
-    // this lane's row of the tile: a diagonal row, or one of the rows below
-    const int row = lane < 16 ? jb * 16 + lane : (jb + 1) * 16 + wv * 48 + lane - 16;
-    const bool in = row < kNB + kTR;
-    double a[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) a[j] = in ? P[(jb * 16 + j) * S + row] : 0.0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      if (jb * 16 + k < kb) {
-        double d = lane_bcast(a[k], k);
-        if (!(d > tol)) {
-          d = repl;
-          if (tid == 0 && blockIdx.x == 0) atomicAdd(npert, 1);
+        for (int c = 0; c < 4; ++c) {
+          x[c] -= acc[c];
+          acc[c] = (dbl4){0.0, 0.0, 0.0, 0.0};
         }
-        double s, r;
-        sqrt_recip(d, s, r);
-        a[k] = lane == k ? s : a[k] * r;
-#pragma unroll
-        for (int j = k + 1; j < 16; ++j) a[j] = fma(-a[k], lane_bcast(a[k], j), a[j]);
       }
     }
-    // the rows below the 16 to LDS for the columns to the right.  What is
-    // done with goes to memory: the rows' solution to the front, the 16
-    // diagonal rows (the same in every block and wavefront; LDS keeps the
-    // unfactored ones, which a slower wavefront may not have read yet) and
-    // the diagonal block's rows below them once
-    const int gi = r0 + row - kNB;
+  }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int c = jb * 16 + j;
-      if (in && lane >= 16) P[c * S + row] = a[j];
-      if (c < kb) {
-        if (in && row >= kNB && gi < rows) L[(int64_t)(k0 + c) * ld + gi] = a[j];
-        if (blockIdx.x == 0 && row < kb && row >= c && (lane >= 16 || wv == 0)) Dq[(int64_t)c * kb + row] = a[j];
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + wv * 16 + lr] = x[c][e];
+  __syncthreads();
+  PivotRule rule;
+  rule.tol = tol;
+  sqrt_recip(repl, rule.s_repl, rule.r_repl);
+  int bad = 0;  // static pivots
+  const int nb = (kb + 15) / 16;
+  constexpr int CW = (kNB + kTR - 16 + 47) / 48;  // wavefronts that hold rows in the column phase
+  for (int jb = 0; jb < nb; ++jb) {
+    // one 16 x 16 tile of the columns to the right, on or below the diagonal:
+    // column group c, row group g, its update by the 16 columns of block b
+    auto tile = [&](int b, int c, int g) {
+      dbl4 y;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = -P[(c * 16 + lk + 4 * e) * S + g * 16 + lr];
+#pragma unroll
+      for (int k4 = 0; k4 < 4; ++k4) {
+        const double* col = P + (b * 16 + 4 * k4 + lk) * S;
+        y = __builtin_amdgcn_mfma_f64_16x16x4f64(col[c * 16 + lr], col[g * 16 + lr], y, 0, 0, 0);
       }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + g * 16 + lr] = -y[e];
+    };
+    // the column phase: this lane's row of the tile is a diagonal row, or one
+    // of the rows below
+    double a[16];
+    const int t = lane < 16 ? jb * 16 + lane : (jb + 1) * 16 + wv * 48 + lane - 16;
+    if (wv < CW) {
+      const bool in = t < kNB + kTR;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) a[j] = in ? P[(jb * 16 + j) * S + t] : 0.0;
+      // columns past kb are carried along, and used by nothing
+      eliminate16(a, lane, kb - jb * 16, rule, bad);
+      if (in && lane >= 16) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) P[(jb * 16 + j) * S + t] = a[j];
+      }
+    } else if (jb > 0) {
+      // meanwhile the other wavefronts give the columns right of this block
+      // their update by the block before
+      int q = wv - CW;
+      for (int c = jb + 1; c < nb; ++c)
+        for (int g = c; g < NG; ++g, q = q == 0 ? NWV - CW - 1 : q - 1)
+          if (q == 0) tile(jb - 1, c, g);
     }
     __syncthreads();
-    // the columns to the right: 16 x 16 tiles on and below the diagonal
-    const int nc = 3 - jb;  // column groups left
-    for (int t = wv; t < nc * (NG - 1 - jb); t += 4) {
-      const int c = jb + 1 + t % nc, g = jb + 1 + t / nc;
-      if (g < c) continue;
-      dbl4 x;
+    // the 16 diagonal rows are the same in every wavefront, and a slower one
+    // may only now have read the unfactored ones
+    if (wv == 0 && lane < 16) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = -P[(c * 16 + lk + 4 * e) * S + g * 16 + lr];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double* col = P + (jb * 16 + 4 * q + lk) * S;
-        x = __builtin_amdgcn_mfma_f64_16x16x4f64(col[c * 16 + lr], col[g * 16 + lr], x, 0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) P[(c * 16 + lk + 4 * e) * S + g * 16 + lr] = -x[e];
+      for (int j = 0; j < 16; ++j) P[(jb * 16 + j) * S + t] = a[j];
     }
+    if (jb + 1 < nb && jb + 1 + wv < NG) tile(jb, jb + 1, jb + 1 + wv);
     __syncthreads();
   }
+  // the rows' solution to the front, the diagonal block once
+#pragma unroll 4
+  for (int c = wv; c < kb; c += NWV)
+    if (r0 + lane < rows) L[(int64_t)(k0 + c) * ld + r0 + lane] = P[c * S + kNB + lane];
+  if (blockIdx.x == 0) {
+    double* Dq = A.D + (int64_t)blockIdx.y * A.Dstride + (int64_t)(k0 / kNB) * kNB * kNB;
+#pragma unroll 4
+    for (int c = wv; c < kb; c += NWV)
+      if (lane >= c && lane < kb) Dq[(int64_t)c * kb + lane] = P[c * S + lane];
+  }
+  if (bad && tid == 0 && blockIdx.x == 0) atomicAdd(npert, bad);
 }
 
 // Trailing update after a panel: C -= P P^T on the lower part of rows
@@ -475,29 +565,34 @@ __global__ void __launch_bounds__(256) k_panel(FrontArg A, int32_t kbeg, int32_t
 // 16 consecutive rows of a column of the column-major front; every entry is
 // one ascending chain over the panel's columns, whatever the tile.
 //
-// What bounds it is keeping the matrix cores issued: one wavefront per SIMD
-// reaches half their rate, so a block in its first loads or its last
-// read-modify-write has to leave others running.  64 x 64 tiles of 4
-// wavefronts (32 x 32 each, 63 VGPRs) with 8 panel columns per LDS round (20 KB
-// for both buffers) leave 7 blocks on a CU: 58 TFLOP/s at 4323 columns x 1024
-// panel columns x 8 periods, 47 at 4114 x 204 x 8, 55 at 2976 x 1024 x 2; 128 x
-// 128 tiles of 4 wavefronts (2 blocks on a CU) reached 51, 33 and 37, of 8
-// wavefronts 60, 45 and 43, and twice the time on launches of few tiles.
-// Tiles are taken in column groups of kGroup, row by row, and each XCD gets a
-// contiguous run of (period, tile) items, so that the tiles running side by
-// side share panel slices in its L2.
+// What bounds a large launch is keeping the matrix cores issued: a block in its
+// first loads or its last read-modify-write has to leave others running.  64 x
+// 64 tiles of 4 wavefronts (32 x 32 each, 63 VGPRs) with 8 panel columns per
+// LDS round (20 KB for both buffers) leave 7 blocks on a CU: 58 TFLOP/s at
+// 4323 columns x 1024 panel columns x 8 periods, 47 at 4114 x 204 x 8, 55 at
+// 2976 x 1024 x 2; 128 x 128 tiles of 4 wavefronts (2 blocks on a CU) reached
+// 51, 33 and 37, of 8 wavefronts 60, 45 and 43, and twice the time on launches
+// of few tiles.  Tiles are taken in column groups of kGroup, row by row, and
+// each XCD gets a contiguous run of (period, tile) items, so that the tiles
+// running side by side share panel slices in its L2.
+// What bounds a launch that leaves CUs without a block is the latency of one
+// block: 32 x 32 tiles, a quarter of the matrix-core chain, and 64 columns per
+// round, so that few round trips to memory follow one another (see
+// launch_update).
 constexpr int kGroup = 8;
-__global__ void __launch_bounds__(256, 6) k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
-  constexpr int KC = 8;              // panel columns per LDS round
-  constexpr int S = kTile + 16;      // column stride: an operand load's 4 columns fall on distinct banks
-  constexpr int CS = 256 / kTile;    // columns a load of the block covers
+template <int TM, int KC>
+__global__ void __launch_bounds__(256, TM == 64 ? 6 : 1)
+k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
+  constexpr int S = TM + 16;         // column stride: an operand load's 4 columns fall on distinct banks
+  constexpr int CS = 256 / TM;       // columns a load of the block covers
   constexpr int NLD = KC / CS;       // loads per thread and side
+  constexpr int W = TM / 2, N = W / 16;  // a wavefront's quarter, in rows and 16-row groups
   // two LDS buffers: the next round is loaded into registers while the
   // matrix cores work on the current one
   __shared__ double Pi[2][KC * S], Pj[2][KC * S];
   if (stopped(A.stop)) return;
   const int rows = A.p + A.u, cend = min(cmax, rows);
-  const int R = (rows - r0 + kTile - 1) / kTile, Cn = (cend - r0 + kTile - 1) / kTile;
+  const int R = (rows - r0 + TM - 1) / TM, Cn = (cend - r0 + TM - 1) / TM;
   // blocks are dealt round-robin to the 8 XCDs in launch order
   const int ntl = (int)gridDim.x, total = ntl * (int)gridDim.y;
   int item = (int)(blockIdx.y * gridDim.x + blockIdx.x);
@@ -526,20 +621,20 @@ __global__ void __launch_bounds__(256, 6) k_update(FrontArg A, int32_t k0, int32
   double* L = A.L + (int64_t)per * A.Lstride;
   double* U = A.U + (int64_t)per * A.Ustride;
   const int64_t ld = A.ld;
-  const int i0 = r0 + ti * kTile, j0 = r0 + tj * kTile;
+  const int i0 = r0 + ti * TM, j0 = r0 + tj * TM;
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wr = wv & 1, wc = wv >> 1;  // the wavefront's 32-row / 32-column quarter
+  const int wr = wv & 1, wc = wv >> 1;  // the wavefront's quarter
   // a quarter wholly above the diagonal or right of the region contributes nothing
-  const bool skip = i0 + wr * 32 + 31 < j0 + wc * 32 || j0 + wc * 32 >= cend;
-  dbl4 acc[2][2];
+  const bool skip = i0 + wr * W + W - 1 < j0 + wc * W || j0 + wc * W >= cend;
+  dbl4 acc[N][N];
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < N; ++c)
 #pragma unroll
-    for (int r = 0; r < 2; ++r) acc[c][r] = (dbl4){0.0, 0.0, 0.0, 0.0};
+    for (int r = 0; r < N; ++r) acc[c][r] = (dbl4){0.0, 0.0, 0.0, 0.0};
   const int lr = lane & 15, lk = lane >> 4;
   // this thread's row of both slices (rows past the front are clamped onto
   // its last one: what is computed for them is never stored)
-  const int rr = tid % kTile, lc = tid / kTile;
+  const int rr = tid % TM, lc = tid / TM;
   const double* pi = L + (int64_t)(k0 + lc) * ld + min(i0 + rr, rows - 1);
   const double* pj = L + (int64_t)(k0 + lc) * ld + min(j0 + rr, rows - 1);
   const int64_t step = CS * ld;
@@ -577,18 +672,18 @@ __global__ void __launch_bounds__(256, 6) k_update(FrontArg A, int32_t k0, int32
     const bool more = l0 + KC < kb;
     if (more) fetch(l0 + KC);
     if (!skip) {
-#pragma unroll
+#pragma unroll 4
       for (int k4 = 0; k4 < KC; k4 += 4) {
-        double aj[2], bi[2];
+        double aj[N], bi[N];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          aj[q] = Pj[buf][(k4 + lk) * S + wc * 32 + q * 16 + lr];
-          bi[q] = Pi[buf][(k4 + lk) * S + wr * 32 + q * 16 + lr];
+        for (int q = 0; q < N; ++q) {
+          aj[q] = Pj[buf][(k4 + lk) * S + wc * W + q * 16 + lr];
+          bi[q] = Pi[buf][(k4 + lk) * S + wr * W + q * 16 + lr];
         }
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < N; ++c)
 #pragma unroll
-          for (int r = 0; r < 2; ++r) acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(aj[c], bi[r], acc[c][r], 0, 0, 0);
+          for (int r = 0; r < N; ++r) acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(aj[c], bi[r], acc[c][r], 0, 0, 0);
       }
     }
     if (more) park(buf ^ 1);
@@ -597,13 +692,13 @@ __global__ void __launch_bounds__(256, 6) k_update(FrontArg A, int32_t k0, int32
   }
   if (skip) return;
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < N; ++c)
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int i = i0 + wr * 32 + r * 16 + lr;
+    for (int r = 0; r < N; ++r) {
+      const int i = i0 + wr * W + r * 16 + lr;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int j = j0 + wc * 32 + c * 16 + lk + 4 * e;
+        const int j = j0 + wc * W + c * 16 + lk + 4 * e;
         if (i >= rows || j >= cend || i < j) continue;
         if (j < A.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
         else U[(int64_t)(j - A.p) * A.ldU + (i - A.p)] -= acc[c][r][e];
@@ -981,9 +1076,6 @@ struct opf_chol {
   double* gx = nullptr;
   bool use_graph = true;
   bool stop_on_pivot = false;  // skip the rest of a factorization after its first static pivot
-  // the library handle of the large trailing updates (NULL: every update on
-  // k_update); atomics off, so its products are reproducible run to run
-  rocblas_handle blas = nullptr;
   std::vector<void*> allocs;
   double flops = 0.0, flops_int = 0.0;
   int64_t factor_entries = 0, arena_entries = 0;
@@ -1113,49 +1205,22 @@ int setup_device(opf_chol* F, CholInst& C) {
   return OPF_OK;
 }
 
-// A trailing update through the library's strided-batched GEMM, every call
-// batched over the nt periods by their strides.  The lower part of the
-// target columns is covered by column blocks of kBlasCols: block [j, j+w)
-// takes rows [j, end) in one product, so it also writes the upper part of
-// its w x w diagonal block (no kernel reads above the diagonal of a factor
-// or update block).  The library's SYRK measured 2-12 TFLOP/s on these
-// shapes against 40-70 for GEMM.  Columns in the factor block first, then
-// those in the update block.
-int blas_update(rocblas_handle h, const FrontArg& A, int nt, int k0, int kb, int r0, int cend, hipStream_t st) {
-  const int rows = A.p + A.u;
-  const int64_t ld = A.ld;
-  if (rocblas_set_stream(h, st) != rocblas_status_success) return api_fail(OPF_EHIP, "chol: rocblas_set_stream failed");
-  const double* P = A.L + (int64_t)k0 * ld;  // panel: row r of column k0 + c at P[c * ld + r]
-  // columns [c, c + n) of the target, rows [c, rows), at C (leading dimension ldc, period stride sc)
-  auto lower = [&](int c, int n, double* C, int64_t ldc, int64_t sc) -> int {
-    const double mone = -1.0, one = 1.0;
-    for (int j = 0; j < n; j += kBlasCols) {
-      const int w = std::min(kBlasCols, n - j);
-      const double* Aj = P + c + j;
-      if (rocblas_dgemm_strided_batched(h, rocblas_operation_none, rocblas_operation_transpose, rows - c - j, w, kb,
-                                        &mone, Aj, (rocblas_int)ld, A.Lstride, Aj, (rocblas_int)ld, A.Lstride, &one,
-                                        C + (int64_t)j * ldc + j, (rocblas_int)ldc, sc, nt) != rocblas_status_success)
-        return api_fail(OPF_EHIP, "chol: rocblas_dgemm_strided_batched failed");
-    }
-    return OPF_OK;
-  };
-  const int n1 = std::min(A.p, cend) - r0;  // target columns in the factor block
-  if (n1 > 0) CHK(lower(r0, n1, A.L + (int64_t)r0 * ld + r0, ld, A.Lstride));
-  const int c0 = std::max(r0, A.p);
-  const int n3 = cend - c0;  // target columns in the update block
-  if (n3 > 0) CHK(lower(c0, n3, A.U + (int64_t)(c0 - A.p) * A.ldU + (c0 - A.p), A.ldU, A.Ustride));
-  return OPF_OK;
-}
-
-int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, hipStream_t st, rocblas_handle h) {
+// Small tiles where 64 x 64 ones would leave CUs without a block: at 256
+// panel columns, 144 columns and 544 rows of two fronts 9.6 us against 20.
+int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, hipStream_t st) {
   const int rows = A.p + A.u;
   const int cend = std::min(cmax, rows);
   if (r0 >= rows || cend <= r0) return OPF_OK;
-  if (h && kb >= kBlasMinCols && rows - r0 >= kBlasMinRows) return blas_update(h, A, nt, k0, kb, r0, cend, st);
-  const int64_t R = (rows - r0 + kTile - 1) / kTile, Cn = (cend - r0 + kTile - 1) / kTile;
-  const int64_t ntiles = Cn * R - Cn * (Cn - 1) / 2;
-  if (ntiles > 0x7fffffff) return api_fail(OPF_EINVAL, "chol: front too large");
-  hipLaunchKernelGGL(k_update, dim3((unsigned)ntiles, nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
+  auto tiles = [&](int64_t tm) {
+    const int64_t R = (rows - r0 + tm - 1) / tm, Cn = (cend - r0 + tm - 1) / tm;
+    return Cn * R - Cn * (Cn - 1) / 2;
+  };
+  const int64_t n = tiles(kTile);
+  if (n > 0x7fffffff) return api_fail(OPF_EINVAL, "chol: front too large");
+  if (n * nt < kFewTiles)
+    hipLaunchKernelGGL((k_update<32, 64>), dim3((unsigned)tiles(32), nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
+  else
+    hipLaunchKernelGGL((k_update<kTile, 8>), dim3((unsigned)n, nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
   LAUNCH_OK("chol update");
   return OPF_OK;
 }
@@ -1165,40 +1230,38 @@ int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, h
 // wider blocks recursively: the first half, the first half's update of the
 // second half's columns, the second half.  The trailing columns are left to
 // the caller.
-int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl, int32_t* npert, hipStream_t st,
-                rocblas_handle bh) {
+int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl, int32_t* npert, hipStream_t st) {
   const int rows = A.p + A.u;
   if (k >= A.p) return OPF_OK;
   if (w == kWide) {
     for (int k0 = k; k0 < std::min(k + kWide, A.p); k0 += kNB) {
       const int kb = std::min(kNB, A.p - k0);
-      hipLaunchKernelGGL(k_panel, dim3(std::max(1, (rows - k0 - kb + kTR - 1) / kTR), nt), dim3(256), 0, st, A, k, k0,
+      hipLaunchKernelGGL(k_panel, dim3(std::max(1, (rows - k0 - kb + kTR - 1) / kTR), nt), dim3(kPT), 0, st, A, k, k0,
                          kb, tol, repl, npert);
       LAUNCH_OK("chol panel");
     }
     return OPF_OK;
   }
   const int h = w / 2;
-  CHK(factor_cols(A, nt, k, h, tol, repl, npert, st, bh));
+  CHK(factor_cols(A, nt, k, h, tol, repl, npert, st));
   const int kh = std::min(h, A.p - k);
   const int k2 = std::min(h, A.p - k - kh);
   if (k2 > 0) {
     const int r1 = k + kh;
-    CHK(launch_update(A, nt, k, kh, r1, r1 + k2, st, bh));
-    CHK(factor_cols(A, nt, r1, h, tol, repl, npert, st, bh));
+    CHK(launch_update(A, nt, k, kh, r1, r1 + k2, st));
+    CHK(factor_cols(A, nt, r1, h, tol, repl, npert, st));
   }
   return OPF_OK;
 }
 
-int factor_front(const FrontArg& A, int nt, double tol, double repl, int32_t* npert, hipStream_t st,
-                 rocblas_handle bh) {
+int factor_front(const FrontArg& A, int nt, double tol, double repl, int32_t* npert, hipStream_t st) {
   const int rows = A.p + A.u;
   // kStep-column steps, each factored recursively, then one trailing update
   // with the kStep-wide panel
   for (int k0 = 0; k0 < A.p; k0 += kStep) {
-    CHK(factor_cols(A, nt, k0, kStep, tol, repl, npert, st, bh));
+    CHK(factor_cols(A, nt, k0, kStep, tol, repl, npert, st));
     const int kb = std::min(kStep, A.p - k0);
-    CHK(launch_update(A, nt, k0, kb, k0 + kb, rows, st, bh));
+    CHK(launch_update(A, nt, k0, kb, k0 + kb, rows, st));
   }
   return OPF_OK;
 }
@@ -1276,7 +1339,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
     A.D = C.Dc + (int64_t)t * C.dcsize;
     A.Dstride = nt > 1 ? (int64_t)(t2 - t) * C.dcsize : 0;
     A.stop = C.dev.stop;
-    return factor_front(A, nt, tol, repl, npert, F->cs, F->blas);
+    return factor_front(A, nt, tol, repl, npert, F->cs);
   };
   auto chain_steps = [&](bool all) -> int {
     for (;;) {
@@ -1347,7 +1410,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
         A.D = C.Df + (int64_t)t0 * C.dsize + C.doff[s];
         A.Dstride = C.dsize;
         A.stop = C.dev.stop;
-        CHK(factor_front(A, nt, tol, repl, npert, fst, nullptr));
+        CHK(factor_front(A, nt, tol, repl, npert, fst));
       }
       for (int k = 0; k < nfs; ++k)
         if (hipEventRecord(F->join_ev[k], F->fs[k]) != hipSuccess ||
@@ -1597,16 +1660,6 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
         opf_chol_destroy(F);
         return api_fail(OPF_EHIP, "chol: stream or event creation failed");
       }
-      // OPF_CHOL_BLAS=0 keeps every trailing update on k_update
-      const char* eb = std::getenv("OPF_CHOL_BLAS");
-      if (!(eb && eb[0] == '0')) {
-        if (rocblas_create_handle(&F->blas) != rocblas_status_success ||
-            rocblas_set_atomics_mode(F->blas, rocblas_atomics_not_allowed) != rocblas_status_success ||
-            rocblas_set_pointer_mode(F->blas, rocblas_pointer_mode_host) != rocblas_status_success) {
-          opf_chol_destroy(F);
-          return api_fail(OPF_EHIP, "chol: rocBLAS handle creation failed");
-        }
-      }
     } else {
       for (auto& C : F->inst) {
         C.chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>(C.plan.T, arena_budget() / (C.plan.usize * 8)));
@@ -1636,7 +1689,6 @@ void opf_chol_destroy(opf_chol* chol) {
     if (chol->join_ev[k]) (void)hipEventDestroy(chol->join_ev[k]);
     if (chol->fs[k]) (void)hipStreamDestroy(chol->fs[k]);
   }
-  if (chol->blas) (void)rocblas_destroy_handle(chol->blas);
   if (chol->cs) (void)hipStreamDestroy(chol->cs);
   if (chol->gs) (void)hipStreamDestroy(chol->gs);
   release(chol);
