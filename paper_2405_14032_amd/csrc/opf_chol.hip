@@ -39,7 +39,7 @@ namespace {
 constexpr int kSmall = 64;   // largest front factored in LDS by one wavefront
 constexpr int kNB = 64;      // panel width of the blocked fronts
 constexpr int kTile = 64;    // trailing-update tile
-constexpr int kChainCols = 128;  // column chunk of the chain's L21 z
+constexpr int kChainCols = 128;  // columns summed together in the chain's L21 z (a multiple of kNB)
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
 constexpr int kWide = 256;       // columns whose panels update each other within their launches
 constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 ones (one block per CU)
@@ -54,24 +54,33 @@ struct CDev {
   const int32_t* stop;  // the static-pivot count when the factor stops at the first one, else NULL
 };
 
-// One front as the blocked kernels see it: factor block (ld x p, first p
-// columns of the front) and update block (ldU x u), per-period strides.
-struct FrontArg {
-  double* L;
-  int64_t Lstride;
-  int32_t ld, p, u;
-  double* U;
-  int64_t Ustride;
-  int32_t ldU;
-  double* D;  // the factored diagonal blocks (see diag_size)
-  int64_t Dstride;
+// One front as the blocked kernels see it: p pivots, u update rows and where
+// its parts start in a period's storage: factor block ((p+u) x p, leading
+// dimension ld), diagonal
+// blocks (see diag_size), update block (u x u), update vector of the solves,
+// row list; its first elimination position and its node.
+struct FrontRec {
+  int64_t L, D, U, W, R;
+  int32_t p, u, ld, f, s;
+};
+
+// A batch of fronts for one launch (front blockIdx.z of rec, in falling order
+// of p: the ones that still have columns come first) over several periods
+// (blockIdx.y): the first period's storage and the strides from one to the
+// next.
+struct Fronts {
+  const FrontRec* rec;
+  double *L, *D, *U;
+  int64_t sL, sD, sU;
   const int32_t* stop;  // as CDev::stop
 };
 
 // The factored 64 x 64 diagonal blocks of a blocked front live apart from
-// its factor block, one after the other, the last one kb x kb (column-major,
-// leading dimension kb): every block of a panel launch reads the unfactored
-// block from the front while one of them stores the factored one.
+// its factor block, one after the other, the last one kb x kb (leading
+// dimension kb), the triangle mirrored: the forward solve wants its rows side
+// by side, the backward solve its columns.  Every block of a panel launch
+// reads the unfactored block from the front while one of them stores the
+// factored one.
 __host__ __device__ __forceinline__ int64_t diag_size(int p) {
   const int64_t np = (p + kNB - 1) / kNB, kb = p - (np - 1) * kNB;
   return (np - 1) * kNB * kNB + kb * kb;
@@ -396,7 +405,7 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // Blocked front, one panel of kb <= 64 columns [k0, k0+kb): its update by the
 // columns [kbeg, k0) before it, its diagonal block's factorization and the
 // solve of the kTR rows of each block against it, in one launch.  Grid (row
-// blocks below the panel, at least one; periods).
+// blocks below the panel of the largest front, at least one; periods; fronts).
 //
 // What bounds it is latency: a front's panels follow one another, 64 serial
 // pivots each.  So every block repeats the diagonal block's work (64 rows
@@ -411,18 +420,20 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 // 31 us, and one matrix-core update launch per 64 columns, 16 us at least.)
 constexpr int kTR = 64;
 constexpr int kPT = 512;  // threads
-__global__ void __launch_bounds__(kPT) k_panel(FrontArg A, int32_t kbeg, int32_t k0, int32_t kb, double tol,
-                                               double repl, int32_t* __restrict__ npert) {
+__global__ void __launch_bounds__(kPT) k_panel(Fronts F, int32_t kbeg, int32_t k0, double tol, double repl,
+                                               int32_t* __restrict__ npert) {
   constexpr int NG = (kNB + kTR) / 16;      // 16-row groups, one per wavefront: 4 of the diagonal block, then the block's own rows
   constexpr int S = kNB + kTR + 16;         // column stride: the 4 columns an operand load touches fall on distinct banks
   constexpr int NWV = kPT / 64;
   static_assert(NG == NWV && kTR == 64, "one row group per wavefront, one own row per lane");
   __shared__ double P[kNB * S];
-  if (stopped(A.stop)) return;
-  double* __restrict__ L = A.L + (int64_t)blockIdx.y * A.Lstride;
-  const int64_t ld = A.ld;
-  const int rows = A.p + A.u;
+  const FrontRec f = F.rec[blockIdx.z];
+  const int rows = f.p + f.u, kb = min(kNB, f.p - k0);
   const int r0 = k0 + kb + (int)blockIdx.x * kTR;
+  if (blockIdx.x > 0 && r0 >= rows) return;
+  if (stopped(F.stop)) return;
+  double* __restrict__ L = F.L + (int64_t)blockIdx.y * F.sL + f.L;
+  const int64_t ld = f.ld;
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   // rows and columns past the front are clamped onto its last ones: what is
@@ -433,7 +444,7 @@ __global__ void __launch_bounds__(kPT) k_panel(FrontArg A, int32_t kbeg, int32_t
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[c][e] = L[(int64_t)min(k0 + c * 16 + lk + 4 * e, A.p - 1) * ld + row];
+    for (int e = 0; e < 4; ++e) x[c][e] = L[(int64_t)min(k0 + c * 16 + lk + 4 * e, f.p - 1) * ld + row];
   // the columns before, 64 at a time through LDS, the next 64 loaded while the
   // matrix cores work on these; in the blocks of the recursive elimination
   // order (the 128 first ones, then 64: k0 - kbeg is 0, 64, 128 or 192), each
@@ -547,17 +558,23 @@ __global__ void __launch_bounds__(kPT) k_panel(FrontArg A, int32_t kbeg, int32_t
   for (int c = wv; c < kb; c += NWV)
     if (r0 + lane < rows) L[(int64_t)(k0 + c) * ld + r0 + lane] = P[c * S + kNB + lane];
   if (blockIdx.x == 0) {
-    double* Dq = A.D + (int64_t)blockIdx.y * A.Dstride + (int64_t)(k0 / kNB) * kNB * kNB;
+    double* Dq = F.D + (int64_t)blockIdx.y * F.sD + f.D + (int64_t)k0 * kNB;
 #pragma unroll 4
     for (int c = wv; c < kb; c += NWV)
-      if (lane >= c && lane < kb) Dq[(int64_t)c * kb + lane] = P[c * S + lane];
+      if (lane >= c && lane < kb) {
+        const double v = P[c * S + lane];
+        Dq[c * kb + lane] = v;
+        Dq[lane * kb + c] = v;
+      }
   }
   if (bad && tid == 0 && blockIdx.x == 0) atomicAdd(npert, bad);
 }
 
-// Trailing update after a panel: C -= P P^T on the lower part of rows
-// [r0, p+u) x columns [r0, min(cmax, p+u)), P the panel columns [k0, k0+kb).
-// Columns < p live in the factor block, the others in the update block.
+// Trailing update after a panel of kb = min(w, p - k0) columns from k0 on, r0
+// = k0 + kb: C -= P P^T on the lower part of the rows from r0 on x the columns
+// from r0 on -- inner: the next w pivot columns only, else all of them.
+// Columns < p live in the factor block, the others in the update block.  Grid
+// (tiles of the largest front; periods; fronts).
 //
 // FP64 matrix cores: v_mfma_f64_16x16x4, lane l supplies A(l%16, l/16) and
 // B(l/16, l%16) and holds D(l/16 + 4r, l%16), r < 4.  The product is formed
@@ -582,7 +599,7 @@ __global__ void __launch_bounds__(kPT) k_panel(FrontArg A, int32_t kbeg, int32_t
 constexpr int kGroup = 8;
 template <int TM, int KC>
 __global__ void __launch_bounds__(256, TM == 64 ? 6 : 1)
-k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
+k_update(Fronts F, int32_t k0, int32_t w, int32_t inner) {
   constexpr int S = TM + 16;         // column stride: an operand load's 4 columns fall on distinct banks
   constexpr int CS = 256 / TM;       // columns a load of the block covers
   constexpr int NLD = KC / CS;       // loads per thread and side
@@ -590,8 +607,9 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
   // two LDS buffers: the next round is loaded into registers while the
   // matrix cores work on the current one
   __shared__ double Pi[2][KC * S], Pj[2][KC * S];
-  if (stopped(A.stop)) return;
-  const int rows = A.p + A.u, cend = min(cmax, rows);
+  const FrontRec f = F.rec[blockIdx.z];
+  const int rows = f.p + f.u, kb = min(w, f.p - k0), r0 = k0 + kb, cend = inner ? min(r0 + w, f.p) : rows;
+  if (cend <= r0) return;
   const int R = (rows - r0 + TM - 1) / TM, Cn = (cend - r0 + TM - 1) / TM;
   // blocks are dealt round-robin to the 8 XCDs in launch order
   const int ntl = (int)gridDim.x, total = ntl * (int)gridDim.y;
@@ -600,9 +618,11 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
   if (item < (q8 << 3)) item = (item & 7) * q8 + (item >> 3);
   const int per = item / ntl;
   int x = item % ntl, ti = 0, tj = 0;
+  if (x >= Cn * R - Cn * (Cn - 1) / 2) return;
+  if (stopped(F.stop)) return;
   for (int g = 0;; g += kGroup) {
-    // column group [g, g + w): a triangle of w rows, then full rows
-    const int w = min(kGroup, Cn - g), tri = w * (w + 1) / 2, cnt = tri + (R - g - w) * w;
+    // column group [g, g + gw): a triangle of gw rows, then full rows
+    const int gw = min(kGroup, Cn - g), tri = gw * (gw + 1) / 2, cnt = tri + (R - g - gw) * gw;
     if (x >= cnt) {
       x -= cnt;
       continue;
@@ -613,14 +633,14 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
       ti = g + i;
       tj = g + x;
     } else {
-      ti = g + w + (x - tri) / w;
-      tj = g + (x - tri) % w;
+      ti = g + gw + (x - tri) / gw;
+      tj = g + (x - tri) % gw;
     }
     break;
   }
-  double* L = A.L + (int64_t)per * A.Lstride;
-  double* U = A.U + (int64_t)per * A.Ustride;
-  const int64_t ld = A.ld;
+  double* L = F.L + (int64_t)per * F.sL + f.L;
+  double* U = F.U + (int64_t)per * F.sU + f.U;
+  const int64_t ld = f.ld;
   const int i0 = r0 + ti * TM, j0 = r0 + tj * TM;
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wr = wv & 1, wc = wv >> 1;  // the wavefront's quarter
@@ -700,8 +720,8 @@ k_update(FrontArg A, int32_t k0, int32_t kb, int32_t r0, int32_t cmax) {
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + wc * W + c * 16 + lk + 4 * e;
         if (i >= rows || j >= cend || i < j) continue;
-        if (j < A.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
-        else U[(int64_t)(j - A.p) * A.ldU + (i - A.p)] -= acc[c][r][e];
+        if (j < f.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
+        else U[(int64_t)(j - f.p) * f.u + (i - f.p)] -= acc[c][r][e];
       }
     }
 }
@@ -781,26 +801,27 @@ __global__ void __launch_bounds__(64) k_fwd_small(CDev D, const int32_t* __restr
   else if (i < f) Wt[D.node_woff[s] + i - p] = v[i];
 }
 
-// Forward, large front, step 1: pull the children's update vectors (pivot
-// rows subtracted from Y in place, other rows summed into this front's W).
-__global__ void __launch_bounds__(256) k_fwd_pull(CDev D, int32_t s, double* __restrict__ Y,
+// Forward, large fronts of one level, step 1: pull the children's update
+// vectors (pivot rows subtracted from Y in place, other rows summed into this
+// front's W).  Grid (periods; 1; fronts).
+__global__ void __launch_bounds__(256) k_fwd_pull(CDev D, const FrontRec* __restrict__ rec, double* __restrict__ Y,
                                                   double* __restrict__ W) {
+  const FrontRec f = rec[blockIdx.z];
   const int t = (int)blockIdx.x;
-  const int p = D.node_p[s], u = D.node_u[s], fs = D.node_f[s];
-  double* Yt = Y + (int64_t)t * D.n_p;
+  double* Ys = Y + (int64_t)t * D.n_p + f.f;
   double* Wt = W + (int64_t)t * D.wsize;
-  double* Ws = Wt + D.node_woff[s];
-  for (int a = (int)threadIdx.x; a < u; a += (int)blockDim.x) Ws[a] = 0.0;
+  double* Ws = Wt + f.W;
+  for (int a = (int)threadIdx.x; a < f.u; a += (int)blockDim.x) Ws[a] = 0.0;
   __syncthreads();
-  for (int64_t q = D.kid_ptr[s]; q < D.kid_ptr[s + 1]; ++q) {
+  for (int64_t q = D.kid_ptr[f.s]; q < D.kid_ptr[f.s + 1]; ++q) {
     const int c = D.kids[q];
     const int uc = D.node_u[c];
     const int32_t* rel = D.rel + D.row_ptr[c];
     const double* Wc = Wt + D.node_woff[c];
     for (int a = (int)threadIdx.x; a < uc; a += (int)blockDim.x) {
       const int r = rel[a];
-      if (r < p) Yt[fs + r] -= Wc[a];
-      else Ws[r - p] += Wc[a];
+      if (r < f.p) Ys[r] -= Wc[a];
+      else Ws[r - f.p] += Wc[a];
     }
     __syncthreads();
   }
@@ -822,166 +843,170 @@ __global__ void __launch_bounds__(256) k_fwd_root_pull(CDev D, const int32_t* __
   }
 }
 
-// Forward triangle L11 z = y (pivot part of one front), one panel
-// [k0, k0+kb) per launch, grid (row blocks, periods): every block solves
-// the panel's diagonal triangle (staged in LDS, one wavefront, the solved
-// entry broadcast across lanes) from y, block 0 stores the solution in z,
-// and each block subtracts the panel's contribution from its 256 rows of y
-// below the panel.  y's panel entries are only read here and z is only
-// written, so the blocks of one launch never touch an entry another block
-// writes.
-__global__ void __launch_bounds__(256) k_fwd_panel(const double* __restrict__ Lb, int64_t Lstride,
-                                                   const double* __restrict__ Db, int64_t Dstride, int32_t ld,
-                                                   int32_t p, int32_t k0, double* __restrict__ yb,
-                                                   double* __restrict__ zb, int64_t ystride) {
-  __shared__ double Tr[64 * 65];
+// A batch of fronts as the blocked solve kernels see it (front blockIdx.z of
+// rec, batch entry blockIdx.y: a period, or a pg front of the chain): factor
+// and diagonal blocks, right-hand side / solution y, forward solution z,
+// update vector w and its running sums v, each with its stride.
+struct Tri {
+  const FrontRec* rec;
+  const double *L, *D;
+  double *y, *z, *w, *v;
+  int64_t sL, sD, sy, sw, sv;
+};
+
+// The 64 x 64 triangle of a panel, solved by one wavefront for the entry v of
+// each lane (rows past kb: v = 0): lane i holds row i of the symmetric
+// diagonal block in registers (forward: its entries left of the diagonal,
+// backward those right of it, which are column i below the diagonal), and step
+// k broadcasts entry k.  64 dependent steps of a broadcast, a product with the
+// pivot's reciprocal and an update bound a panel launch of the solves.
+template <bool FWD>
+__device__ __forceinline__ double solve64(const double* __restrict__ D, int kb, int lane, double v) {
+  double t[64], x = 0.0;
+#pragma unroll
+  for (int k = 0; k < 64; ++k) t[k] = (k < kb && lane < kb && (FWD ? k < lane : k > lane)) ? D[k * kb + lane] : 0.0;
+  const double r = lane < kb ? 1.0 / D[lane * kb + lane] : 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = FWD ? q : 3 - q;
+    if (b * 16 >= kb) continue;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int k = b * 16 + (FWD ? j : 15 - j);
+      const double xk = lane_bcast(v, k) * lane_bcast(r, k);
+      x = lane == k ? xk : x;
+      v = fma(-t[k], xk, v);  // of use to the lanes still to come
+    }
+  }
+  return x;
+}
+
+// Forward, one panel [k0, k0+kb) of each front per launch, grid (row blocks
+// below the panel of the largest front, at least one; batch; fronts): a fifth
+// wavefront of every block solves the panel's triangle (solve64) while the
+// four others load their rows of the panel; block 0 stores the solution in z,
+// and each block gives its 256 rows below the panel their products: pivot rows
+// subtract theirs from y, update rows carry one running sum over the panels in
+// v.  y's panel entries are only read here and z is only written, so the
+// blocks of one launch never touch an entry another block writes.
+// chunk 0 (interior fronts): the sum over all columns goes onto w at the last
+// panel.  chunk > 0 (the pg chain, a multiple of 64): the sums over chunk
+// columns are added up in w one after the other, from 0; at the last panel w
+// is also subtracted from next, the right-hand side of the chain neighbour
+// (stride sn), unless next is NULL.
+__global__ void __launch_bounds__(320) k_fwd_panel(Tri A, int32_t k0, int32_t chunk, double* __restrict__ next,
+                                                   int64_t sn) {
   __shared__ double xs[64];
-  const double* L = Lb + (int64_t)blockIdx.y * Lstride;
-  double* y = yb + (int64_t)blockIdx.y * ystride;
-  double* z = zb + (int64_t)blockIdx.y * ystride;
+  const FrontRec f = A.rec[blockIdx.z];
+  const int kb = min(kNB, f.p - k0), rows = f.p + f.u;
   const int tid = (int)threadIdx.x;
-  const int kb = min(64, p - k0);
-  // this thread's row of the panel below the triangle, loaded first so that
-  // its latency overlaps the triangle (summed in column order afterwards)
-  const int i = k0 + kb + (int)blockIdx.x * (int)blockDim.x + tid;
-  const bool row = i < p;
+  const int i = k0 + kb + (int)blockIdx.x * 256 + tid;
+  if (blockIdx.x > 0 && i - tid >= rows) return;
+  const double* L = A.L + (int64_t)blockIdx.y * A.sL + f.L;
+  double* y = A.y + (int64_t)blockIdx.y * A.sy + f.f;
+  if (tid >= 256) {
+    const int lane = tid - 256;
+    const double x = solve64<true>(A.D + (int64_t)blockIdx.y * A.sD + f.D + (int64_t)k0 * kNB, kb, lane,
+                                   lane < kb ? y[k0 + lane] : 0.0);
+    xs[lane] = x;
+    if (blockIdx.x == 0 && lane < kb) A.z[(int64_t)blockIdx.y * A.sy + f.f + k0 + lane] = x;
+    __syncthreads();
+    return;
+  }
+  const bool row = i < rows;
+  const double* Li = L + (int64_t)k0 * f.ld + i;
   double rv[64];
 #pragma unroll
-  for (int l = 0; l < 64; ++l) rv[l] = (row && l < kb) ? L[(int64_t)(k0 + l) * ld + i] : 0.0;
-  const double* D = Db + (int64_t)blockIdx.y * Dstride + (int64_t)k0 * 64;
-  for (int e = tid; e < 64 * 64; e += (int)blockDim.x) {
-    const int c = e >> 6, r = e & 63;
-    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = D[c * kb + r];
-  }
+  for (int l = 0; l < 64; ++l) rv[l] = (row && l < kb) ? Li[(int64_t)l * f.ld] : 0.0;
+  const int j = i - f.p;  // update row
+  double* w = A.w + (int64_t)blockIdx.y * A.sw + f.W + j;
+  double* v = A.v + (int64_t)blockIdx.y * A.sv + f.W + j;
+  const bool first = chunk ? k0 % chunk == 0 : k0 == 0;
+  double acc = row && j >= 0 && !first ? *v : 0.0;
   __syncthreads();
-  if (tid < 64) {
-    // lane i holds entry i and the reciprocal of its diagonal; step k
-    // broadcasts entry k and its reciprocal (uniform lane reads)
-    double vi = tid < kb ? y[k0 + tid] : 0.0;
-    const double ri = tid < kb ? 1.0 / Tr[tid * 65 + tid] : 0.0;
-    for (int k = 0; k < kb; ++k) {
-      const double xk = lane_bcast(vi, k) * lane_bcast(ri, k);
-      if (tid == k) vi = xk;
-      else if (tid > k && tid < kb) vi -= Tr[k * 65 + tid] * xk;
-    }
-    xs[tid] = vi;
-    if (blockIdx.x == 0 && tid < kb) z[k0 + tid] = vi;
-  }
-  __syncthreads();
-  if (row) {
-    double acc = 0.0;
+  if (!row) return;
 #pragma unroll
-    for (int l = 0; l < 64; ++l)
-      if (l < kb) acc += rv[l] * xs[l];
+  for (int q = 0; q < 4; ++q) {
+    if (q * 16 >= kb) break;
+#pragma unroll
+    for (int l = q * 16; l < q * 16 + 16; ++l) acc += rv[l] * xs[l];
+  }
+  if (j < 0) {
     y[i] -= acc;
+    return;
+  }
+  const bool end = k0 + kb == f.p;
+  if (!chunk) {
+    if (end) *w += acc;
+    else *v = acc;
+  } else if (end || (k0 + kb) % chunk == 0) {
+    const double s = (k0 < chunk ? 0.0 : *w) + acc;
+    *w = s;
+    if (end && next) next[(int64_t)blockIdx.y * sn + j] -= s;
+  } else {
+    *v = acc;
   }
 }
 
-// w = L21 z with the columns split over chunks of cc (grid: row blocks x
-// chunks); partial sums part[chunk][u], summed in chunk order next.
-__global__ void __launch_bounds__(256) k_gemv_part(const double* __restrict__ L, int32_t ld, int32_t p, int32_t u,
-                                                   const double* __restrict__ z, int32_t cc,
-                                                   double* __restrict__ part) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= u) return;
-  const int k0 = (int)blockIdx.y * cc, k1 = min(p, k0 + cc);
-  double acc = 0.0;
-  for (int k = k0; k < k1; ++k) acc += L[(int64_t)k * ld + p + i] * z[k];
-  part[(int64_t)blockIdx.y * u + i] = acc;
-}
-
-__global__ void k_gemv_sum(const double* __restrict__ part, int32_t nch, int32_t u, double* __restrict__ w) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= u) return;
-  double acc = 0.0;
-  for (int c = 0; c < nch; ++c) acc += part[(int64_t)c * u + i];
-  w[i] = acc;
-}
-
-// Forward, w[i] (+)= sum_k L21[i, k] z[k] over the u update rows (rows p ..
-// p+u-1 of the factor block); grid (row blocks, periods).
-__global__ void __launch_bounds__(256) k_fwd_gemv(const double* __restrict__ Lb, int64_t Lstride, int32_t ld,
-                                                  int32_t p, int32_t u, const double* __restrict__ zb,
-                                                  int64_t zstride, double* __restrict__ wb, int64_t wstride,
-                                                  int32_t accumulate) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= u) return;
-  const double* L = Lb + (int64_t)blockIdx.y * Lstride + p + i;
-  const double* z = zb + (int64_t)blockIdx.y * zstride;
-  double acc = 0.0;
-  for (int k = 0; k < p; ++k) acc += L[(int64_t)k * ld] * z[k];
-  double* w = wb + (int64_t)blockIdx.y * wstride;
-  w[i] = accumulate ? w[i] + acc : acc;
-}
-
-// Backward, v[j] = y[j] - sum_i L21[i, j] x_u[i] for the p pivot columns,
-// one wavefront per column; x_u gathered through rows (or contiguous when
-// rows is NULL).  Grid (column blocks of 4, periods).
-__global__ void __launch_bounds__(256) k_bwd_gemv(const double* __restrict__ Lb, int64_t Lstride, int32_t ld,
-                                                  int32_t p, int32_t u, const int32_t* __restrict__ rows,
-                                                  const double* __restrict__ xb, int64_t xstride,
-                                                  double* __restrict__ yb, int64_t ystride) {
+// Backward, z[j] -= sum_i L21[i, j] x_u[i] for the pivot columns, one
+// wavefront per column; x_u gathered through the front's row list (interior:
+// rows, x the period's solution) or contiguous (rows NULL).  Grid (column
+// blocks of 4; batch; fronts).
+__global__ void __launch_bounds__(256) k_bwd_gemv(Tri A, const int32_t* __restrict__ rows,
+                                                  const double* __restrict__ x, int64_t sx) {
+  const FrontRec f = A.rec[blockIdx.z];
   const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   const int lane = (int)(threadIdx.x & 63);
-  if (j >= p) return;
-  const double* col = Lb + (int64_t)blockIdx.y * Lstride + (int64_t)j * ld + p;
-  const double* xs = xb + (int64_t)blockIdx.y * xstride;
+  if (j >= f.p) return;
+  const double* col = A.L + (int64_t)blockIdx.y * A.sL + f.L + (int64_t)j * f.ld + f.p;
+  const double* xs = x + (int64_t)blockIdx.y * sx;
+  const int32_t* rr = rows ? rows + f.R : nullptr;
   double acc = 0.0;
-  for (int a = lane; a < u; a += 64) acc += col[a] * xs[rows ? rows[a] : a];
+#pragma unroll 4
+  for (int a = lane; a < f.u; a += 64) acc += col[a] * xs[rr ? rr[a] : a];
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) yb[(int64_t)blockIdx.y * ystride + j] -= acc;
+  if (lane == 0) A.z[(int64_t)blockIdx.y * A.sy + f.f + j] -= acc;
 }
 
-// Backward triangle L11^T x = z (pivot part of one front), one panel
-// [k0, k0+kb) per launch, panels from the last: every block solves the
-// panel's triangle from z (panel entries only read here), block 0 stores x
-// in y, and each block's 4 wavefronts subtract the panel's contribution
-// from their columns j < k0 of z (one wavefront per column, lanes over the
-// panel's rows).  Grid (column blocks of kBwdCols, periods).
-__global__ void __launch_bounds__(256) k_bwd_panel(const double* __restrict__ Lb, int64_t Lstride,
-                                                   const double* __restrict__ Db, int64_t Dstride, int32_t ld,
-                                                   int32_t p, int32_t k0, double* __restrict__ yb,
-                                                   double* __restrict__ zb, int64_t ystride) {
-  __shared__ double Tr[64 * 65];
+// Backward triangle L11^T x = z, one panel of each front per launch, the
+// panels from the last (panel q counted from there): a fifth wavefront of
+// every block solves the panel's triangle from z (panel entries only read
+// here), block 0 stores x in y, and each block's four other wavefronts, whose
+// loads overlap the triangle, subtract the panel's contribution from their
+// columns j < k0 of z (one wavefront per column, lanes over the panel's rows).
+// Grid (column blocks of kBwdCols; batch; fronts).
+__global__ void __launch_bounds__(320) k_bwd_panel(Tri A, int32_t q) {
   __shared__ double xs[64];
-  const double* L = Lb + (int64_t)blockIdx.y * Lstride;
-  double* y = yb + (int64_t)blockIdx.y * ystride;
-  double* z = zb + (int64_t)blockIdx.y * ystride;
-  const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int kb = min(64, p - k0);
-  // this wavefront's columns j < k0 (jb + wv, + 4, ...): their panel
-  // entries, loaded first so that their latency overlaps the triangle
+  const FrontRec f = A.rec[blockIdx.z];
+  const int k0 = ((f.p - 1) / kNB - q) * kNB;
+  if (k0 < 0) return;
+  const int kb = min(kNB, f.p - k0);
   const int jb = (int)blockIdx.x * kBwdCols, je = min(jb + kBwdCols, k0);
+  if (blockIdx.x > 0 && jb >= k0) return;
+  const double* L = A.L + (int64_t)blockIdx.y * A.sL + f.L;
+  double* z = A.z + (int64_t)blockIdx.y * A.sy + f.f;
+  const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (wv == 4) {
+    const double x = solve64<false>(A.D + (int64_t)blockIdx.y * A.sD + f.D + (int64_t)k0 * kNB, kb, lane,
+                                    lane < kb ? z[k0 + lane] : 0.0);
+    xs[lane] = x;
+    if (blockIdx.x == 0 && lane < kb) A.y[(int64_t)blockIdx.y * A.sy + f.f + k0 + lane] = x;
+    __syncthreads();
+    return;
+  }
   constexpr int kPerWave = kBwdCols / 4;
   double cv[kPerWave];
 #pragma unroll
-  for (int q = 0; q < kPerWave; ++q) {
-    const int j = jb + wv + 4 * q;
-    cv[q] = (j < je && lane < kb) ? L[(int64_t)j * ld + k0 + lane] : 0.0;
-  }
-  const double* D = Db + (int64_t)blockIdx.y * Dstride + (int64_t)k0 * 64;
-  for (int e = tid; e < 64 * 64; e += (int)blockDim.x) {
-    const int c = e >> 6, r = e & 63;
-    if (c < kb && r < kb && r >= c) Tr[c * 65 + r] = D[c * kb + r];
-  }
-  __syncthreads();
-  if (tid < 64) {
-    double vj = tid < kb ? z[k0 + tid] : 0.0;
-    const double rj = tid < kb ? 1.0 / Tr[tid * 65 + tid] : 0.0;
-    for (int k = kb - 1; k >= 0; --k) {
-      const double xk = lane_bcast(vj, k) * lane_bcast(rj, k);
-      if (tid == k) vj = xk;
-      else if (tid < k) vj -= Tr[tid * 65 + k] * xk;
-    }
-    xs[tid] = tid < kb ? vj : 0.0;
-    if (blockIdx.x == 0 && tid < kb) y[k0 + tid] = vj;
+  for (int c = 0; c < kPerWave; ++c) {
+    const int j = jb + wv + 4 * c;
+    cv[c] = (j < je && lane < kb) ? L[(int64_t)j * f.ld + k0 + lane] : 0.0;
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kPerWave; ++q) {
-    const int j = jb + wv + 4 * q;
+  for (int c = 0; c < kPerWave; ++c) {
+    const int j = jb + wv + 4 * c;
     if (j < je) {
-      double acc = lane < kb ? cv[q] * xs[lane] : 0.0;
+      double acc = lane < kb ? cv[c] * xs[lane] : 0.0;
       for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
       if (lane == 0) z[j] -= acc;
     }
@@ -1039,10 +1064,11 @@ struct CholInst {
           *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr;
   int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
           *d_slot = nullptr;
-  double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
-  double* Gp = nullptr;  // column-chunk partials of the chain's L21 z
-  std::vector<int64_t> woff;  // per-front offsets of the forward update vectors
-  std::vector<int64_t> doff;  // per-front offsets of the diagonal blocks (large fronts)
+  double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *V = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
+  double* Gp = nullptr;  // running sums of the chain's L21 z (two fronts)
+  std::vector<FrontRec> rec;  // the large fronts, by level
+  FrontRec crec[2];           // the pg fronts (with update rows, without)
+  FrontRec *d_rec = nullptr, *d_crec = nullptr;
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
 };
@@ -1058,16 +1084,6 @@ struct opf_chol {
   // interior fronts of the next chunk (events order the two)
   hipStream_t cs = nullptr;
   std::vector<hipEvent_t> evs;
-  // the large fronts of one level are independent: they are dealt in turn
-  // to the model's stream and these streams, forked and joined by events per
-  // level.  One is enough: with the model's and the chain's stream that
-  // makes three, within the four hardware queues HIP gives a process by
-  // default; more streams share queues, and work queued behind another
-  // stream's event wait stalls (measured: one extra 1.76 s, two 2.36 s, none
-  // 1.90 s per paper-scale factorization)
-  static constexpr int kFrontStreams = 1;
-  hipStream_t fs[kFrontStreams] = {};
-  hipEvent_t fork_ev = nullptr, join_ev[kFrontStreams] = {};
   // the solve recorded once into a HIP graph per (b, x) pair and replayed
   // on the model's stream (its launch sequence is fixed for the object)
   hipStream_t gs = nullptr;
@@ -1137,20 +1153,28 @@ void release(opf_chol* F) {
 
 int setup_device(opf_chol* F, CholInst& C) {
   const CholPlan& P = C.plan;
-  std::vector<int64_t>& woff = C.woff;
-  woff.assign(P.nnodes, 0);
+  std::vector<int64_t> woff(P.nnodes, 0);  // per-front offsets of the forward update vectors
   int64_t w = 0;
   for (int32_t s = 0; s < P.nnodes; ++s) {
     woff[s] = w;
     w += P.node_u[s];
   }
   C.wsize = std::max<int64_t>(w, 1);
-  C.doff.assign(P.nnodes, 0);
-  for (int32_t s : P.lvl_large) {
-    C.doff[s] = C.dsize;
-    C.dsize += diag_size(P.node_p[s]);
+  // the large fronts, level by level, those with more pivots first
+  for (int32_t h = 0; h < P.nlevels; ++h) {
+    std::vector<int32_t> v(P.lvl_large.begin() + P.lvl_large_ptr[h], P.lvl_large.begin() + P.lvl_large_ptr[h + 1]);
+    std::stable_sort(v.begin(), v.end(), [&](int32_t x, int32_t y) { return P.node_p[x] > P.node_p[y]; });
+    for (int32_t s : v) {
+      C.rec.push_back({P.node_loff[s], C.dsize, P.node_uoff[s], woff[s], P.row_ptr[s], P.node_p[s], P.node_u[s],
+                       P.node_p[s] + P.node_u[s], P.node_f[s], s});
+      C.dsize += diag_size(P.node_p[s]);
+    }
   }
   C.dcsize = diag_size(P.G);
+  C.crec[0] = {0, 0, 0, 0, 0, P.G, P.G, 2 * P.G, 0, 0};  // a pg front of the chain, and the one that closes it
+  C.crec[1] = {0, 0, 0, 0, 0, P.G, 0, 2 * P.G, 0, 0};
+  CHK(upload(F, C.rec, &C.d_rec));
+  CHK(upload(F, std::vector<FrontRec>(C.crec, C.crec + 2), &C.d_crec));
   std::vector<int32_t> items = P.items;
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
@@ -1183,7 +1207,8 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(dalloc(F, G * T, &C.Wc));
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Y));
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Z));
-  CHK(dalloc(F, (int64_t)((G + kChainCols - 1) / kChainCols) * G, &C.Gp));
+  CHK(dalloc(F, 2 * G, &C.Gp));
+  CHK(dalloc(F, C.wsize * T, &C.V));
   CDev& D = C.dev;
   D.node_f = C.d_node_f;
   D.node_p = C.d_node_p;
@@ -1205,63 +1230,81 @@ int setup_device(opf_chol* F, CholInst& C) {
   return OPF_OK;
 }
 
+// A batch of fronts as the host launches it: the records on both sides and
+// the number of periods.
+struct Batch {
+  Fronts F;
+  const FrontRec* rec;
+  int n, nt;
+  // the fronts with pivots from position k on
+  int active(int k) const {
+    int a = 0;
+    while (a < n && rec[a].p > k) ++a;
+    return a;
+  }
+};
+
 // Small tiles where 64 x 64 ones would leave CUs without a block: at 256
 // panel columns, 144 columns and 544 rows of two fronts 9.6 us against 20.
-int launch_update(const FrontArg& A, int nt, int k0, int kb, int r0, int cmax, hipStream_t st) {
-  const int rows = A.p + A.u;
-  const int cend = std::min(cmax, rows);
-  if (r0 >= rows || cend <= r0) return OPF_OK;
-  auto tiles = [&](int64_t tm) {
-    const int64_t R = (rows - r0 + tm - 1) / tm, Cn = (cend - r0 + tm - 1) / tm;
-    return Cn * R - Cn * (Cn - 1) / 2;
-  };
-  const int64_t n = tiles(kTile);
-  if (n > 0x7fffffff) return api_fail(OPF_EINVAL, "chol: front too large");
-  if (n * nt < kFewTiles)
-    hipLaunchKernelGGL((k_update<32, 64>), dim3((unsigned)tiles(32), nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
+int launch_update(const Batch& B, int k0, int w, bool inner, hipStream_t st) {
+  const int n = B.active(inner ? k0 + w : k0);
+  int64_t most[2] = {0, 0}, sum = 0;  // tiles of the largest front, by tile size; 64 x 64 tiles of all
+  for (int i = 0; i < n; ++i) {
+    const FrontRec& f = B.rec[i];
+    const int rows = f.p + f.u, r0 = k0 + std::min(w, f.p - k0), cend = inner ? std::min(r0 + w, f.p) : rows;
+    if (cend <= r0) continue;
+    for (int s = 0; s < 2; ++s) {
+      const int64_t tm = s ? 32 : kTile, R = (rows - r0 + tm - 1) / tm, Cn = (cend - r0 + tm - 1) / tm;
+      const int64_t t = Cn * R - Cn * (Cn - 1) / 2;
+      most[s] = std::max(most[s], t);
+      if (!s) sum += t;
+    }
+  }
+  if (sum == 0) return OPF_OK;
+  if (most[1] > 0x7fffffff) return api_fail(OPF_EINVAL, "chol: front too large");
+  if (sum * B.nt < kFewTiles)
+    hipLaunchKernelGGL((k_update<32, 64>), dim3((unsigned)most[1], B.nt, n), dim3(256), 0, st, B.F, k0, w, (int)inner);
   else
-    hipLaunchKernelGGL((k_update<kTile, 8>), dim3((unsigned)n, nt), dim3(256), 0, st, A, k0, kb, r0, cmax);
+    hipLaunchKernelGGL((k_update<kTile, 8>), dim3((unsigned)most[0], B.nt, n), dim3(256), 0, st, B.F, k0, w, (int)inner);
   LAUNCH_OK("chol update");
   return OPF_OK;
 }
 
-// Columns [k, k+w) of a front, w a power of two >= kWide: up to kWide columns
-// by panels that each take their update from the block's columns before them;
-// wider blocks recursively: the first half, the first half's update of the
-// second half's columns, the second half.  The trailing columns are left to
-// the caller.
-int factor_cols(const FrontArg& A, int nt, int k, int w, double tol, double repl, int32_t* npert, hipStream_t st) {
-  const int rows = A.p + A.u;
-  if (k >= A.p) return OPF_OK;
+// Columns [k, k+w) of a batch of fronts, w a power of two >= kWide: up to
+// kWide columns by panels that each take their update from the block's columns
+// before them; wider blocks recursively: the first half, the first half's
+// update of the second half's columns, the second half.  The trailing columns
+// are left to the caller.
+int factor_cols(const Batch& B, int k, int w, double tol, double repl, int32_t* npert, hipStream_t st) {
   if (w == kWide) {
-    for (int k0 = k; k0 < std::min(k + kWide, A.p); k0 += kNB) {
-      const int kb = std::min(kNB, A.p - k0);
-      hipLaunchKernelGGL(k_panel, dim3(std::max(1, (rows - k0 - kb + kTR - 1) / kTR), nt), dim3(kPT), 0, st, A, k, k0,
-                         kb, tol, repl, npert);
+    for (int k0 = k; k0 < k + kWide; k0 += kNB) {
+      const int n = B.active(k0);
+      if (n == 0) break;
+      int g = 1;
+      for (int i = 0; i < n; ++i) {
+        const FrontRec& f = B.rec[i];
+        g = std::max(g, (f.p + f.u - k0 - std::min(kNB, f.p - k0) + kTR - 1) / kTR);
+      }
+      hipLaunchKernelGGL(k_panel, dim3(g, B.nt, n), dim3(kPT), 0, st, B.F, k, k0, tol, repl, npert);
       LAUNCH_OK("chol panel");
     }
     return OPF_OK;
   }
   const int h = w / 2;
-  CHK(factor_cols(A, nt, k, h, tol, repl, npert, st));
-  const int kh = std::min(h, A.p - k);
-  const int k2 = std::min(h, A.p - k - kh);
-  if (k2 > 0) {
-    const int r1 = k + kh;
-    CHK(launch_update(A, nt, k, kh, r1, r1 + k2, st));
-    CHK(factor_cols(A, nt, r1, h, tol, repl, npert, st));
+  CHK(factor_cols(B, k, h, tol, repl, npert, st));
+  if (B.active(k + h) > 0) {
+    CHK(launch_update(B, k, h, true, st));
+    CHK(factor_cols(B, k + h, h, tol, repl, npert, st));
   }
   return OPF_OK;
 }
 
-int factor_front(const FrontArg& A, int nt, double tol, double repl, int32_t* npert, hipStream_t st) {
-  const int rows = A.p + A.u;
-  // kStep-column steps, each factored recursively, then one trailing update
-  // with the kStep-wide panel
-  for (int k0 = 0; k0 < A.p; k0 += kStep) {
-    CHK(factor_cols(A, nt, k0, kStep, tol, repl, npert, st));
-    const int kb = std::min(kStep, A.p - k0);
-    CHK(launch_update(A, nt, k0, kb, k0 + kb, rows, st));
+// A batch of fronts: kStep-column steps, each factored recursively, then one
+// trailing update with the kStep-wide panel.
+int factor_fronts(const Batch& B, double tol, double repl, int32_t* npert, hipStream_t st) {
+  for (int k0 = 0; B.active(k0) > 0; k0 += kStep) {
+    CHK(factor_cols(B, k0, kStep, tol, repl, npert, st));
+    CHK(launch_update(B, k0, kStep, false, st));
   }
   return OPF_OK;
 }
@@ -1327,19 +1370,13 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   };
   // nt = 2: fronts kl and kr in one batch (period stride kr - kl)
   auto chain_front = [&](int t, int nt, int t2, int u, double* Ub) -> int {
-    FrontArg A;
-    A.L = C.Cf + (int64_t)t * C.csize;
-    A.Lstride = nt > 1 ? (int64_t)(t2 - t) * C.csize : 0;
-    A.ld = 2 * G;
-    A.p = G;
-    A.u = u;
-    A.U = Ub;
-    A.Ustride = nt > 1 ? gg : 0;
-    A.ldU = G;
-    A.D = C.Dc + (int64_t)t * C.dcsize;
-    A.Dstride = nt > 1 ? (int64_t)(t2 - t) * C.dcsize : 0;
-    A.stop = C.dev.stop;
-    return factor_front(A, nt, tol, repl, npert, F->cs);
+    Batch B;
+    B.F = {C.d_crec + (u ? 0 : 1), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
+           (int64_t)(t2 - t) * C.csize, (int64_t)(t2 - t) * C.dcsize, gg, C.dev.stop};
+    B.rec = C.crec + (u ? 0 : 1);
+    B.n = 1;
+    B.nt = nt;
+    return factor_fronts(B, tol, repl, npert, F->cs);
   };
   auto chain_steps = [&](bool all) -> int {
     for (;;) {
@@ -1387,35 +1424,15 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
         LAUNCH_OK("chol small fronts");
       }
       const int64_t q0 = P.lvl_large_ptr[h], q1 = P.lvl_large_ptr[h + 1];
-      const int nfs = (int)std::min<int64_t>(opf_chol::kFrontStreams, q1 - q0 - 1);
-      if (nfs > 0) {
-        if (hipEventRecord(F->fork_ev, st) != hipSuccess) return api_fail(OPF_EHIP, "chol: front stream fork");
-        for (int k = 0; k < nfs; ++k)
-          if (hipStreamWaitEvent(F->fs[k], F->fork_ev, 0) != hipSuccess)
-            return api_fail(OPF_EHIP, "chol: front stream fork");
+      if (q1 > q0) {
+        Batch B;
+        B.F = {C.d_rec + q0, C.Lf + (int64_t)t0 * P.lsize, C.Df + (int64_t)t0 * C.dsize, C.Ar, P.lsize, C.dsize, P.usize,
+               C.dev.stop};
+        B.rec = C.rec.data() + q0;
+        B.n = (int)(q1 - q0);
+        B.nt = nt;
+        CHK(factor_fronts(B, tol, repl, npert, st));
       }
-      for (int64_t q = q0; q < q1; ++q) {
-        const int s = P.lvl_large[q];
-        const int64_t slot = (q - q0) % (nfs + 1);
-        hipStream_t fst = slot == 0 ? st : F->fs[slot - 1];
-        FrontArg A;
-        A.L = C.Lf + (int64_t)t0 * P.lsize + P.node_loff[s];
-        A.Lstride = P.lsize;
-        A.ld = P.node_p[s] + P.node_u[s];
-        A.p = P.node_p[s];
-        A.u = P.node_u[s];
-        A.U = C.Ar + P.node_uoff[s];
-        A.Ustride = P.usize;
-        A.ldU = std::max(1, P.node_u[s]);
-        A.D = C.Df + (int64_t)t0 * C.dsize + C.doff[s];
-        A.Dstride = C.dsize;
-        A.stop = C.dev.stop;
-        CHK(factor_front(A, nt, tol, repl, npert, fst));
-      }
-      for (int k = 0; k < nfs; ++k)
-        if (hipEventRecord(F->join_ev[k], F->fs[k]) != hipSuccess ||
-            hipStreamWaitEvent(st, F->join_ev[k], 0) != hipSuccess)
-          return api_fail(OPF_EHIP, "chol: front stream join");
     }
     const int cb = CholOptions().col_block;
     hipLaunchKernelGGL(k_extend_root, dim3((G + cb - 1) / cb, nt), dim3(256), 0, st, C.dev, C.d_roots,
@@ -1438,26 +1455,31 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   return OPF_OK;
 }
 
-// Forward / backward triangle of one front's pivot block by panels (see
-// k_fwd_panel / k_bwd_panel): y is the right-hand side in, z the forward
-// solution; the backward pass reads z and leaves x in y.
-int fwd_tri(const double* L, int64_t Ls, const double* D, int64_t Ds, int ld, int p, double* y, double* z, int64_t ys, int nper,
-            hipStream_t st) {
-  for (int k0 = 0; k0 < p; k0 += 64) {
-    const int below = p - k0 - std::min(64, p - k0);
-    hipLaunchKernelGGL(k_fwd_panel, dim3(std::max(1, (below + 255) / 256), nper), dim3(256), 0, st, L, Ls, D, Ds,
-                       ld, p, k0, y, z, ys);
+// Forward / backward triangle of a batch of fronts (nb batch entries, in
+// falling order of p) by panels, see k_fwd_panel / k_bwd_panel: y is the
+// right-hand side in, z the forward solution; the backward pass reads z and
+// leaves x in y.
+int fwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, int chunk, double* next, int64_t sn, hipStream_t st) {
+  for (int k0 = 0; n > 0; k0 += kNB) {
+    int g = 1;
+    for (int i = 0; i < n; ++i) {
+      const int below = rec[i].p + rec[i].u - k0 - std::min(kNB, rec[i].p - k0);
+      g = std::max(g, (below + 255) / 256);
+    }
+    hipLaunchKernelGGL(k_fwd_panel, dim3(g, nb, n), dim3(320), 0, st, A, k0, chunk, next, sn);
+    while (n > 0 && rec[n - 1].p <= k0 + kNB) --n;
   }
-  LAUNCH_OK("chol forward triangle");
+  LAUNCH_OK("chol forward panel");
   return OPF_OK;
 }
 
-int bwd_tri(const double* L, int64_t Ls, const double* D, int64_t Ds, int ld, int p, double* y, double* z, int64_t ys, int nper,
-            hipStream_t st) {
-  for (int k0 = ((p - 1) / 64) * 64; k0 >= 0; k0 -= 64)
-    hipLaunchKernelGGL(k_bwd_panel, dim3(std::max(1, (k0 + kBwdCols - 1) / kBwdCols), nper), dim3(256), 0, st, L,
-                       Ls, D, Ds, ld, p, k0, y, z, ys);
-  LAUNCH_OK("chol backward triangle");
+int bwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, hipStream_t st) {
+  for (int q = 0; n > 0; ++q) {
+    const int k0 = ((rec[0].p - 1) / kNB - q) * kNB;
+    hipLaunchKernelGGL(k_bwd_panel, dim3(std::max(1, (k0 + kBwdCols - 1) / kBwdCols), nb, n), dim3(320), 0, st, A, q);
+    while (n > 0 && (rec[n - 1].p - 1) / kNB <= q) --n;
+  }
+  LAUNCH_OK("chol backward panel");
   return OPF_OK;
 }
 
@@ -1468,6 +1490,9 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   const int64_t np = P.n_p;
   hipLaunchKernelGGL(k_gather, dim3(grid_for(np * T, 256)), dim3(256), 0, st, b + I.x_off, P.n_p, T, C.d_perm, C.Y);
   LAUNCH_OK("chol gather");
+  auto tree = [&](int64_t q0) {
+    return Tri{C.d_rec + q0, C.Lf, C.Df, C.Y, C.Z, C.W, C.V, P.lsize, C.dsize, np, C.wsize, C.wsize};
+  };
   // forward through the interior trees, all periods at once (small fronts
   // leave their forward solution in Y, large ones in Z)
   for (int h = 0; h < P.nlevels; ++h) {
@@ -1477,16 +1502,11 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
                          C.Y, C.W);
       LAUNCH_OK("chol forward small");
     }
-    for (int64_t q = P.lvl_large_ptr[h]; q < P.lvl_large_ptr[h + 1]; ++q) {
-      const int s = P.lvl_large[q];
-      const int p = P.node_p[s], u = P.node_u[s], fs = P.node_f[s];
-      const double* L = C.Lf + P.node_loff[s];
-      hipLaunchKernelGGL(k_fwd_pull, dim3(T), dim3(256), 0, st, C.dev, s, C.Y, C.W);
-      CHK(fwd_tri(L, P.lsize, C.Df + C.doff[s], C.dsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
-      if (u > 0)
-        hipLaunchKernelGGL(k_fwd_gemv, dim3((u + 255) / 256, T), dim3(256), 0, st, L, P.lsize, p + u, p, u,
-                           (const double*)(C.Z + fs), np, C.W + C.woff[s], C.wsize, 1);
-      LAUNCH_OK("chol forward large");
+    const int64_t q0 = P.lvl_large_ptr[h];
+    const int nl = (int)(P.lvl_large_ptr[h + 1] - q0);
+    if (nl > 0) {
+      hipLaunchKernelGGL(k_fwd_pull, dim3(T, 1, nl), dim3(256), 0, st, C.dev, C.d_rec + q0, C.Y, C.W);
+      CHK(fwd_tri(tree(q0), C.rec.data() + q0, nl, T, 0, nullptr, 0, st));
     }
   }
   hipLaunchKernelGGL(k_fwd_root_pull, dim3(T), dim3(256), 0, st, C.dev, C.d_roots, (int32_t)P.roots.size(), C.Y,
@@ -1497,22 +1517,17 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   // step while both sides have one, then front m
   const int m = (T - 1) / 2;
   auto off = [&](int t) { return (int64_t)t * np + P.n_int; };
-  auto front = [&](int t) { return (const double*)(C.Cf + (int64_t)t * C.csize); };
-  auto diag = [&](int t) { return (const double*)(C.Dc + (int64_t)t * C.dcsize); };
-  // y_t -= L21_s z_s of its chain neighbour s (held in Wc[s])
-  auto pull = [&](int t, int s) -> int {
+  // fronts t and, when nb = 2, t2 as one batch
+  auto chain = [&](int t, int nb, int t2) {
+    const int64_t d = nb > 1 ? t2 - t : 0;
+    return Tri{C.d_crec + (t == m ? 1 : 0), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
+               C.Z + off(t), C.Wc + (int64_t)t * G, C.Gp, d * C.csize, d * C.dcsize, d * np, d * G, G};
+  };
+  // front m collects its two neighbours' updates (Wc), left then right; the
+  // others take theirs from the last panel of the neighbour before them
+  auto pull_to = [&](int t, int s) -> int {
     hipLaunchKernelGGL(k_sub, dim3((G + 255) / 256), dim3(256), 0, st, C.Y + off(t),
                        (const double*)(C.Wc + (int64_t)s * G), G);
-    LAUNCH_OK("chol forward chain");
-    return OPF_OK;
-  };
-  // Wc[t] = L21_t z_t
-  auto push = [&](int t) -> int {
-    const int nch = (G + kChainCols - 1) / kChainCols;
-    hipLaunchKernelGGL(k_gemv_part, dim3((G + 255) / 256, nch), dim3(256), 0, st, front(t), 2 * G, G, G,
-                       (const double*)(C.Z + off(t)), kChainCols, C.Gp);
-    hipLaunchKernelGGL(k_gemv_sum, dim3((G + 255) / 256), dim3(256), 0, st, (const double*)C.Gp, nch, G,
-                       C.Wc + (int64_t)t * G);
     LAUNCH_OK("chol forward chain");
     return OPF_OK;
   };
@@ -1520,60 +1535,50 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     int kl = 0, kr = T - 1;
     while (kl < m || kr > m) {
       const bool l = kl < m, r = kr > m;
-      if (l && kl >= 1) CHK(pull(kl, kl - 1));
-      if (r && kr <= T - 2) CHK(pull(kr, kr + 1));
-      if (l && r)
-        CHK(fwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, diag(kl), (int64_t)(kr - kl) * C.dcsize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
-                    (int64_t)(kr - kl) * np, 2, st));
-      else
-        CHK(fwd_tri(front(l ? kl : kr), 0, diag(l ? kl : kr), 0, 2 * G, G,
-                    C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
-      if (l) CHK(push(kl));
-      if (r) CHK(push(kr));
+      const int t = l ? kl : kr, nb = l && r ? 2 : 1;
+      // the two sides reach front m in different steps unless both end there
+      const int nl = kl + 1, nr = kr - 1;
+      double* next = (l && nl == m) || (r && nr == m) ? nullptr : C.Y + off(l ? nl : nr);
+      CHK(fwd_tri(chain(t, nb, kr), C.crec, 1, nb, kChainCols, next, nb > 1 ? (int64_t)(nr - nl) * np : 0, st));
+      if (!next) {
+        // one side may still have a neighbour other than m to pass on to
+        if (l && nl != m) CHK(pull_to(nl, kl));
+        if (r && nr != m) CHK(pull_to(nr, kr));
+      }
       if (l) ++kl;
       if (r) --kr;
     }
-    if (m >= 1) CHK(pull(m, m - 1));
-    if (m + 1 <= T - 1) CHK(pull(m, m + 1));
-    CHK(fwd_tri(front(m), 0, diag(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
+    if (m >= 1) CHK(pull_to(m, m - 1));
+    if (m + 1 <= T - 1) CHK(pull_to(m, m + 1));
+    CHK(fwd_tri(chain(m, 1, m), C.crec + 1, 1, 1, kChainCols, nullptr, 0, st));
   }
   // backward along the pg chain: front m, then outwards (each front reads
   // its chain neighbour's solution, held in Y)
   {
-    CHK(bwd_tri(front(m), 0, diag(m), 0, 2 * G, G, C.Y + off(m), C.Z + off(m), 0, 1, st));
+    CHK(bwd_tri(chain(m, 1, m), C.crec + 1, 1, 1, st));
     int kl = m - 1, kr = m + 1;
     while (kl >= 0 || kr <= T - 1) {
       const bool l = kl >= 0, r = kr <= T - 1;
-      if (l)
-        hipLaunchKernelGGL(k_bwd_gemv, dim3((G + 3) / 4, 1), dim3(256), 0, st, front(kl), (int64_t)0, 2 * G, G, G,
-                           (const int32_t*)nullptr, (const double*)(C.Y + off(kl + 1)), (int64_t)0, C.Z + off(kl),
-                           (int64_t)0);
-      if (r)
-        hipLaunchKernelGGL(k_bwd_gemv, dim3((G + 3) / 4, 1), dim3(256), 0, st, front(kr), (int64_t)0, 2 * G, G, G,
-                           (const int32_t*)nullptr, (const double*)(C.Y + off(kr - 1)), (int64_t)0, C.Z + off(kr),
-                           (int64_t)0);
+      const int t = l ? kl : kr, nb = l && r ? 2 : 1;
+      const Tri A = chain(t, nb, kr);
+      hipLaunchKernelGGL(k_bwd_gemv, dim3((G + 3) / 4, nb, 1), dim3(256), 0, st, A, (const int32_t*)nullptr,
+                         (const double*)(C.Y + off(l ? kl + 1 : kr - 1)), nb > 1 ? (int64_t)(kr - kl - 2) * np : 0);
       LAUNCH_OK("chol backward chain");
-      if (l && r)
-        CHK(bwd_tri(front(kl), (int64_t)(kr - kl) * C.csize, diag(kl), (int64_t)(kr - kl) * C.dcsize, 2 * G, G, C.Y + off(kl), C.Z + off(kl),
-                    (int64_t)(kr - kl) * np, 2, st));
-      else
-        CHK(bwd_tri(front(l ? kl : kr), 0, diag(l ? kl : kr), 0, 2 * G, G,
-                    C.Y + off(l ? kl : kr), C.Z + off(l ? kl : kr), 0, 1, st));
+      CHK(bwd_tri(A, C.crec, 1, nb, st));
       if (l) --kl;
       if (r) ++kr;
     }
   }
   // backward through the interior trees, top down
   for (int h = P.nlevels - 1; h >= 0; --h) {
-    for (int64_t q = P.lvl_large_ptr[h]; q < P.lvl_large_ptr[h + 1]; ++q) {
-      const int s = P.lvl_large[q];
-      const int p = P.node_p[s], u = P.node_u[s], fs = P.node_f[s];
-      const double* L = C.Lf + P.node_loff[s];
-      if (u > 0)
-        hipLaunchKernelGGL(k_bwd_gemv, dim3((p + 3) / 4, T), dim3(256), 0, st, L, P.lsize, p + u, p, u,
-                           (const int32_t*)(C.d_rows + P.row_ptr[s]), (const double*)C.Y, np, C.Z + fs, np);
-      CHK(bwd_tri(L, P.lsize, C.Df + C.doff[s], C.dsize, p + u, p, C.Y + fs, C.Z + fs, np, T, st));
+    const int64_t q0 = P.lvl_large_ptr[h];
+    const int nl = (int)(P.lvl_large_ptr[h + 1] - q0);
+    if (nl > 0) {
+      const Tri A = tree(q0);
+      hipLaunchKernelGGL(k_bwd_gemv, dim3((C.rec[q0].p + 3) / 4, T, nl), dim3(256), 0, st, A,
+                         (const int32_t*)C.d_rows, (const double*)C.Y, np);
       LAUNCH_OK("chol backward large");
+      CHK(bwd_tri(A, C.rec.data() + q0, nl, T, st));
     }
     const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1];
     if (s1 > s0) {
@@ -1646,11 +1651,7 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
       int nev = 1;
       for (auto& C : F->inst) nev = std::max(nev, (C.plan.T + C.chunk - 1) / C.chunk + 1);
       bool ok = hipStreamCreateWithFlags(&F->cs, hipStreamNonBlocking) == hipSuccess &&
-                hipStreamCreateWithFlags(&F->gs, hipStreamNonBlocking) == hipSuccess &&
-                hipEventCreateWithFlags(&F->fork_ev, hipEventDisableTiming) == hipSuccess;
-      for (int k = 0; ok && k < opf_chol::kFrontStreams; ++k)
-        ok = hipStreamCreateWithFlags(&F->fs[k], hipStreamNonBlocking) == hipSuccess &&
-             hipEventCreateWithFlags(&F->join_ev[k], hipEventDisableTiming) == hipSuccess;
+                hipStreamCreateWithFlags(&F->gs, hipStreamNonBlocking) == hipSuccess;
       for (int k = 0; ok && k < nev; ++k) {
         hipEvent_t e = nullptr;
         ok = hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
@@ -1684,11 +1685,6 @@ void opf_chol_destroy(opf_chol* chol) {
   if (chol->device >= 0) (void)hipDeviceSynchronize();
   if (chol->gexec) (void)hipGraphExecDestroy(chol->gexec);
   for (hipEvent_t e : chol->evs) (void)hipEventDestroy(e);
-  if (chol->fork_ev) (void)hipEventDestroy(chol->fork_ev);
-  for (int k = 0; k < opf_chol::kFrontStreams; ++k) {
-    if (chol->join_ev[k]) (void)hipEventDestroy(chol->join_ev[k]);
-    if (chol->fs[k]) (void)hipStreamDestroy(chol->fs[k]);
-  }
   if (chol->cs) (void)hipStreamDestroy(chol->cs);
   if (chol->gs) (void)hipStreamDestroy(chol->gs);
   release(chol);
