@@ -337,14 +337,17 @@ int opf_autotune(opf_model *model, const char *cache_path);
  * periods: the other variables first (approximate minimum degree), the pg
  * variables last; the interior fronts of all periods are factored together,
  * then the pg fronts form a chain over the periods (block elimination in
- * time), eliminated from both ends of the horizon towards its middle period.
+ * time), eliminated from both ends of the horizon towards its middle period,
+ * or over long horizons by cyclic reduction.
  * Instances of a batched model are factored one after another. */
 typedef struct opf_chol opf_chol;
 
 typedef struct {
-  int64_t factor_entries; /* stored factor doubles, all instances and periods */
+  int64_t factor_entries; /* factor doubles, all instances and periods          */
   int64_t arena_entries;  /* update-matrix workspace doubles                  */
-  double flops;           /* factorization flops (multiply-add = 2)           */
+  double flops;           /* factorization flops (multiply-add = 2); both for
+                             the chain from both ends, cyclic reduction stores
+                             and computes more                                */
   double flops_interior;  /* of which in the per-period interior fronts       */
   int32_t nodes;          /* interior fronts per period, summed over instances */
   int32_t levels;         /* largest interior tree height                      */

@@ -15,7 +15,8 @@
 //     and its chain neighbour's update: a chain over t, eliminated from both
 //     ends at once (fronts t < m carry update rows pg_{t+1}, fronts t > m
 //     update rows pg_{t-1}, front m closes it; m = (T - 1) / 2), one front of
-//     each side per launch.
+//     each side per launch; over long horizons by cyclic reduction instead
+//     (every other front at once, see k_cyc_add).
 // Solves run the same tree forward (update vectors pulled by the parent)
 // and backward (gathers of the ancestors' solution), batched over periods.
 #include <hip/hip_runtime.h>
@@ -43,6 +44,15 @@ constexpr int kChainCols = 128;  // columns summed together in the chain's L21 z
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
 constexpr int kWide = 256;       // columns whose panels update each other within their launches
 constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 ones (one block per CU)
+// The pg chain by cyclic reduction (see k_cyc_add) from kCycT periods, up to
+// fronts of kCycG: factor + solve, from both ends against by reduction, 54
+// generators x 64 periods 2.44 / 1.12 ms, 400 x 64 25.9 / 18.5, 400 x 168 51 /
+// 43, 1000 x 168 185 / 140, 1400 x 168 314 / 285, but 2000 x 168 675 / 722: the
+// third of the work it adds outgrows the steps it saves.  Short horizons gain
+// less (400 x 24: 11.2 / 8.9 ms) and stay with the chain: an interior-point
+// iterate shows a changed elimination order at 1e-8, and small grids keep
+// theirs bit for bit.
+constexpr int kCycT = 64, kCycG = 1536;
 constexpr int kBwdCols = 16;     // earlier columns updated per block of a backward panel (a multiple of 4)
 
 // Device view of one instance's plan.
@@ -131,17 +141,20 @@ __global__ void k_scatter(const double* __restrict__ kv, int64_t k_off, int64_t 
 }
 
 // The ramp pairs (pg_t,g , pg_{t-1},g), t in [t0, t0 + gridDim.y), t >= 1:
-// entries of the L21 block (row G + g, column g) of the one of the two pg
-// fronts that the chain eliminates first: front t-1 when t <= m (the chain's
-// left side), front t otherwise (its right side).
+// entries of the coupling block of the one of the two pg fronts that is
+// eliminated first.  Two-ended chain (m >= 0): row G + g of front t-1 when t <=
+// m (the left side), of front t otherwise (the right side).  Cyclic reduction
+// (m < 0): the even one of the two, its right neighbour's rows at G, its left
+// neighbour's at 2 G.
 __global__ void k_scatter_ramp(const double* __restrict__ kv, int64_t k_off, int64_t nnzk_p, int32_t G, int32_t t0,
                                int32_t m, const int32_t* __restrict__ ramp_pos, double* __restrict__ Cf,
-                               int64_t csize) {
+                               int64_t csize, int32_t cld) {
   const int t = t0 + (int)blockIdx.y;
   const int64_t kp = k_off + (int64_t)t * nnzk_p + (int64_t)(t - 1) * G;
-  const int f = t <= m ? t - 1 : t;
+  const int f = m >= 0 ? (t <= m ? t - 1 : t) : (t & ~1);
+  const int row = m < 0 && f == t ? 2 * G : G;
   for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < G; g += gridDim.x * blockDim.x)
-    Cf[(int64_t)f * csize + (int64_t)g * 2 * G + G + g] = kv[kp + ramp_pos[g]];
+    Cf[(int64_t)f * csize + (int64_t)g * cld + row + g] = kv[kp + ramp_pos[g]];
 }
 
 // Extend-add for the fronts of one level: work item (s, c0) owns columns
@@ -194,15 +207,15 @@ __global__ void __launch_bounds__(256) k_extend(CDev D, const int32_t* __restric
   }
 }
 
-// The period's tree roots into its pg front (ld 2G, pivot block only).
+// The period's tree roots into its pg front (leading dimension ld, pivot block
+// only).
 __global__ void __launch_bounds__(256) k_extend_root(CDev D, const int32_t* __restrict__ roots, int32_t nroots,
                                                      int32_t cb, int32_t t0, double* __restrict__ Cf, int64_t csize,
-                                                     const double* __restrict__ Ar) {
+                                                     int64_t ld, const double* __restrict__ Ar) {
   if (stopped(D.stop)) return;
   const int tt = (int)blockIdx.y;
   const int c0 = (int)blockIdx.x * cb, c1 = min(c0 + cb, D.G);
   double* L = Cf + (int64_t)(t0 + tt) * csize;
-  const int64_t ld = 2 * (int64_t)D.G;
   for (int k = 0; k < nroots; ++k) {
     const int c = roots[k];
     const int uc = D.node_u[c];
@@ -735,6 +748,63 @@ __global__ void k_add_chain(const double* __restrict__ Us, int32_t G, double* __
   }
 }
 
+// ---- cyclic reduction of the pg chain
+//
+// At level k (h = 2^k) the fronts h - 1 + j h, j < n = T / h, are left; the
+// even ones, c = (n + 1) / 2 of them, are eliminated together, front j = 2 i
+// with its right (j + 1) and left (j - 1) neighbours' pg variables as update
+// rows, in this order (a missing neighbour's rows are zero; a level of one
+// front has no left rows).  Its update block links the two.  T = 168 periods
+// take 8 levels where the two-ended chain takes 84 steps, at 19/3 G^3 instead
+// of 7/3 G^3 multiply-adds for most fronts.
+
+// Front i's updates (2G x 2G blocks Ub, ub rows) into the pivot blocks of the
+// fronts that stay: front s = 2 i + 1 takes its left neighbour's (i, its right
+// rows) and its right one's (i + 1, its left rows; i + 1 < c).  Grid (elements;
+// fronts that stay).
+__global__ void k_cyc_add(const double* __restrict__ Ub, int32_t ub, int32_t c, int32_t G, double* __restrict__ C0,
+                          int64_t sC, int64_t ld, const int32_t* __restrict__ stop) {
+  if (stopped(stop)) return;
+  const int i = (int)blockIdx.y;
+  const double* Ul = Ub + (int64_t)i * ub * ub;
+  const double* Ur = i + 1 < c ? Ul + (int64_t)ub * ub + (int64_t)G * ub + G : nullptr;
+  double* C = C0 + (int64_t)i * sC;
+  const int64_t n = (int64_t)G * G;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t q = e / G, r = e % G;
+    if (r < q) continue;
+    double v = C[q * ld + r] + Ul[q * ub + r];
+    if (Ur) v += Ur[q * ub + r];
+    C[q * ld + r] = v;
+  }
+}
+
+// The coupling of the neighbours that stay, s and s + 1 (s = i, counted among
+// the ones that stay): the (left, right) block of front i + 1's update, into
+// the one of the two that goes first at the next level -- the even one: s
+// itself, its right rows (transposed), or s + 1, its left rows.  32 x 32 tiles.
+// Grid (tile column, tile row, pairs).
+__global__ void __launch_bounds__(256) k_cyc_link(const double* __restrict__ Ub, int32_t ub, int32_t G,
+                                                  double* __restrict__ C0, int64_t sC, int64_t ld,
+                                                  const int32_t* __restrict__ stop) {
+  __shared__ double tile[32][33];
+  if (stopped(stop)) return;
+  const int s = (int)blockIdx.z;
+  const double* X = Ub + (int64_t)(s + 1) * ub * ub + G;  // row a (left), column b (right) at X[b * ub + a]
+  const int a0 = (int)blockIdx.x * 32, b0 = (int)blockIdx.y * 32, x = (int)threadIdx.x & 31, y = (int)threadIdx.x >> 5;
+  if (s & 1) {
+    double* C = C0 + (int64_t)(s + 1) * sC + 2 * G;
+    for (int j = y; j < 32; j += 8)
+      if (a0 + x < G && b0 + j < G) C[(int64_t)(b0 + j) * ld + a0 + x] = X[(int64_t)(b0 + j) * ub + a0 + x];
+    return;
+  }
+  for (int j = y; j < 32; j += 8) tile[j][x] = (a0 + x < G && b0 + j < G) ? X[(int64_t)(b0 + j) * ub + a0 + x] : 0.0;
+  __syncthreads();
+  double* C = C0 + (int64_t)s * sC + G;
+  for (int j = y; j < 32; j += 8)
+    if (b0 + x < G && a0 + j < G) C[(int64_t)(a0 + j) * ld + b0 + x] = tile[x][j];
+}
+
 // ------------------------------------------------------------------ solves
 __global__ void k_sub(double* __restrict__ y, const double* __restrict__ w, int32_t n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) y[i] -= w[i];
@@ -968,6 +1038,45 @@ __global__ void __launch_bounds__(256) k_bwd_gemv(Tri A, const int32_t* __restri
   if (lane == 0) A.z[(int64_t)blockIdx.y * A.sy + f.f + j] -= acc;
 }
 
+// Cyclic reduction, forward: what the level's c fronts subtract from the
+// right-hand sides of the fronts that stay (front i: its left neighbour's
+// right rows, then its right one's left rows).  Grid (rows; fronts that stay).
+__global__ void k_cyc_pull(const double* __restrict__ W, int64_t sw, int32_t c, int32_t G, double* __restrict__ Y,
+                           int64_t sy) {
+  const int i = (int)blockIdx.y;
+  const double* w = W + (int64_t)i * sw;
+  double* y = Y + (int64_t)i * sy;
+  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < G; g += gridDim.x * blockDim.x) {
+    double v = y[g] - w[g];
+    if (i + 1 < c) v -= w[sw + G + g];
+    y[g] = v;
+  }
+}
+
+// Cyclic reduction, backward: z[j] -= sum L21[., j] x over the solutions of the
+// right (x + sh) and left (x - sh) neighbours of the fronts (x: the first
+// front's own), one wavefront per column.  n as above.  Grid (column blocks of
+// 4; fronts).
+__global__ void __launch_bounds__(256) k_cyc_gemv(Tri A, int32_t n, const double* __restrict__ x, int64_t sh) {
+  const FrontRec f = A.rec[0];
+  const int i = (int)blockIdx.y, lane = (int)(threadIdx.x & 63);
+  const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (j >= f.p) return;
+  const double* col = A.L + (int64_t)i * A.sL + (int64_t)j * f.ld + f.p;
+  const double* xs = x + (int64_t)i * A.sy;
+  double acc = 0.0;
+  if (2 * i + 1 < n) {
+#pragma unroll 4
+    for (int a = lane; a < f.p; a += 64) acc += col[a] * xs[sh + a];
+  }
+  if (i > 0) {
+#pragma unroll 4
+    for (int a = lane; a < f.p; a += 64) acc += col[f.p + a] * xs[a - sh];
+  }
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  if (lane == 0) A.z[(int64_t)i * A.sy + j] -= acc;
+}
+
 // Backward triangle L11^T x = z, one panel of each front per launch, the
 // panels from the last (panel q counted from there): a fifth wavefront of
 // every block solves the panel's triangle from z (panel entries only read
@@ -1065,9 +1174,12 @@ struct CholInst {
   int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
           *d_slot = nullptr;
   double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *V = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
-  double* Gp = nullptr;  // running sums of the chain's L21 z (two fronts)
+  double* Gp = nullptr;  // running sums of the chain's L21 z (a step's fronts)
   std::vector<FrontRec> rec;  // the large fronts, by level
-  FrontRec crec[2];           // the pg fronts (with update rows, without)
+  FrontRec crec[3];           // the pg fronts: with no, G and 2 G update rows
+  bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends
+  int32_t cld = 0;            // their leading dimension: 2 G or 3 G
+  double* Uc = nullptr;       // cyclic reduction: a level's update blocks
   FrontRec *d_rec = nullptr, *d_crec = nullptr;
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
@@ -1171,10 +1283,11 @@ int setup_device(opf_chol* F, CholInst& C) {
     }
   }
   C.dcsize = diag_size(P.G);
-  C.crec[0] = {0, 0, 0, 0, 0, P.G, P.G, 2 * P.G, 0, 0};  // a pg front of the chain, and the one that closes it
-  C.crec[1] = {0, 0, 0, 0, 0, P.G, 0, 2 * P.G, 0, 0};
+  C.cyclic = P.T >= kCycT && P.G <= kCycG;
+  C.cld = (C.cyclic ? 3 : 2) * P.G;
+  for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
-  CHK(upload(F, std::vector<FrontRec>(C.crec, C.crec + 2), &C.d_crec));
+  CHK(upload(F, std::vector<FrontRec>(C.crec, C.crec + 3), &C.d_crec));
   std::vector<int32_t> items = P.items;
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
@@ -1194,9 +1307,13 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(upload(F, woff, &C.d_woff));
   CHK(upload(F, P.row_ptr, &C.d_rowptr));
   CHK(upload(F, P.kid_ptr, &C.d_kidptr));
-  CHK(upload(F, P.slot_dst, &C.d_slot));
   const int64_t T = P.T, G = P.G;
-  C.csize = 2 * G * G;
+  // the plan numbers a pg front's entries with leading dimension 2 G
+  std::vector<int64_t> slot = P.slot_dst;
+  for (int64_t& d : slot)
+    if (d < 0) d = -1 - ((-1 - d) / (2 * G) * C.cld + (-1 - d) % (2 * G));
+  CHK(upload(F, slot, &C.d_slot));
+  C.csize = C.cld * G;
   C.chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>(T, arena_budget() / (P.usize * 8)));
   CHK(dalloc(F, P.lsize * T, &C.Lf));
   CHK(dalloc(F, C.csize * T, &C.Cf));
@@ -1204,10 +1321,15 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(dalloc(F, C.dcsize * T, &C.Dc));
   CHK(dalloc(F, P.usize * C.chunk, &C.Ar));
   CHK(dalloc(F, C.wsize * T, &C.W));
-  CHK(dalloc(F, G * T, &C.Wc));
+  CHK(dalloc(F, (C.cyclic ? 2 : 1) * G * T, &C.Wc));
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Y));
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Z));
-  CHK(dalloc(F, 2 * G, &C.Gp));
+  CHK(dalloc(F, C.cyclic ? (T + 1) / 2 * 2 * G : 2 * G, &C.Gp));
+  // a level's update blocks: the first level has the most, and the interior
+  // fronts' workspace is free by then
+  const int64_t nuc = C.cyclic ? (T + 1) / 2 * 4 * G * G : 0;
+  if (nuc <= P.usize * C.chunk) C.Uc = C.Ar;
+  else CHK(dalloc(F, nuc, &C.Uc));
   CHK(dalloc(F, C.wsize * T, &C.V));
   CDev& D = C.dev;
   D.node_f = C.d_node_f;
@@ -1309,6 +1431,36 @@ int factor_fronts(const Batch& B, double tol, double repl, int32_t* npert, hipSt
   return OPF_OK;
 }
 
+// The pg chain by cyclic reduction, after the interior fronts.
+int factor_cyclic(CholInst& C, double tol, double repl, int32_t* npert, hipStream_t st) {
+  const int T = C.plan.T, G = C.plan.G;
+  for (int h = 1; h <= T; h *= 2) {
+    const int n = T / h, c = (n + 1) / 2, u = c > 1 ? 2 : (n > 1 ? 1 : 0), ub = u * G;
+    const int64_t s2 = 2 * (int64_t)h;  // from one eliminated front to the next
+    if (u) {
+      hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)c * ub * ub, 256)), dim3(256), 0, st, C.Uc, (int64_t)c * ub * ub);
+      LAUNCH_OK("chol cyclic clear");
+    }
+    Batch B;
+    B.F = {C.d_crec + u, C.Cf + (h - 1) * C.csize, C.Dc + (h - 1) * C.dcsize, C.Uc, s2 * C.csize, s2 * C.dcsize,
+           (int64_t)ub * ub, C.dev.stop};
+    B.rec = C.crec + u;
+    B.n = 1;
+    B.nt = c;
+    CHK(factor_fronts(B, tol, repl, npert, st));
+    const int m = n - c;  // fronts that stay: 2 h - 1, 4 h - 1, ...
+    if (m == 0) break;
+    double* C0 = C.Cf + (s2 - 1) * C.csize;
+    hipLaunchKernelGGL(k_cyc_add, dim3(std::min(grid_for((int64_t)G * G, 256), 2048), m), dim3(256), 0, st, C.Uc, ub, c,
+                       G, C0, s2 * C.csize, (int64_t)C.cld, C.dev.stop);
+    if (m > 1)
+      hipLaunchKernelGGL(k_cyc_link, dim3((G + 31) / 32, (G + 31) / 32, m - 1), dim3(256), 0, st, C.Uc, ub, G, C0,
+                         s2 * C.csize, (int64_t)C.cld, C.dev.stop);
+    LAUNCH_OK("chol cyclic update");
+  }
+  return OPF_OK;
+}
+
 int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double repl, int32_t* npert,
                 hipStream_t st) {
   const CholPlan& P = C.plan;
@@ -1322,7 +1474,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   // interior runs
   if (T > 1) {
     hipLaunchKernelGGL(k_scatter_ramp, dim3(grid_for(G, 256), T - 1), dim3(256), 0, st, kv, I.k_off, I.nnzk_p, G, 1,
-                       (T - 1) / 2, C.d_ramp, C.Cf, C.csize);
+                       C.cyclic ? -1 : (T - 1) / 2, C.d_ramp, C.Cf, C.csize, C.cld);
     LAUNCH_OK("chol ramp scatter");
   }
   const int nslots = (int)P.slot_dst.size();
@@ -1350,7 +1502,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
     if (b > a) chunks.push_back({a, b - a});
   }
   const int nchunk = (int)chunks.size();
-  if (nchunk + 1 > (int)F->evs.size()) return api_fail(OPF_EINVAL, "chol: more period chunks than events");
+  if (!C.cyclic && nchunk + 1 > (int)F->evs.size()) return api_fail(OPF_EINVAL, "chol: more period chunks than events");
   std::vector<char> ready(T, 0);
   int kl = 0, kr = T - 1;
   double* UsL = F->Us;
@@ -1371,9 +1523,9 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   // nt = 2: fronts kl and kr in one batch (period stride kr - kl)
   auto chain_front = [&](int t, int nt, int t2, int u, double* Ub) -> int {
     Batch B;
-    B.F = {C.d_crec + (u ? 0 : 1), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
+    B.F = {C.d_crec + (u ? 1 : 0), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
            (int64_t)(t2 - t) * C.csize, (int64_t)(t2 - t) * C.dcsize, gg, C.dev.stop};
-    B.rec = C.crec + (u ? 0 : 1);
+    B.rec = C.crec + (u ? 1 : 0);
     B.n = 1;
     B.nt = nt;
     return factor_fronts(B, tol, repl, npert, F->cs);
@@ -1436,14 +1588,16 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
     }
     const int cb = CholOptions().col_block;
     hipLaunchKernelGGL(k_extend_root, dim3((G + cb - 1) / cb, nt), dim3(256), 0, st, C.dev, C.d_roots,
-                       (int32_t)P.roots.size(), cb, t0, C.Cf, C.csize, C.Ar);
+                       (int32_t)P.roots.size(), cb, t0, C.Cf, C.csize, (int64_t)C.cld, C.Ar);
     LAUNCH_OK("chol pg front assembly");
+    if (C.cyclic) continue;
     // the chain steps this chunk makes ready, on the chain stream
     if (hipEventRecord(F->evs[chunk_id], st) != hipSuccess || hipStreamWaitEvent(F->cs, F->evs[chunk_id], 0) != hipSuccess)
       return api_fail(OPF_EHIP, "chol: chain stream ordering");
     for (int t = t0; t < t0 + nt; ++t) ready[t] = 1;
     CHK(chain_steps(chunk_id + 1 == nchunk));
   }
+  if (C.cyclic) return factor_cyclic(C, tol, repl, npert, st);
   // front m: both sides' last updates, no update rows
   if (m >= 1) CHK(add_in(m, UsL));
   if (m + 1 <= T - 1) CHK(add_in(m, UsR));
@@ -1480,6 +1634,39 @@ int bwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, hipStream_t st) {
     while (n > 0 && (rec[n - 1].p - 1) / kNB <= q) --n;
   }
   LAUNCH_OK("chol backward panel");
+  return OPF_OK;
+}
+
+// The pg chain's two solves by cyclic reduction: the levels forward, then back.
+int solve_cyclic(CholInst& C, hipStream_t st) {
+  const int T = C.plan.T, G = C.plan.G;
+  const int64_t np = C.plan.n_p, o = C.plan.n_int;
+  auto level = [&](int h, int u) {
+    const int64_t s2 = 2 * (int64_t)h, t = h - 1;
+    return Tri{C.d_crec + u, C.Cf + t * C.csize, C.Dc + t * C.dcsize, C.Y + t * np + o, C.Z + t * np + o,
+               C.Wc + t * 2 * G, C.Gp, s2 * C.csize, s2 * C.dcsize, s2 * np, s2 * 2 * G, 2 * (int64_t)G};
+  };
+  constexpr int kAll = 1 << 30;  // one sum over all columns
+  int top = 1;
+  for (int h = 1; h <= T; h *= 2) {
+    const int n = T / h, c = (n + 1) / 2, u = c > 1 ? 2 : (n > 1 ? 1 : 0);
+    top = h;
+    const Tri A = level(h, u);
+    CHK(fwd_tri(A, C.crec + u, 1, c, kAll, nullptr, 0, st));
+    if (n == c) break;
+    hipLaunchKernelGGL(k_cyc_pull, dim3((G + 255) / 256, n - c), dim3(256), 0, st, (const double*)A.w, A.sw, c, G,
+                       C.Y + (2 * (int64_t)h - 1) * np + o, A.sy);
+    LAUNCH_OK("chol forward cyclic");
+  }
+  for (int h = top; h >= 1; h /= 2) {
+    const int n = T / h, c = (n + 1) / 2, u = c > 1 ? 2 : (n > 1 ? 1 : 0);
+    const Tri A = level(h, u);
+    if (u) {
+      hipLaunchKernelGGL(k_cyc_gemv, dim3((G + 3) / 4, c), dim3(256), 0, st, A, n, (const double*)A.y, h * np);
+      LAUNCH_OK("chol backward cyclic");
+    }
+    CHK(bwd_tri(A, C.crec + u, 1, c, st));
+  }
   return OPF_OK;
 }
 
@@ -1520,7 +1707,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   // fronts t and, when nb = 2, t2 as one batch
   auto chain = [&](int t, int nb, int t2) {
     const int64_t d = nb > 1 ? t2 - t : 0;
-    return Tri{C.d_crec + (t == m ? 1 : 0), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
+    return Tri{C.d_crec + (t == m ? 0 : 1), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
                C.Z + off(t), C.Wc + (int64_t)t * G, C.Gp, d * C.csize, d * C.dcsize, d * np, d * G, G};
   };
   // front m collects its two neighbours' updates (Wc), left then right; the
@@ -1531,7 +1718,9 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     LAUNCH_OK("chol forward chain");
     return OPF_OK;
   };
-  {
+  if (C.cyclic) {
+    CHK(solve_cyclic(C, st));
+  } else {
     int kl = 0, kr = T - 1;
     while (kl < m || kr > m) {
       const bool l = kl < m, r = kr > m;
@@ -1539,7 +1728,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
       // the two sides reach front m in different steps unless both end there
       const int nl = kl + 1, nr = kr - 1;
       double* next = (l && nl == m) || (r && nr == m) ? nullptr : C.Y + off(l ? nl : nr);
-      CHK(fwd_tri(chain(t, nb, kr), C.crec, 1, nb, kChainCols, next, nb > 1 ? (int64_t)(nr - nl) * np : 0, st));
+      CHK(fwd_tri(chain(t, nb, kr), C.crec + 1, 1, nb, kChainCols, next, nb > 1 ? (int64_t)(nr - nl) * np : 0, st));
       if (!next) {
         // one side may still have a neighbour other than m to pass on to
         if (l && nl != m) CHK(pull_to(nl, kl));
@@ -1550,12 +1739,12 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     }
     if (m >= 1) CHK(pull_to(m, m - 1));
     if (m + 1 <= T - 1) CHK(pull_to(m, m + 1));
-    CHK(fwd_tri(chain(m, 1, m), C.crec + 1, 1, 1, kChainCols, nullptr, 0, st));
+    CHK(fwd_tri(chain(m, 1, m), C.crec, 1, 1, kChainCols, nullptr, 0, st));
   }
   // backward along the pg chain: front m, then outwards (each front reads
   // its chain neighbour's solution, held in Y)
-  {
-    CHK(bwd_tri(chain(m, 1, m), C.crec + 1, 1, 1, st));
+  if (!C.cyclic) {
+    CHK(bwd_tri(chain(m, 1, m), C.crec, 1, 1, st));
     int kl = m - 1, kr = m + 1;
     while (kl >= 0 || kr <= T - 1) {
       const bool l = kl >= 0, r = kr <= T - 1;
@@ -1564,7 +1753,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
       hipLaunchKernelGGL(k_bwd_gemv, dim3((G + 3) / 4, nb, 1), dim3(256), 0, st, A, (const int32_t*)nullptr,
                          (const double*)(C.Y + off(l ? kl + 1 : kr - 1)), nb > 1 ? (int64_t)(kr - kl - 2) * np : 0);
       LAUNCH_OK("chol backward chain");
-      CHK(bwd_tri(A, C.crec, 1, nb, st));
+      CHK(bwd_tri(A, C.crec + 1, 1, nb, st));
       if (l) --kl;
       if (r) ++kr;
     }
