@@ -59,6 +59,16 @@ constexpr int kBwdCols = 16;     // earlier columns updated per block of a backw
 struct CDev {
   const int32_t *node_f, *node_p, *node_u, *rel, *kids, *rows;
   const int64_t *node_loff, *node_uoff, *node_woff, *row_ptr, *kid_ptr;
+  // extend-add: per node its rows by position in its parent's front (inv, -1:
+  // none); per column of a large front (col_off) or of the pg front (from
+  // col_root) the children with an entry there in their order, con[col[q]] ..
+  // con[col[q + 1] - 1]: where the child's column starts in the workspace and
+  // its inverse map in inv
+  const int32_t* inv;
+  const int64_t *inv_off, *col_off;
+  const int32_t* col;
+  const longlong2* con;
+  int64_t col_root;
   int64_t lsize, usize, wsize;
   int32_t n_p, n_int, G;
   const int32_t* stop;  // the static-pivot count when the factor stops at the first one, else NULL
@@ -109,16 +119,6 @@ __device__ __forceinline__ bool stopped(const int32_t* stop) {
   return seen > 0;
 }
 
-__device__ __forceinline__ int lower_bound_i32(const int32_t* a, int n, int v) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < v) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
 __global__ void k_fill(double* __restrict__ p, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0.0;
@@ -157,87 +157,75 @@ __global__ void k_scatter_ramp(const double* __restrict__ kv, int64_t k_off, int
     Cf[(int64_t)f * csize + (int64_t)g * cld + row + g] = kv[kp + ramp_pos[g]];
 }
 
-// Extend-add for the fronts of one level: work item (s, c0) owns columns
-// [c0, c0 + cb) of front s; it clears their update part, then adds each
-// child's update matrix entries that land there, child by child.
-__global__ void __launch_bounds__(256) k_extend(CDev D, const int32_t* __restrict__ items, int64_t item0,
-                                                int32_t cb, int32_t t0, double* __restrict__ Lf,
-                                                double* __restrict__ Ar) {
+// One column of a front by extend-add, by one wavefront: rows [j, n) of dst
+// (pivot columns: on top of what is there) plus the entries of the children
+// that have this column, child after child.  Every entry is written once.
+__device__ __forceinline__ void extend_column(const CDev& D, const double* __restrict__ Ut, int32_t q0, int32_t q1,
+                                              int j, int n, bool pivot, double* __restrict__ dst) {
+  constexpr int UN = 4;  // rows per lane in flight
+  const int lane = (int)threadIdx.x & 63;
+  for (int i0 = j + lane; i0 - lane < n; i0 += 64 * UN) {
+    double v[UN];
+#pragma unroll
+    for (int k = 0; k < UN; ++k) v[k] = pivot && i0 + 64 * k < n ? dst[i0 + 64 * k] : 0.0;
+    for (int32_t q = q0; q < q1; ++q) {
+      const longlong2 e = D.con[q];
+      const int32_t* inv = D.inv + e.y;
+      const double* Uc = Ut + e.x;
+      int ic[UN];
+      double w[UN];
+#pragma unroll
+      for (int k = 0; k < UN; ++k) ic[k] = i0 + 64 * k < n ? inv[i0 + 64 * k] : -1;
+#pragma unroll
+      for (int k = 0; k < UN; ++k) w[k] = ic[k] >= 0 ? Uc[ic[k]] : 0.0;
+#pragma unroll
+      for (int k = 0; k < UN; ++k) v[k] = ic[k] >= 0 ? v[k] + w[k] : v[k];
+    }
+#pragma unroll
+    for (int k = 0; k < UN; ++k)
+      if (i0 + 64 * k < n) dst[i0 + 64 * k] = v[k];
+  }
+}
+
+// Columns per extend-add item of a front of n rows: the longest columns a
+// wavefront or two, so that a few fronts still fill the chip.
+__host__ __device__ __forceinline__ int extend_cols(int n) { return n > 256 ? 8 : 32; }
+
+// Extend-add for the large fronts of one level: work item (s, c0) owns columns
+// [c0, c0 + extend_cols) of front s, one wavefront a column.  Gathered by the
+// front's entries through the children's inverse maps: each entry is read and
+// written once, where clearing the update part and adding child by child into
+// scattered entries took 4-6 times as long (1.9 of 11.5 ms per factorization
+// and solve of 2000 buses x 24 periods).
+__global__ void __launch_bounds__(256) k_extend(CDev D, const int32_t* __restrict__ items, int64_t item0, int32_t t0,
+                                                double* __restrict__ Lf, double* __restrict__ Ar) {
   if (stopped(D.stop)) return;
   const int tt = (int)blockIdx.y;
   const int s = items[2 * (item0 + blockIdx.x)], c0 = items[2 * (item0 + blockIdx.x) + 1];
   const int p = D.node_p[s], u = D.node_u[s], ld = p + u;
-  const int c1 = min(c0 + cb, ld);
+  const int c1 = min(c0 + extend_cols(ld), ld);
   double* L = Lf + (int64_t)(t0 + tt) * D.lsize + D.node_loff[s];
-  double* U = Ar + (int64_t)tt * D.usize + D.node_uoff[s];
-  for (int j = max(c0, p); j < c1; ++j)
-    for (int i = j + (int)threadIdx.x; i < ld; i += (int)blockDim.x) U[(int64_t)(j - p) * u + (i - p)] = 0.0;
-  __syncthreads();
-  for (int64_t q = D.kid_ptr[s]; q < D.kid_ptr[s + 1]; ++q) {
-    const int c = D.kids[q];
-    const int uc = D.node_u[c];
-    const int32_t* rel = D.rel + D.row_ptr[c];
-    const double* Uc = Ar + (int64_t)tt * D.usize + D.node_uoff[c];
-    const int b0 = lower_bound_i32(rel, uc, c0), b1 = lower_bound_i32(rel, uc, c1);
-    for (int b = b0; b < b1; ++b) {
-      const int j = rel[b];
-      double* dcol = j < p ? L + (int64_t)j * ld : U + (int64_t)(j - p) * u - p;  // row i at dcol[i]
-      const double* scol = Uc + (int64_t)b * uc;
-      // four entries per lane in flight: every load before any store (the
-      // child's entries of one column land on distinct parent entries)
-      constexpr int UN = 4;
-      const int bd = (int)blockDim.x;
-      for (int a = b + (int)threadIdx.x; a < uc; a += UN * bd) {
-        int ii[UN];
-        double vv[UN], pv[UN];
-#pragma unroll
-        for (int k = 0; k < UN; ++k) {
-          const int aa = a + k * bd;
-          ii[k] = aa < uc ? rel[aa] : -1;
-          vv[k] = aa < uc ? scol[aa] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < UN; ++k) pv[k] = ii[k] >= 0 ? dcol[ii[k]] : 0.0;
-#pragma unroll
-        for (int k = 0; k < UN; ++k)
-          if (ii[k] >= 0) dcol[ii[k]] = pv[k] + vv[k];
-      }
-    }
-    __syncthreads();
+  double* Ut = Ar + (int64_t)tt * D.usize;
+  double* U = Ut + D.node_uoff[s];
+  const int32_t* col = D.col + D.col_off[s];
+  for (int j = c0 + (int)(threadIdx.x >> 6); j < c1; j += 4) {
+    const int32_t q0 = col[j], q1 = col[j + 1];
+    if (j < p && q0 == q1) continue;
+    extend_column(D, Ut, q0, q1, j, ld, j < p, j < p ? L + (int64_t)j * ld : U + (int64_t)(j - p) * u - p);
   }
 }
 
 // The period's tree roots into its pg front (leading dimension ld, pivot block
-// only).
-__global__ void __launch_bounds__(256) k_extend_root(CDev D, const int32_t* __restrict__ roots, int32_t nroots,
-                                                     int32_t cb, int32_t t0, double* __restrict__ Cf, int64_t csize,
+// only), four columns per block.
+__global__ void __launch_bounds__(256) k_extend_root(CDev D, int32_t t0, double* __restrict__ Cf, int64_t csize,
                                                      int64_t ld, const double* __restrict__ Ar) {
   if (stopped(D.stop)) return;
-  const int tt = (int)blockIdx.y;
-  const int c0 = (int)blockIdx.x * cb, c1 = min(c0 + cb, D.G);
-  double* L = Cf + (int64_t)(t0 + tt) * csize;
-  for (int k = 0; k < nroots; ++k) {
-    const int c = roots[k];
-    const int uc = D.node_u[c];
-    const int32_t* rel = D.rel + D.row_ptr[c];
-    const double* Uc = Ar + (int64_t)tt * D.usize + D.node_uoff[c];
-    const int b0 = lower_bound_i32(rel, uc, c0), b1 = lower_bound_i32(rel, uc, c1);
-    for (int b = b0; b < b1; ++b) {
-      const int j = rel[b];
-      for (int a = b + (int)threadIdx.x; a < uc; a += (int)blockDim.x)
-        L[(int64_t)j * ld + rel[a]] += Uc[(int64_t)b * uc + a];
-    }
-    __syncthreads();
-  }
-}
-
-// Static pivot rule: d <= tol (or NaN) is replaced by repl and counted.
-__device__ __forceinline__ double pivot_sqrt(double d, double tol, double repl, int32_t* npert, bool count) {
-  if (!(d > tol)) {
-    d = repl;
-    if (count) atomicAdd(npert, 1);
-  }
-  return sqrt(d);
+  const int tt = (int)blockIdx.y, j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (j >= D.G) return;
+  const int32_t* col = D.col + D.col_root;
+  if (col[j] < col[j + 1])
+    extend_column(D, Ar + (int64_t)tt * D.usize, col[j], col[j + 1], j, D.G, true,
+                  Cf + (int64_t)(t0 + tt) * csize + (int64_t)j * ld);
 }
 
 // Broadcast of lane l's value to the whole wavefront (l uniform).
@@ -247,56 +235,6 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
   r.x = __builtin_amdgcn_readlane(w.x, l);
   r.y = __builtin_amdgcn_readlane(w.y, l);
   return __builtin_bit_cast(double, r);
-}
-
-// Right-looking elimination of the first p pivots of a front of order f <=
-// 64 held by one wavefront, lane i owning row i in registers (a[j] = entry
-// (i, j) for j <= i; the entries above the diagonal are scratch that no
-// valid entry ever reads, so the updates run unmasked).  Pivot d_k comes
-// from the broadcast diagonal; entry (j, k) of column k is broadcast from
-// lane j.  Fully unrolled so that every register index is a constant.
-__device__ __forceinline__ void chol_rows64(double (&a)[64], int p, int f, double tol, double repl,
-                                            int32_t* npert) {
-  const int i = (int)threadIdx.x;
-#pragma unroll
-  for (int k = 0; k < 64; ++k) {
-    if (k < p) {
-      const double d = pivot_sqrt(lane_bcast(a[k], k), tol, repl, npert, i == 0);
-      const double rd = 1.0 / d;
-      a[k] = i > k ? a[k] * rd : (i == k ? d : a[k]);
-#pragma unroll
-      for (int j = k + 1; j < 64; ++j) {
-        if (j < f) a[j] = fma(-a[k], lane_bcast(a[k], j), a[j]);
-      }
-    }
-  }
-}
-
-// Small fronts (p + u <= 64): one wavefront per (front, period), the front
-// in registers (one row per lane).
-__global__ void __launch_bounds__(64) k_factor_small(CDev D, const int32_t* __restrict__ list, int64_t l0,
-                                                     int32_t t0, double* __restrict__ Lf, double* __restrict__ Ar,
-                                                     double tol, double repl, int32_t* __restrict__ npert) {
-  if (stopped(D.stop)) return;
-  const int tt = (int)blockIdx.y;
-  const int s = list[l0 + blockIdx.x];
-  const int p = D.node_p[s], u = D.node_u[s], f = p + u;
-  const int i = (int)threadIdx.x;
-  double* L = Lf + (int64_t)(t0 + tt) * D.lsize + D.node_loff[s];
-  double* U = Ar + (int64_t)tt * D.usize + D.node_uoff[s];
-  double a[64];
-#pragma unroll
-  for (int j = 0; j < 64; ++j) {
-    a[j] = 0.0;
-    if (j < f && i >= j && i < f) a[j] = j < p ? L[(int64_t)j * f + i] : U[(int64_t)(j - p) * u + (i - p)];
-  }
-  chol_rows64(a, p, f, tol, repl, npert);
-#pragma unroll
-  for (int j = 0; j < 64; ++j)
-    if (j < f && i >= j && i < f) {
-      if (j < p) L[(int64_t)j * f + i] = a[j];
-      else U[(int64_t)(j - p) * u + (i - p)] = a[j];
-    }
 }
 
 // sqrt(d) and the reciprocal of that square root, both rounded as sqrt() and
@@ -349,6 +287,83 @@ __device__ __forceinline__ void odd_pivot(double d, const PivotRule& R, bool cou
 __device__ __forceinline__ bool is_odd(double d, double tol) {
   const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, d) >> 32);
   return hi - 0x20c00000u > 0x5f200000u - 0x20c00000u || !(d > tol);
+}
+
+// A small front (p + u = f <= FM <= 64) by one wavefront: lane i owns row i in
+// registers (entries above the diagonal are scratch that no valid entry ever
+// reads, so the updates run unmasked).  The children's update matrices are
+// gathered on the way in (no launch and no pass over memory of their own),
+// child after child.  The front moves one column left at every step, a[0]
+// always the column to eliminate, so that the steps are a loop of one body:
+// unrolled over the columns they spilled some 400 scalar registers.
+template <int FM>
+__device__ __forceinline__ void small_front(const CDev& D, int s, int p, int u, double* __restrict__ L,
+                                            double* __restrict__ Ut, const PivotRule& R, int& low) {
+  const int f = p + u, i = (int)threadIdx.x;
+  double a[FM];
+#pragma unroll
+  for (int j = 0; j < FM; ++j) a[j] = j < p && i >= j && i < f ? L[j * f + i] : 0.0;
+  for (int64_t q = D.kid_ptr[s]; q < D.kid_ptr[s + 1]; ++q) {
+    const int c = D.kids[q], uc = D.node_u[c];
+    const int ic = i < f ? D.inv[D.inv_off[c] + i] : -1;
+    const double* Uc = Ut + D.node_uoff[c];
+    // 8 columns' loads in flight (an entry the child does not have reads its
+    // first one)
+#pragma unroll
+    for (int j0 = 0; j0 < FM; j0 += 8) {
+      double w[8];
+      bool ok[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int jc = __builtin_amdgcn_readlane(ic, j0 + j);
+        ok[j] = jc >= 0 && ic >= jc;
+        w[j] = Uc[ok[j] ? jc * uc + ic : 0];
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) a[j0 + j] = ok[j] ? a[j0 + j] + w[j] : a[j0 + j];
+    }
+  }
+  for (int k = 0; k < p; ++k) {
+    double sq, r;
+    odd_pivot(lane_bcast(a[0], k), R, true, sq, r, low);
+    const double l = i == k ? sq : a[0] * r;
+    if (i >= k && i < f) L[k * f + i] = l;
+#pragma unroll
+    for (int j = 1; j < FM; ++j) a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
+    a[FM - 1] = 0.0;
+  }
+  double* U = Ut + D.node_uoff[s];
+#pragma unroll
+  for (int j = 0; j < FM; ++j)
+    if (j < u && i >= p + j && i < f) U[j * u + (i - p)] = a[j];
+}
+
+// The small fronts of one level, one wavefront per (front, period); those of
+// more than 32 rows in launches of their own (BIG), which need twice the
+// registers.
+template <bool BIG>
+__global__ void __launch_bounds__(64) k_factor_small(CDev D, const int32_t* __restrict__ list, int64_t l0, int32_t t0,
+                                                     double* __restrict__ Lf, double* __restrict__ Ar, double tol,
+                                                     double repl, int32_t* __restrict__ npert) {
+  if (stopped(D.stop)) return;
+  const int tt = (int)blockIdx.y, s = list[l0 + blockIdx.x];
+  const int p = D.node_p[s], u = D.node_u[s];
+  double* L = Lf + (int64_t)(t0 + tt) * D.lsize + D.node_loff[s];
+  double* Ut = Ar + (int64_t)tt * D.usize;
+  PivotRule R;
+  R.tol = tol;
+  sqrt_recip(repl, R.s_repl, R.r_repl);
+  int low = 0;
+  const int f = p + u;
+  if (BIG) {
+    if (f <= 48) small_front<48>(D, s, p, u, L, Ut, R, low);
+    else small_front<64>(D, s, p, u, L, Ut, R, low);
+  } else {
+    if (f <= 16) small_front<16>(D, s, p, u, L, Ut, R, low);
+    else if (f <= 24) small_front<24>(D, s, p, u, L, Ut, R, low);
+    else small_front<32>(D, s, p, u, L, Ut, R, low);
+  }
+  if (low && threadIdx.x == 0) atomicAdd(npert, low);
 }
 
 // Right-looking elimination of 16 columns, one row per lane, lanes 0-15 the
@@ -1170,7 +1185,10 @@ struct CholInst {
   CDev dev{};
   int32_t *d_node_f = nullptr, *d_node_p = nullptr, *d_node_u = nullptr, *d_rel = nullptr, *d_kids = nullptr,
           *d_rows = nullptr, *d_perm = nullptr, *d_items = nullptr, *d_small = nullptr, *d_roots = nullptr,
-          *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr;
+          *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr, *d_inv = nullptr, *d_col = nullptr;
+  int64_t *d_invoff = nullptr, *d_coloff = nullptr;
+  longlong2* d_con = nullptr;
+  std::vector<int64_t> lvl_item, lvl_big;  // per level: extend-add items; the first small front of more than 32 rows
   int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
           *d_slot = nullptr;
   double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *V = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
@@ -1263,6 +1281,74 @@ void release(opf_chol* F) {
     if (e_ != hipSuccess) return api_fail(OPF_EHIP, std::string(what) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// The extend-add's tables (see CDev and k_extend) and the small fronts' lists.
+int setup_extend(opf_chol* F, CholInst& C) {
+  const CholPlan& P = C.plan;
+  auto order = [&](int32_t s) { return P.node_p[s] + P.node_u[s]; };
+  std::vector<int32_t> inv, col, items, small;
+  std::vector<int64_t> inv_off(P.nnodes, 0), col_off(P.nnodes, 0);
+  std::vector<longlong2> con;
+  auto invert = [&](int32_t c, int32_t n) {
+    inv_off[c] = (int64_t)inv.size();
+    inv.resize(inv.size() + n, -1);
+    const int32_t* rel = P.rel.data() + P.row_ptr[c];
+    for (int32_t b = 0; b < P.node_u[c]; ++b) inv[inv_off[c] + rel[b]] = b;
+  };
+  // the columns of a front of n rows and the children that have them
+  auto columns = [&](int32_t n, const int32_t* k0, const int32_t* k1) {
+    const int64_t at = (int64_t)col.size();
+    std::vector<int32_t> cnt(n + 1, 0);
+    for (const int32_t* c = k0; c < k1; ++c)
+      for (int32_t b = 0; b < P.node_u[*c]; ++b) ++cnt[P.rel[P.row_ptr[*c] + b] + 1];
+    for (int32_t j = 0; j < n; ++j) cnt[j + 1] += cnt[j];
+    const int32_t base = (int32_t)con.size();
+    for (int32_t j = 0; j <= n; ++j) col.push_back(base + cnt[j]);
+    con.resize(con.size() + cnt[n]);
+    for (const int32_t* c = k0; c < k1; ++c)
+      for (int32_t b = 0; b < P.node_u[*c]; ++b)
+        con[base + cnt[P.rel[P.row_ptr[*c] + b]]++] =
+            make_longlong2(P.node_uoff[*c] + (int64_t)b * P.node_u[*c], inv_off[*c]);
+    return at;
+  };
+  C.lvl_item.assign(P.nlevels + 1, 0);
+  C.lvl_big.assign(P.nlevels, 0);
+  for (int32_t s = 0; s < P.nnodes; ++s) {
+    const int32_t *k0 = P.kids.data() + P.kid_ptr[s], *k1 = P.kids.data() + P.kid_ptr[s + 1];
+    for (const int32_t* c = k0; c < k1; ++c) invert(*c, order(s));
+    if (order(s) > kSmall) col_off[s] = columns(order(s), k0, k1);
+  }
+  for (int32_t c : P.roots) invert(c, P.G);
+  C.dev.col_root = columns(P.G, P.roots.data(), P.roots.data() + P.roots.size());
+  for (int32_t h = 0; h < P.nlevels; ++h) {
+    for (int64_t q = P.lvl_large_ptr[h]; q < P.lvl_large_ptr[h + 1]; ++q) {
+      const int32_t s = P.lvl_large[q], n = order(s);
+      for (int32_t c0 = 0; c0 < n; c0 += extend_cols(n)) {
+        items.push_back(s);
+        items.push_back(c0);
+      }
+    }
+    C.lvl_item[h + 1] = (int64_t)items.size() / 2;
+    for (int big = 0; big < 2; ++big) {
+      if (big) C.lvl_big[h] = (int64_t)small.size();
+      for (int64_t q = P.lvl_small_ptr[h]; q < P.lvl_small_ptr[h + 1]; ++q)
+        if ((order(P.lvl_small[q]) > 32) == (big == 1)) small.push_back(P.lvl_small[q]);
+    }
+  }
+  CHK(upload(F, items, &C.d_items));
+  CHK(upload(F, small, &C.d_small));
+  CHK(upload(F, inv, &C.d_inv));
+  CHK(upload(F, inv_off, &C.d_invoff));
+  CHK(upload(F, col, &C.d_col));
+  CHK(upload(F, col_off, &C.d_coloff));
+  CHK(upload(F, con, &C.d_con));
+  C.dev.inv = C.d_inv;
+  C.dev.inv_off = C.d_invoff;
+  C.dev.col = C.d_col;
+  C.dev.col_off = C.d_coloff;
+  C.dev.con = C.d_con;
+  return OPF_OK;
+}
+
 int setup_device(opf_chol* F, CholInst& C) {
   const CholPlan& P = C.plan;
   std::vector<int64_t> woff(P.nnodes, 0);  // per-front offsets of the forward update vectors
@@ -1288,7 +1374,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
   CHK(upload(F, std::vector<FrontRec>(C.crec, C.crec + 3), &C.d_crec));
-  std::vector<int32_t> items = P.items;
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
   CHK(upload(F, P.node_u, &C.d_node_u));
@@ -1296,8 +1381,7 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(upload(F, P.kids, &C.d_kids));
   CHK(upload(F, P.rows, &C.d_rows));
   CHK(upload(F, P.perm, &C.d_perm));
-  CHK(upload(F, items, &C.d_items));
-  CHK(upload(F, P.lvl_small, &C.d_small));
+  CHK(setup_extend(F, C));
   CHK(upload(F, P.roots, &C.d_roots));
   CHK(upload(F, P.kpos0, &C.d_kpos0));
   CHK(upload(F, P.kpos1, &C.d_kpos1));
@@ -1563,18 +1647,20 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
                        nslots, C.d_slot, C.d_kpos0, C.d_kpos1, C.Lf, P.lsize, C.Cf, C.csize);
     LAUNCH_OK("chol scatter");
     for (int h = 0; h < P.nlevels; ++h) {
-      const int64_t i0 = P.lvl_items_ptr[h], i1 = P.lvl_items_ptr[h + 1];
+      const int64_t i0 = C.lvl_item[h], i1 = C.lvl_item[h + 1];
       if (i1 > i0) {
-        hipLaunchKernelGGL(k_extend, dim3((unsigned)(i1 - i0), nt), dim3(256), 0, st, C.dev, C.d_items, i0,
-                           CholOptions().col_block, t0, C.Lf, C.Ar);
+        hipLaunchKernelGGL(k_extend, dim3((unsigned)(i1 - i0), nt), dim3(256), 0, st, C.dev, C.d_items, i0, t0, C.Lf,
+                           C.Ar);
         LAUNCH_OK("chol extend-add");
       }
-      const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1];
-      if (s1 > s0) {
-        hipLaunchKernelGGL(k_factor_small, dim3((unsigned)(s1 - s0), nt), dim3(64), 0, st, C.dev, C.d_small, s0, t0,
-                           C.Lf, C.Ar, tol, repl, npert);
-        LAUNCH_OK("chol small fronts");
-      }
+      const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1], sb = C.lvl_big[h];
+      if (sb > s0)
+        hipLaunchKernelGGL(k_factor_small<false>, dim3((unsigned)(sb - s0), nt), dim3(64), 0, st, C.dev, C.d_small, s0,
+                           t0, C.Lf, C.Ar, tol, repl, npert);
+      if (s1 > sb)
+        hipLaunchKernelGGL(k_factor_small<true>, dim3((unsigned)(s1 - sb), nt), dim3(64), 0, st, C.dev, C.d_small, sb,
+                           t0, C.Lf, C.Ar, tol, repl, npert);
+      LAUNCH_OK("chol small fronts");
       const int64_t q0 = P.lvl_large_ptr[h], q1 = P.lvl_large_ptr[h + 1];
       if (q1 > q0) {
         Batch B;
@@ -1586,9 +1672,8 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
         CHK(factor_fronts(B, tol, repl, npert, st));
       }
     }
-    const int cb = CholOptions().col_block;
-    hipLaunchKernelGGL(k_extend_root, dim3((G + cb - 1) / cb, nt), dim3(256), 0, st, C.dev, C.d_roots,
-                       (int32_t)P.roots.size(), cb, t0, C.Cf, C.csize, (int64_t)C.cld, C.Ar);
+    hipLaunchKernelGGL(k_extend_root, dim3((G + 3) / 4, nt), dim3(256), 0, st, C.dev, t0, C.Cf, C.csize,
+                       (int64_t)C.cld, C.Ar);
     LAUNCH_OK("chol pg front assembly");
     if (C.cyclic) continue;
     // the chain steps this chunk makes ready, on the chain stream
