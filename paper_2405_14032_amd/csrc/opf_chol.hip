@@ -53,7 +53,7 @@ constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 
 // iterate shows a changed elimination order at 1e-8, and small grids keep
 // theirs bit for bit.
 constexpr int kCycT = 64, kCycG = 1536;
-constexpr int kBwdCols = 16;     // earlier columns updated per block of a backward panel (a multiple of 4)
+constexpr int kBwdCols = 32;     // earlier columns updated per block of a backward launch, at least
 
 // Device view of one instance's plan.
 struct CDev {
@@ -84,12 +84,27 @@ struct FrontRec {
   int32_t p, u, ld, f, s;
 };
 
+// Front z of a batch: rec's, or the one given by value where rec is NULL (no
+// load before the first address), in scalar registers either way.
+__device__ __forceinline__ FrontRec pick_front(const FrontRec* __restrict__ rec, const FrontRec& one, int z) {
+  const FrontRec g = rec ? rec[z] : one;
+  constexpr int N = sizeof(FrontRec) / 4;
+  int32_t w[N];
+  __builtin_memcpy(w, &g, sizeof(g));
+#pragma unroll
+  for (int k = 0; k < N; ++k) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+  FrontRec f;
+  __builtin_memcpy(&f, w, sizeof(f));
+  return f;
+}
+
 // A batch of fronts for one launch (front blockIdx.z of rec, in falling order
 // of p: the ones that still have columns come first) over several periods
 // (blockIdx.y): the first period's storage and the strides from one to the
 // next.
 struct Fronts {
-  const FrontRec* rec;
+  const FrontRec* rec;  // NULL: the one front below
+  FrontRec one;
   double *L, *D, *U;
   int64_t sL, sD, sU;
   const int32_t* stop;  // as CDev::stop
@@ -455,7 +470,7 @@ __global__ void __launch_bounds__(kPT) k_panel(Fronts F, int32_t kbeg, int32_t k
   constexpr int NWV = kPT / 64;
   static_assert(NG == NWV && kTR == 64, "one row group per wavefront, one own row per lane");
   __shared__ double P[kNB * S];
-  const FrontRec f = F.rec[blockIdx.z];
+  const FrontRec f = pick_front(F.rec, F.one, blockIdx.z);
   const int rows = f.p + f.u, kb = min(kNB, f.p - k0);
   const int r0 = k0 + kb + (int)blockIdx.x * kTR;
   if (blockIdx.x > 0 && r0 >= rows) return;
@@ -635,7 +650,7 @@ k_update(Fronts F, int32_t k0, int32_t w, int32_t inner) {
   // two LDS buffers: the next round is loaded into registers while the
   // matrix cores work on the current one
   __shared__ double Pi[2][KC * S], Pj[2][KC * S];
-  const FrontRec f = F.rec[blockIdx.z];
+  const FrontRec f = pick_front(F.rec, F.one, blockIdx.z);
   const int rows = f.p + f.u, kb = min(w, f.p - k0), r0 = k0 + kb, cend = inner ? min(r0 + w, f.p) : rows;
   if (cend <= r0) return;
   const int R = (rows - r0 + TM - 1) / TM, Cn = (cend - r0 + TM - 1) / TM;
@@ -933,24 +948,39 @@ __global__ void __launch_bounds__(256) k_fwd_root_pull(CDev D, const int32_t* __
 // and diagonal blocks, right-hand side / solution y, forward solution z,
 // update vector w and its running sums v, each with its stride.
 struct Tri {
-  const FrontRec* rec;
+  const FrontRec* rec;  // NULL: the one front below
+  FrontRec one;
   const double *L, *D;
   double *y, *z, *w, *v;
   int64_t sL, sD, sy, sw, sv;
 };
 
-// The 64 x 64 triangle of a panel, solved by one wavefront for the entry v of
-// each lane (rows past kb: v = 0): lane i holds row i of the symmetric
-// diagonal block in registers (forward: its entries left of the diagonal,
-// backward those right of it, which are column i below the diagonal), and step
-// k broadcasts entry k.  64 dependent steps of a broadcast, a product with the
-// pivot's reciprocal and an update bound a panel launch of the solves.
+// The 64 x 64 triangle of a panel, solved by one wavefront: lane i holds row i
+// of the symmetric diagonal block in registers (forward: its entries left of
+// the diagonal, backward those right of it, which are column i below the
+// diagonal; 0 elsewhere), its entry v of the right-hand side and its pivot's
+// reciprocal.  Step k: every lane's product v r, of which lane k's is entry k
+// of the solution, broadcast, and one update -- four instructions, and 64 of
+// these steps are what a solve launch waits for.  Lanes past kb hold zeros.
+struct Triangle {
+  double t[64], r;
+};
 template <bool FWD>
-__device__ __forceinline__ double solve64(const double* __restrict__ D, int kb, int lane, double v) {
-  double t[64], x = 0.0;
+__device__ __forceinline__ void load64(Triangle& T, const double* __restrict__ D, int kb, int lane) {
+  const int at = min(lane, kb - 1);
 #pragma unroll
-  for (int k = 0; k < 64; ++k) t[k] = (k < kb && lane < kb && (FWD ? k < lane : k > lane)) ? D[k * kb + lane] : 0.0;
-  const double r = lane < kb ? 1.0 / D[lane * kb + lane] : 0.0;
+  for (int k = 0; k < 64; ++k) T.t[k] = D[min(k, kb - 1) * kb + at];
+  const double d = D[at * kb + at];
+  int ln = lane < kb ? lane : (FWD ? 0 : 64);
+  // the masks below are taken when they are needed (kept over a front's
+  // panels they would fill the scalar registers four times over)
+  asm volatile("" : "+v"(ln));
+#pragma unroll
+  for (int k = 0; k < 64; ++k) T.t[k] = (FWD ? k < ln : k > ln) ? T.t[k] : 0.0;
+  T.r = lane < kb ? 1.0 / d : 0.0;
+}
+template <bool FWD>
+__device__ __forceinline__ double solve64(const Triangle& T, int kb, double v) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int b = FWD ? q : 3 - q;
@@ -958,78 +988,170 @@ __device__ __forceinline__ double solve64(const double* __restrict__ D, int kb, 
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int k = b * 16 + (FWD ? j : 15 - j);
-      const double xk = lane_bcast(v, k) * lane_bcast(r, k);
-      x = lane == k ? xk : x;
-      v = fma(-t[k], xk, v);  // of use to the lanes still to come
+      v = fma(-T.t[k], lane_bcast(v * T.r, k), v);
     }
   }
-  return x;
+  return v * T.r;
 }
 
-// Forward, one panel [k0, k0+kb) of each front per launch, grid (row blocks
-// below the panel of the largest front, at least one; batch; fronts): a fifth
-// wavefront of every block solves the panel's triangle (solve64) while the
-// four others load their rows of the panel; block 0 stores the solution in z,
-// and each block gives its 256 rows below the panel their products: pivot rows
-// subtract theirs from y, update rows carry one running sum over the panels in
-// v.  y's panel entries are only read here and z is only written, so the
-// blocks of one launch never touch an entry another block writes.
+// Sum over a wavefront, the same in every lane: the butterfly over lane
+// distances 32, 16, 8, 4, 2, 1.  The first two swap halves and rows of 16
+// lanes; after them every row holds the same values, and the lanes of a row
+// repeat with the next distance's period, so a rotation within the row pairs
+// the same values as an exchange would.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, false),
+                                              __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, false)));
+}
+template <int N>
+__device__ __forceinline__ void wave_sum(double (&v)[N]) {
+  auto words = [](double x) { return __builtin_bit_cast(uint2, x); };
+  auto both = [](uint32_t x, uint32_t y) { return __builtin_bit_cast(double, make_uint2(x, y)); };
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const uint2 w = words(v[n]);
+    const auto x = __builtin_amdgcn_permlane32_swap(w.x, w.x, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(w.y, w.y, false, false);
+    v[n] = both(x[0], y[0]) + both(x[1], y[1]);
+  }
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    const uint2 w = words(v[n]);
+    const auto x = __builtin_amdgcn_permlane16_swap(w.x, w.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(w.y, w.y, false, false);
+    v[n] = both(x[0], y[0]) + both(x[1], y[1]);
+  }
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_move<0x128>(v[n]);  // row_ror:8
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_move<0x124>(v[n]);  // row_ror:4
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_move<0x122>(v[n]);  // row_ror:2
+#pragma unroll
+  for (int n = 0; n < N; ++n) v[n] += dpp_move<0x121>(v[n]);  // row_ror:1
+}
+
+// Forward, kSolve columns from k0 on of each front per launch, grid (row blocks
+// below them of the largest front, at least one; batch; fronts).  The launches
+// of a front follow one another, so a launch goes as far as one block can
+// alone: the columns' 64-column panels one after the other, each one's triangle
+// by one of two wavefronts in turn (solve64; the other loads the next), while
+// the others load their rows of the panel -- the rows of the later panels,
+// which every block repeats, and the block's own ROWS.  (A launch per panel
+// took 8 us, most of it the way to the first loads and back; four panels in
+// one 11.)  Block 0 stores the solution in z.  Each row takes a panel's products
+// as one sum: pivot rows subtract it from y, update rows carry one running sum
+// over the panels in v.  Of y the launch's own columns are only read and z is
+// only written, so the blocks of one launch never touch an entry another block
+// writes.
 // chunk 0 (interior fronts): the sum over all columns goes onto w at the last
 // panel.  chunk > 0 (the pg chain, a multiple of 64): the sums over chunk
 // columns are added up in w one after the other, from 0; at the last panel w
 // is also subtracted from next, the right-hand side of the chain neighbour
 // (stride sn), unless next is NULL.
-__global__ void __launch_bounds__(320) k_fwd_panel(Tri A, int32_t k0, int32_t chunk, double* __restrict__ next,
-                                                   int64_t sn) {
-  __shared__ double xs[64];
-  const FrontRec f = A.rec[blockIdx.z];
-  const int kb = min(kNB, f.p - k0), rows = f.p + f.u;
+constexpr int kSolve = 256;           // columns per launch
+constexpr int kInner = kSolve - kNB;  // of which rows of later panels
+template <int ROWS>
+__global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_t k0, int32_t chunk,
+                                                                   double* __restrict__ next, int64_t sn) {
+  __shared__ double xs[kNB], ys[kSolve];
+  const FrontRec f = pick_front(A.rec, A.one, blockIdx.z);
+  const int rows = f.p + f.u, kend = min(k0 + kSolve, f.p);
   const int tid = (int)threadIdx.x;
-  const int i = k0 + kb + (int)blockIdx.x * 256 + tid;
-  if (blockIdx.x > 0 && i - tid >= rows) return;
+  const int own = kend + (int)blockIdx.x * ROWS;  // first own row
+  if (blockIdx.x > 0 && own >= rows) return;
   const double* L = A.L + (int64_t)blockIdx.y * A.sL + f.L;
+  const double* D = A.D + (int64_t)blockIdx.y * A.sD + f.D;
   double* y = A.y + (int64_t)blockIdx.y * A.sy + f.f;
-  if (tid >= 256) {
-    const int lane = tid - 256;
-    const double x = solve64<true>(A.D + (int64_t)blockIdx.y * A.sD + f.D + (int64_t)k0 * kNB, kb, lane,
-                                   lane < kb ? y[k0 + lane] : 0.0);
-    xs[lane] = x;
-    if (blockIdx.x == 0 && lane < kb) A.z[(int64_t)blockIdx.y * A.sy + f.f + k0 + lane] = x;
-    __syncthreads();
+  double* z = A.z + (int64_t)blockIdx.y * A.sy + f.f;
+  if (tid >= kInner + ROWS) {
+    const int lane = tid & 63, odd = (tid - kInner - ROWS) >> 6;
+    Triangle T;
+    auto load = [&](int k) {
+      if (k < kend) load64<true>(T, D + (int64_t)k * kNB, min(kNB, kend - k), lane);
+    };
+    double v = lane < kend - k0 ? y[k0 + lane] : 0.0;
+    load(k0 + odd * kNB);
+    for (int k = k0, q = 0; k < kend; k += kNB, ++q) {
+      const int kb = min(kNB, kend - k);
+      const bool mine = (q & 1) == odd;
+      if (mine) {
+        const double x = solve64<true>(T, kb, v);
+        xs[lane] = x;
+        if (blockIdx.x == 0 && lane < kb) z[k + lane] = x;
+      }
+      __syncthreads();
+      if (mine) load(k + 2 * kNB);
+      __syncthreads();
+      v = k + kNB + lane < kend ? ys[k + kNB - k0 + lane] : 0.0;
+    }
     return;
   }
-  const bool row = i < rows;
-  const double* Li = L + (int64_t)k0 * f.ld + i;
-  double rv[64];
-#pragma unroll
-  for (int l = 0; l < 64; ++l) rv[l] = (row && l < kb) ? Li[(int64_t)l * f.ld] : 0.0;
+  const bool inner = tid < kInner;
+  const int i = inner ? k0 + kNB + tid : own + tid - kInner;
+  const bool row = i < (inner ? kend : rows);
   const int j = i - f.p;  // update row
+  const bool up = row && j >= 0;
+  // the row's entries of the panel, 16 at a time; rows of no use read row k0's
+  const int64_t ld = f.ld;
+  const double* Li = L + (row ? i : k0);
+  double rv[64];
+  auto load = [&](int k, int q) {
+    const double* at = Li + (int64_t)(k + q * 16) * ld;
+    if (k + q * 16 + 16 <= kend) {
+#pragma unroll
+      for (int l = 0; l < 16; ++l, at += ld) rv[q * 16 + l] = *at;
+    } else {
+#pragma unroll
+      for (int l = 0; l < 16; ++l, at += ld) rv[q * 16 + l] = k + q * 16 + l < kend ? *at : 0.0;
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < 4; ++q) load(k0, q);
+  // pivot rows: the right-hand side; update rows: the running sum, w and next
   double* w = A.w + (int64_t)blockIdx.y * A.sw + f.W + j;
   double* v = A.v + (int64_t)blockIdx.y * A.sv + f.W + j;
-  const bool first = chunk ? k0 % chunk == 0 : k0 == 0;
-  double acc = row && j >= 0 && !first ? *v : 0.0;
-  __syncthreads();
-  if (!row) return;
+  double yi = row && !up ? y[i] : 0.0;
+  double sum = up && (chunk ? k0 % chunk != 0 : k0 != 0) ? *v : 0.0;
+  double wi = up && (chunk ? k0 >= chunk : true) ? *w : 0.0;
+  for (int k = k0; k < kend; k += kNB) {
+    const int kb = min(kNB, kend - k);
+    __syncthreads();  // the panel's solution
+    // (an inner wavefront holds one panel's rows: none of them is below k then)
+    if (inner && (tid & ~63) + k0 < k) {
+      __syncthreads();
+      continue;
+    }
+    double acc = up && !(chunk && k % chunk == 0) ? sum : 0.0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (q * 16 >= kb) break;
+    for (int q = 0; q < 4; ++q) {
+      if (q * 16 < kb) {
 #pragma unroll
-    for (int l = q * 16; l < q * 16 + 16; ++l) acc += rv[l] * xs[l];
+        for (int l = q * 16; l < q * 16 + 16; ++l) acc += rv[l] * xs[l];
+      }
+      if (k + kNB < kend && !(inner && (tid & ~63) + k0 < k + kNB)) load(k + kNB, q);
+    }
+    if (up) {
+      sum = acc;
+      if (chunk && (k + kb == f.p || (k + kb) % chunk == 0)) wi += sum;
+    } else {
+      yi -= acc;
+      if (inner) ys[i - k0] = yi;
+    }
+    __syncthreads();
   }
-  if (j < 0) {
-    y[i] -= acc;
-    return;
-  }
-  const bool end = k0 + kb == f.p;
-  if (!chunk) {
-    if (end) *w += acc;
-    else *v = acc;
-  } else if (end || (k0 + kb) % chunk == 0) {
-    const double s = (k0 < chunk ? 0.0 : *w) + acc;
-    *w = s;
-    if (end && next) next[(int64_t)blockIdx.y * sn + j] -= s;
+  if (!row || inner) return;
+  if (!up) {
+    y[i] = yi;
+  } else if (!chunk) {
+    if (kend == f.p) *w = wi + sum;
+    else *v = sum;
   } else {
-    *v = acc;
+    *w = wi;
+    *v = sum;
+    if (kend == f.p && next) next[(int64_t)blockIdx.y * sn + j] -= wi;
   }
 }
 
@@ -1039,7 +1161,7 @@ __global__ void __launch_bounds__(320) k_fwd_panel(Tri A, int32_t k0, int32_t ch
 // blocks of 4; batch; fronts).
 __global__ void __launch_bounds__(256) k_bwd_gemv(Tri A, const int32_t* __restrict__ rows,
                                                   const double* __restrict__ x, int64_t sx) {
-  const FrontRec f = A.rec[blockIdx.z];
+  const FrontRec f = pick_front(A.rec, A.one, blockIdx.z);
   const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   const int lane = (int)(threadIdx.x & 63);
   if (j >= f.p) return;
@@ -1049,8 +1171,9 @@ __global__ void __launch_bounds__(256) k_bwd_gemv(Tri A, const int32_t* __restri
   double acc = 0.0;
 #pragma unroll 4
   for (int a = lane; a < f.u; a += 64) acc += col[a] * xs[rr ? rr[a] : a];
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) A.z[(int64_t)blockIdx.y * A.sy + f.f + j] -= acc;
+  double sum[1] = {acc};
+  wave_sum(sum);
+  if (lane == 0) A.z[(int64_t)blockIdx.y * A.sy + f.f + j] -= sum[0];
 }
 
 // Cyclic reduction, forward: what the level's c fronts subtract from the
@@ -1073,7 +1196,7 @@ __global__ void k_cyc_pull(const double* __restrict__ W, int64_t sw, int32_t c, 
 // front's own), one wavefront per column.  n as above.  Grid (column blocks of
 // 4; fronts).
 __global__ void __launch_bounds__(256) k_cyc_gemv(Tri A, int32_t n, const double* __restrict__ x, int64_t sh) {
-  const FrontRec f = A.rec[0];
+  const FrontRec f = A.one;
   const int i = (int)blockIdx.y, lane = (int)(threadIdx.x & 63);
   const int j = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (j >= f.p) return;
@@ -1088,52 +1211,88 @@ __global__ void __launch_bounds__(256) k_cyc_gemv(Tri A, int32_t n, const double
 #pragma unroll 4
     for (int a = lane; a < f.p; a += 64) acc += col[f.p + a] * xs[a - sh];
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) A.z[(int64_t)i * A.sy + j] -= acc;
+  double sum[1] = {acc};
+  wave_sum(sum);
+  if (lane == 0) A.z[(int64_t)i * A.sy + j] -= sum[0];
 }
 
-// Backward triangle L11^T x = z, one panel of each front per launch, the
-// panels from the last (panel q counted from there): a fifth wavefront of
-// every block solves the panel's triangle from z (panel entries only read
-// here), block 0 stores x in y, and each block's four other wavefronts, whose
-// loads overlap the triangle, subtract the panel's contribution from their
-// columns j < k0 of z (one wavefront per column, lanes over the panel's rows).
-// Grid (column blocks of kBwdCols; batch; fronts).
-__global__ void __launch_bounds__(320) k_bwd_panel(Tri A, int32_t q) {
-  __shared__ double xs[64];
-  const FrontRec f = A.rec[blockIdx.z];
-  const int k0 = ((f.p - 1) / kNB - q) * kNB;
-  if (k0 < 0) return;
-  const int kb = min(kNB, f.p - k0);
-  const int jb = (int)blockIdx.x * kBwdCols, je = min(jb + kBwdCols, k0);
+// Backward triangle L11^T x = z, kSolve columns of each front per launch, from
+// the last (the q-th kSolve columns counted from the front's last panel), as
+// the forward launch: the 64-column panels one after the other, each one's
+// triangle by one of the last two wavefronts in turn from z (the launch's own
+// columns are only read), the others subtract the panel's contribution from the columns of the
+// launch's earlier panels, which every block repeats (held in LDS), and from
+// the block's own columns of z before them: a column per wavefront, lanes over
+// the panel's rows, 4 columns' loads in flight.  Block 0 stores x in y.  Grid
+// (blocks of cols columns; batch; fronts).
+constexpr int kBwdT = 512 + 128;
+__global__ void __launch_bounds__(kBwdT) k_bwd_panel(Tri A, int32_t q, int32_t cols) {
+  __shared__ double xs[kNB], zs[kSolve];
+  const FrontRec f = pick_front(A.rec, A.one, blockIdx.z);
+  // the launch's columns [k0, kend), whole panels from the front's last one
+  const int np = (f.p + kNB - 1) / kNB, pe = np - q * (kSolve / kNB), pb = max(0, pe - kSolve / kNB);
+  if (pe <= 0) return;
+  const int k0 = pb * kNB, kend = min(pe * kNB, f.p);
+  const int jb = (int)blockIdx.x * cols, je = min(jb + cols, k0);
   if (blockIdx.x > 0 && jb >= k0) return;
   const double* L = A.L + (int64_t)blockIdx.y * A.sL + f.L;
+  const double* D = A.D + (int64_t)blockIdx.y * A.sD + f.D;
+  double* y = A.y + (int64_t)blockIdx.y * A.sy + f.f;
   double* z = A.z + (int64_t)blockIdx.y * A.sy + f.f;
   const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (wv == 4) {
-    const double x = solve64<false>(A.D + (int64_t)blockIdx.y * A.sD + f.D + (int64_t)k0 * kNB, kb, lane,
-                                    lane < kb ? z[k0 + lane] : 0.0);
-    xs[lane] = x;
-    if (blockIdx.x == 0 && lane < kb) A.y[(int64_t)blockIdx.y * A.sy + f.f + k0 + lane] = x;
-    __syncthreads();
+  for (int e = tid; e < kend - k0; e += kBwdT) zs[e] = z[k0 + e];
+  __syncthreads();
+  constexpr int NW = kBwdT / 64 - 2, UN = 4;
+  if (wv >= NW) {
+    const int odd = wv - NW;
+    Triangle T;
+    auto load = [&](int k) {
+      if (k >= k0) load64<false>(T, D + (int64_t)k * kNB, min(kNB, f.p - k), lane);
+    };
+    load((pe - 1 - odd) * kNB);
+    for (int k = (pe - 1) * kNB, c = 0; k >= k0; k -= kNB, ++c) {
+      const int kb = min(kNB, f.p - k);
+      const bool mine = (c & 1) == odd;
+      if (mine) {
+        const double x = solve64<false>(T, kb, lane < kb ? zs[k - k0 + lane] : 0.0);
+        xs[lane] = x;
+        if (blockIdx.x == 0 && lane < kb) y[k + lane] = x;
+      }
+      __syncthreads();
+      if (mine) load(k - 2 * kNB);
+      __syncthreads();
+    }
     return;
   }
-  constexpr int kPerWave = kBwdCols / 4;
-  double cv[kPerWave];
+  for (int k = (pe - 1) * kNB; k >= k0; k -= kNB) {
+    const int kb = min(kNB, f.p - k);
+    // columns: the launch's earlier ones, then the block's own
+    const int ni = k - k0, n = ni + max(0, je - jb);
+    bool waited = false;
+    for (int c0 = wv; c0 < n || !waited; c0 += NW * UN) {
+      double cv[UN];
 #pragma unroll
-  for (int c = 0; c < kPerWave; ++c) {
-    const int j = jb + wv + 4 * c;
-    cv[c] = (j < je && lane < kb) ? L[(int64_t)j * f.ld + k0 + lane] : 0.0;
-  }
-  __syncthreads();
+      for (int u = 0; u < UN; ++u) {
+        const int c = c0 + u * NW, j = c < ni ? k0 + c : jb + c - ni;
+        cv[u] = c < n && lane < kb ? L[(int64_t)j * f.ld + k + lane] : 0.0;
+      }
+      if (!waited) {
+        __syncthreads();  // the panel's solution
+        waited = true;
+      }
+      const double xk = xs[lane];
 #pragma unroll
-  for (int c = 0; c < kPerWave; ++c) {
-    const int j = jb + wv + 4 * c;
-    if (j < je) {
-      double acc = lane < kb ? cv[c] * xs[lane] : 0.0;
-      for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-      if (lane == 0) z[j] -= acc;
+      for (int u = 0; u < UN; ++u) cv[u] = lane < kb ? cv[u] * xk : 0.0;
+      wave_sum(cv);
+      // lane u keeps column u's
+      const double acc = lane == 0 ? cv[0] : lane == 1 ? cv[1] : lane == 2 ? cv[2] : cv[3];
+      const int c = c0 + lane * NW;
+      if (lane < UN && c < n) {
+        if (c < ni) zs[c] -= acc;
+        else z[jb + c - ni] -= acc;
+      }
     }
+    __syncthreads();
   }
 }
 
@@ -1198,7 +1357,7 @@ struct CholInst {
   bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends
   int32_t cld = 0;            // their leading dimension: 2 G or 3 G
   double* Uc = nullptr;       // cyclic reduction: a level's update blocks
-  FrontRec *d_rec = nullptr, *d_crec = nullptr;
+  FrontRec* d_rec = nullptr;
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
 };
@@ -1373,7 +1532,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   C.cld = (C.cyclic ? 3 : 2) * P.G;
   for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
-  CHK(upload(F, std::vector<FrontRec>(C.crec, C.crec + 3), &C.d_crec));
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
   CHK(upload(F, P.node_u, &C.d_node_u));
@@ -1526,7 +1684,7 @@ int factor_cyclic(CholInst& C, double tol, double repl, int32_t* npert, hipStrea
       LAUNCH_OK("chol cyclic clear");
     }
     Batch B;
-    B.F = {C.d_crec + u, C.Cf + (h - 1) * C.csize, C.Dc + (h - 1) * C.dcsize, C.Uc, s2 * C.csize, s2 * C.dcsize,
+    B.F = {nullptr, C.crec[u], C.Cf + (h - 1) * C.csize, C.Dc + (h - 1) * C.dcsize, C.Uc, s2 * C.csize, s2 * C.dcsize,
            (int64_t)ub * ub, C.dev.stop};
     B.rec = C.crec + u;
     B.n = 1;
@@ -1607,7 +1765,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   // nt = 2: fronts kl and kr in one batch (period stride kr - kl)
   auto chain_front = [&](int t, int nt, int t2, int u, double* Ub) -> int {
     Batch B;
-    B.F = {C.d_crec + (u ? 1 : 0), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
+    B.F = {nullptr, C.crec[u ? 1 : 0], C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
            (int64_t)(t2 - t) * C.csize, (int64_t)(t2 - t) * C.dcsize, gg, C.dev.stop};
     B.rec = C.crec + (u ? 1 : 0);
     B.n = 1;
@@ -1664,7 +1822,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
       const int64_t q0 = P.lvl_large_ptr[h], q1 = P.lvl_large_ptr[h + 1];
       if (q1 > q0) {
         Batch B;
-        B.F = {C.d_rec + q0, C.Lf + (int64_t)t0 * P.lsize, C.Df + (int64_t)t0 * C.dsize, C.Ar, P.lsize, C.dsize, P.usize,
+        B.F = {C.d_rec + q0, FrontRec(), C.Lf + (int64_t)t0 * P.lsize, C.Df + (int64_t)t0 * C.dsize, C.Ar, P.lsize, C.dsize, P.usize,
                C.dev.stop};
         B.rec = C.rec.data() + q0;
         B.n = (int)(q1 - q0);
@@ -1695,28 +1853,38 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
 }
 
 // Forward / backward triangle of a batch of fronts (nb batch entries, in
-// falling order of p) by panels, see k_fwd_panel / k_bwd_panel: y is the
+// falling order of p), see k_fwd_panel / k_bwd_panel: y is the
 // right-hand side in, z the forward solution; the backward pass reads z and
 // leaves x in y.
 int fwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, int chunk, double* next, int64_t sn, hipStream_t st) {
-  for (int k0 = 0; n > 0; k0 += kNB) {
-    int g = 1;
-    for (int i = 0; i < n; ++i) {
-      const int below = rec[i].p + rec[i].u - k0 - std::min(kNB, rec[i].p - k0);
-      g = std::max(g, (below + 255) / 256);
-    }
-    hipLaunchKernelGGL(k_fwd_panel, dim3(g, nb, n), dim3(320), 0, st, A, k0, chunk, next, sn);
-    while (n > 0 && rec[n - 1].p <= k0 + kNB) --n;
+  for (int k0 = 0; n > 0; k0 += kSolve) {
+    int below = 1;
+    for (int i = 0; i < n; ++i) below = std::max(below, rec[i].p + rec[i].u - std::min(k0 + kSolve, rec[i].p));
+    // 64 rows per block while those blocks fit the chip at once (one CU loads
+    // no more than about 64 bytes a cycle), else 192, as every block repeats
+    // the launch's triangles
+    if ((int64_t)(below + 63) / 64 * nb * n <= 512)
+      hipLaunchKernelGGL(k_fwd_panel<64>, dim3((below + 63) / 64, nb, n), dim3(kInner + 64 + 128), 0, st, A, k0, chunk,
+                         next, sn);
+    else
+      hipLaunchKernelGGL(k_fwd_panel<192>, dim3((below + 191) / 192, nb, n), dim3(kInner + 192 + 128), 0, st, A, k0,
+                         chunk, next, sn);
+    while (n > 0 && rec[n - 1].p <= k0 + kSolve) --n;
   }
   LAUNCH_OK("chol forward panel");
   return OPF_OK;
 }
 
 int bwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, hipStream_t st) {
+  constexpr int per = kSolve / kNB;
   for (int q = 0; n > 0; ++q) {
-    const int k0 = ((rec[0].p - 1) / kNB - q) * kNB;
-    hipLaunchKernelGGL(k_bwd_panel, dim3(std::max(1, (k0 + kBwdCols - 1) / kBwdCols), nb, n), dim3(320), 0, st, A, q);
-    while (n > 0 && (rec[n - 1].p - 1) / kNB <= q) --n;
+    const int k0 = std::max(0, (rec[0].p + kNB - 1) / kNB - (q + 1) * per) * kNB;  // columns before the launch's
+    // as few columns per block as leave it no more of them than the chip takes
+    // at once: each block repeats the launch's triangles
+    int cols = kBwdCols;
+    while (cols < 1024 && (int64_t)(k0 + cols - 1) / cols * nb * n > 512) cols *= 2;
+    hipLaunchKernelGGL(k_bwd_panel, dim3(std::max(1, (k0 + cols - 1) / cols), nb, n), dim3(kBwdT), 0, st, A, q, cols);
+    while (n > 0 && (rec[n - 1].p + kNB - 1) / kNB <= (q + 1) * per) --n;
   }
   LAUNCH_OK("chol backward panel");
   return OPF_OK;
@@ -1728,7 +1896,7 @@ int solve_cyclic(CholInst& C, hipStream_t st) {
   const int64_t np = C.plan.n_p, o = C.plan.n_int;
   auto level = [&](int h, int u) {
     const int64_t s2 = 2 * (int64_t)h, t = h - 1;
-    return Tri{C.d_crec + u, C.Cf + t * C.csize, C.Dc + t * C.dcsize, C.Y + t * np + o, C.Z + t * np + o,
+    return Tri{nullptr, C.crec[u], C.Cf + t * C.csize, C.Dc + t * C.dcsize, C.Y + t * np + o, C.Z + t * np + o,
                C.Wc + t * 2 * G, C.Gp, s2 * C.csize, s2 * C.dcsize, s2 * np, s2 * 2 * G, 2 * (int64_t)G};
   };
   constexpr int kAll = 1 << 30;  // one sum over all columns
@@ -1763,7 +1931,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   hipLaunchKernelGGL(k_gather, dim3(grid_for(np * T, 256)), dim3(256), 0, st, b + I.x_off, P.n_p, T, C.d_perm, C.Y);
   LAUNCH_OK("chol gather");
   auto tree = [&](int64_t q0) {
-    return Tri{C.d_rec + q0, C.Lf, C.Df, C.Y, C.Z, C.W, C.V, P.lsize, C.dsize, np, C.wsize, C.wsize};
+    return Tri{C.d_rec + q0, FrontRec(), C.Lf, C.Df, C.Y, C.Z, C.W, C.V, P.lsize, C.dsize, np, C.wsize, C.wsize};
   };
   // forward through the interior trees, all periods at once (small fronts
   // leave their forward solution in Y, large ones in Z)
@@ -1792,7 +1960,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   // fronts t and, when nb = 2, t2 as one batch
   auto chain = [&](int t, int nb, int t2) {
     const int64_t d = nb > 1 ? t2 - t : 0;
-    return Tri{C.d_crec + (t == m ? 0 : 1), C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
+    return Tri{nullptr, C.crec[t == m ? 0 : 1], C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
                C.Z + off(t), C.Wc + (int64_t)t * G, C.Gp, d * C.csize, d * C.dcsize, d * np, d * G, G};
   };
   // front m collects its two neighbours' updates (Wc), left then right; the
