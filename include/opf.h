@@ -502,9 +502,11 @@ typedef struct {
 void opf_ipm_default_options(opf_ipm_options *opt);
 /* chol: opf_chol_analyze of the same model.  x_out: device [n], receives
  * the final primal point; y_out: device [m] or NULL, the final multipliers
- * of c(x) - s = 0.  opt NULL = defaults.  Allocates its work vectors on the
- * model's device for the duration of the call and synchronises the model's
- * stream once per iteration (and once per line-search trial).  Returns
+ * of c(x) - s = 0.  opt NULL = defaults.  Its work vectors (about 13 n + 17 m +
+ * nnz_jac + nnz_hess + nnz_kkt doubles on the model's device) are allocated by
+ * the first call and kept in the factor object until that is destroyed.
+ * Synchronises the model's stream once per iteration (and once per line-search
+ * trial).  Returns
  * OPF_OK also when the iteration limit or a stall stops it
  * (res->converged = 0, res->status says which); OPF_EINVAL on bad options, a non-finite
  * iterate (any non-finite residual) or a failed inertia correction;

@@ -19,4 +19,8 @@ const std::vector<InstHost>& model_insts(const opf_model* M);
 int64_t model_n(const opf_model* M);
 int64_t model_nnzk(const opf_model* M);
 const opf_model* chol_model(const opf_chol* F);  // the model F was analysed from
+// Device memory of the factor object for a caller's work vectors: at least
+// bytes, uninitialised, valid until the next call on F or until F is destroyed.
+// Grown when a call asks for more, otherwise the same block again.
+int chol_workspace(opf_chol* F, size_t bytes, void** out);
 }  // namespace opf

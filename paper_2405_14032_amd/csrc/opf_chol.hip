@@ -1382,11 +1382,26 @@ struct opf_chol {
   bool use_graph = true;
   bool stop_on_pivot = false;  // skip the rest of a factorization after its first static pivot
   std::vector<void*> allocs;
+  void* work = nullptr;  // chol_workspace
+  size_t work_bytes = 0;
   double flops = 0.0, flops_int = 0.0;
   int64_t factor_entries = 0, arena_entries = 0;
 };
 
 const opf_model* opf::chol_model(const opf_chol* F) { return F ? F->model : nullptr; }
+
+int opf::chol_workspace(opf_chol* F, size_t bytes, void** out) {
+  if (bytes > F->work_bytes) {
+    if (F->work) (void)hipFree(F->work);
+    F->work = nullptr;
+    F->work_bytes = 0;
+    if (hipMalloc(&F->work, bytes) != hipSuccess)
+      return api_fail(OPF_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
+    F->work_bytes = bytes;
+  }
+  *out = F->work;
+  return OPF_OK;
+}
 
 namespace {
 
@@ -1426,6 +1441,8 @@ int dalloc(opf_chol* F, int64_t n, double** d) {
 void release(opf_chol* F) {
   for (void* p : F->allocs) (void)hipFree(p);
   F->allocs.clear();
+  if (F->work) (void)hipFree(F->work);
+  F->work = nullptr;
 }
 
 #define CHK(x)                      \
