@@ -1208,12 +1208,7 @@ int opf_set_load(opf_model* M, const double* pd, const double* qd) {
   OPF_CHECK_MODEL(M);
   OPF_REQUIRE(pd && qd, "pd / qd");
   DeviceGuard g(M->device);
-  for (size_t k = 0; k < M->inst.size(); ++k) {
-    const InstHost& I = M->inst[k];
-    const size_t bytes = (size_t)I.T * I.N * sizeof(double);
-    OPF_HIP(hipMemcpyAsync(M->h_dev[k].pd, pd + I.ld_off, bytes, hipMemcpyDeviceToDevice, M->stream));
-    OPF_HIP(hipMemcpyAsync(M->h_dev[k].qd, qd + I.ld_off, bytes, hipMemcpyDeviceToDevice, M->stream));
-  }
+  OPF_LAUNCHED(launch_set_load(launch_of(M, OP_LADJ), pd, qd), "load kernel");
   return OPF_OK;
 }
 

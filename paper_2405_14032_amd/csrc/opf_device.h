@@ -240,6 +240,7 @@ hipError_t launch_jac_struct(const Launch& L, int32_t* rows, int32_t* cols);
 hipError_t launch_hess_struct(const Launch& L, int32_t* rows, int32_t* cols);
 hipError_t launch_kkt_struct(const Launch& L, int ninst, int64_t* rowptr, int32_t* colind);
 hipError_t launch_bounds(const Launch& L, double* lv, double* uv, double* lc, double* uc);
+hipError_t launch_set_load(const Launch& L, const double* pd, const double* qd);
 hipError_t launch_load_adjoint(const Launch& L, const double* lam, double* gpd, double* gqd);
 
 }  // namespace opf
