@@ -576,9 +576,26 @@ int build_fused(opf_model* M) {
 }
 
 // The default shape of an op, or narrower tiles when a tile's K rows do
-// not fit the LDS budget (buses of high degree).
+// not fit the LDS budget (buses of high degree).  256 elements and one period
+// per tile, except in the whole sweep:
+//   * the bus pass has blocks of one wavefront (nothing its wavefronts share is
+//     worth waiting for each other: 0-8 % at every size measured);
+//   * the line pass, where the model has few wavefronts of lines and generators
+//     for the chip's 1024 SIMDs, too: with at most one per SIMD one period each
+//     (1000 buses x 8 periods 27.6 -> 23.8 us a sweep, 300 x 24 26.8 -> 24.3),
+//     up to three per SIMD two periods, the second one's loads behind the first
+//     (2000 x 24 44.1 -> 40.2, 2000 x 48 70 -> 64); beyond, blocks of 256 share
+//     their K rows' writes better (6000 x 24 82.6 us against 86.6, 2000 x 168
+//     159 against 182).
 int set_default_shape(opf_model* M, int op) {
   Shape s;
+  if (op == OP_SWB) s.block = 64;
+  if (op == OP_SWA) {
+    int64_t waves = 0;
+    for (const auto& I : M->inst) waves += (int64_t)I.T * ((I.B + 63) / 64 + (I.G + 63) / 64);
+    if (waves <= 3 * 1024) s.block = 64;
+    if (waves > 1024 && waves <= 3 * 1024) s.ppt = 2;
+  }
   int rc = set_shape(M, op, s);
   for (int blk = s.block / 2; rc == OPF_EINVAL && blk >= 64; blk /= 2) {
     s.block = blk;
