@@ -65,9 +65,12 @@ struct CDev {
   // con[col[q + 1] - 1]: where the child's column starts in the workspace and
   // its inverse map in inv
   const int32_t* inv;
-  const int64_t *inv_off, *col_off;
+  const int64_t* col_off;
   const int32_t* col;
   const longlong2* con;
+  // per child, in kid_ptr's order: where its update matrix and its inverse map
+  // start, its rows
+  const longlong4* kid;
   int64_t col_root;
   int64_t lsize, usize, wsize;
   int32_t n_p, n_int, G;
@@ -108,6 +111,7 @@ struct Fronts {
   double *L, *D, *U;
   int64_t sL, sD, sU;
   const int32_t* stop;  // as CDev::stop
+  int32_t fresh;        // the update blocks hold nothing yet: the first trailing update stores into them
 };
 
 // The factored 64 x 64 diagonal blocks of a blocked front live apart from
@@ -134,9 +138,14 @@ __device__ __forceinline__ bool stopped(const int32_t* stop) {
   return seen > 0;
 }
 
-__global__ void k_fill(double* __restrict__ p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
+// The start of a factorization: factor blocks, pg fronts and (where given) the
+// count of static pivots cleared.
+__global__ void k_clear(double* __restrict__ p, int64_t n, double* __restrict__ q, int64_t m,
+                        int32_t* __restrict__ npert) {
+  const int64_t at = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (at == 0 && npert) *npert = 0;
+  for (int64_t i = at; i < n; i += step) p[i] = 0.0;
+  for (int64_t i = at; i < m; i += step) q[i] = 0.0;
 }
 
 // K's template slots of periods t0 .. t0+nt-1 into the factor blocks (or the
@@ -318,10 +327,15 @@ __device__ __forceinline__ void small_front(const CDev& D, int s, int p, int u, 
   double a[FM];
 #pragma unroll
   for (int j = 0; j < FM; ++j) a[j] = j < p && i >= j && i < f ? L[j * f + i] : 0.0;
-  for (int64_t q = D.kid_ptr[s]; q < D.kid_ptr[s + 1]; ++q) {
-    const int c = D.kids[q], uc = D.node_u[c];
-    const int ic = i < f ? D.inv[D.inv_off[c] + i] : -1;
-    const double* Uc = Ut + D.node_uoff[c];
+  // the next child's map is on its way while one is added
+  const int64_t q0 = D.kid_ptr[s], q1 = D.kid_ptr[s + 1];
+  const int at = min(i, f - 1);
+  int icn = q0 < q1 ? D.inv[D.kid[q0].y + at] : -1;
+  for (int64_t q = q0; q < q1; ++q) {
+    const longlong4 kd = D.kid[q];
+    const int uc = (int)kd.z, ic = i < f ? icn : -1;
+    const double* Uc = Ut + kd.x;
+    if (q + 1 < q1) icn = D.inv[D.kid[q + 1].y + at];
     // 8 columns' loads in flight (an entry the child does not have reads its
     // first one)
 #pragma unroll
@@ -754,6 +768,7 @@ k_update(Fronts F, int32_t k0, int32_t w, int32_t inner) {
     buf ^= 1;
   }
   if (skip) return;
+  const bool fresh = F.fresh && k0 == 0;
 #pragma unroll
   for (int c = 0; c < N; ++c)
 #pragma unroll
@@ -763,18 +778,25 @@ k_update(Fronts F, int32_t k0, int32_t w, int32_t inner) {
       for (int e = 0; e < 4; ++e) {
         const int j = j0 + wc * W + c * 16 + lk + 4 * e;
         if (i >= rows || j >= cend || i < j) continue;
-        if (j < f.p) L[(int64_t)j * ld + i] -= acc[c][r][e];
-        else U[(int64_t)(j - f.p) * f.u + (i - f.p)] -= acc[c][r][e];
+        if (j < f.p) {
+          L[(int64_t)j * ld + i] -= acc[c][r][e];
+        } else {
+          double* q = U + (int64_t)(j - f.p) * f.u + (i - f.p);
+          *q = (fresh ? 0.0 : *q) - acc[c][r][e];
+        }
       }
     }
 }
 
-// G x G lower update block of pg front t-1 into the pivot block of front t.
-__global__ void k_add_chain(const double* __restrict__ Us, int32_t G, double* __restrict__ C) {
+// G x G lower update blocks of the pg fronts before them into the pivot blocks
+// of fronts: entry blockIdx.y of both sides.
+__global__ void k_add_chain(const double* __restrict__ Us, int64_t sU, int32_t G, double* __restrict__ C, int64_t sC) {
+  const double* U = Us + (int64_t)blockIdx.y * sU;
+  double* c = C + (int64_t)blockIdx.y * sC;
   const int64_t n = (int64_t)G * G;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t j = e / G, i = e % G;
-    if (i >= j) C[j * 2 * G + i] += Us[e];
+    if (i >= j) c[j * 2 * G + i] += U[e];
   }
 }
 
@@ -836,8 +858,14 @@ __global__ void __launch_bounds__(256) k_cyc_link(const double* __restrict__ Ub,
 }
 
 // ------------------------------------------------------------------ solves
-__global__ void k_sub(double* __restrict__ y, const double* __restrict__ w, int32_t n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) y[i] -= w[i];
+// y -= u, then -= w (either may be NULL).
+__global__ void k_sub(double* __restrict__ y, const double* __restrict__ u, const double* __restrict__ w, int32_t n) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    double v = y[i];
+    if (u) v -= u[i];
+    if (w) v -= w[i];
+    y[i] = v;
+  }
 }
 
 __global__ void k_gather(const double* __restrict__ b, int32_t n_p, int32_t T, const int32_t* __restrict__ perm,
@@ -1050,12 +1078,13 @@ __device__ __forceinline__ void wave_sum(double (&v)[N]) {
 // panel.  chunk > 0 (the pg chain, a multiple of 64): the sums over chunk
 // columns are added up in w one after the other, from 0; at the last panel w
 // is also subtracted from next, the right-hand side of the chain neighbour
-// (stride sn), unless next is NULL.
+// (stride sn), by the batch entries whose bit in pass is set.
 constexpr int kSolve = 256;           // columns per launch
 constexpr int kInner = kSolve - kNB;  // of which rows of later panels
 template <int ROWS>
 __global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_t k0, int32_t chunk,
-                                                                   double* __restrict__ next, int64_t sn) {
+                                                                   double* __restrict__ next, int64_t sn,
+                                                                   int32_t pass) {
   __shared__ double xs[kNB], ys[kSolve];
   const FrontRec f = pick_front(A.rec, A.one, blockIdx.z);
   const int rows = f.p + f.u, kend = min(k0 + kSolve, f.p);
@@ -1151,7 +1180,7 @@ __global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_
   } else {
     *w = wi;
     *v = sum;
-    if (kend == f.p && next) next[(int64_t)blockIdx.y * sn + j] -= wi;
+    if (kend == f.p && blockIdx.y < 2 && (pass >> blockIdx.y & 1)) next[(int64_t)blockIdx.y * sn + j] -= wi;
   }
 }
 
@@ -1345,8 +1374,9 @@ struct CholInst {
   int32_t *d_node_f = nullptr, *d_node_p = nullptr, *d_node_u = nullptr, *d_rel = nullptr, *d_kids = nullptr,
           *d_rows = nullptr, *d_perm = nullptr, *d_items = nullptr, *d_small = nullptr, *d_roots = nullptr,
           *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr, *d_inv = nullptr, *d_col = nullptr;
-  int64_t *d_invoff = nullptr, *d_coloff = nullptr;
+  int64_t* d_coloff = nullptr;
   longlong2* d_con = nullptr;
+  longlong4* d_kid = nullptr;
   std::vector<int64_t> lvl_item, lvl_big;  // per level: extend-add items; the first small front of more than 32 rows
   int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
           *d_slot = nullptr;
@@ -1494,6 +1524,8 @@ int setup_extend(opf_chol* F, CholInst& C) {
     if (order(s) > kSmall) col_off[s] = columns(order(s), k0, k1);
   }
   for (int32_t c : P.roots) invert(c, P.G);
+  std::vector<longlong4> kid;
+  for (int32_t c : P.kids) kid.push_back(make_longlong4(P.node_uoff[c], inv_off[c], P.node_u[c], 0));
   C.dev.col_root = columns(P.G, P.roots.data(), P.roots.data() + P.roots.size());
   for (int32_t h = 0; h < P.nlevels; ++h) {
     for (int64_t q = P.lvl_large_ptr[h]; q < P.lvl_large_ptr[h + 1]; ++q) {
@@ -1513,15 +1545,15 @@ int setup_extend(opf_chol* F, CholInst& C) {
   CHK(upload(F, items, &C.d_items));
   CHK(upload(F, small, &C.d_small));
   CHK(upload(F, inv, &C.d_inv));
-  CHK(upload(F, inv_off, &C.d_invoff));
   CHK(upload(F, col, &C.d_col));
   CHK(upload(F, col_off, &C.d_coloff));
   CHK(upload(F, con, &C.d_con));
+  CHK(upload(F, kid, &C.d_kid));
   C.dev.inv = C.d_inv;
-  C.dev.inv_off = C.d_invoff;
   C.dev.col = C.d_col;
   C.dev.col_off = C.d_coloff;
   C.dev.con = C.d_con;
+  C.dev.kid = C.d_kid;
   return OPF_OK;
 }
 
@@ -1696,13 +1728,9 @@ int factor_cyclic(CholInst& C, double tol, double repl, int32_t* npert, hipStrea
   for (int h = 1; h <= T; h *= 2) {
     const int n = T / h, c = (n + 1) / 2, u = c > 1 ? 2 : (n > 1 ? 1 : 0), ub = u * G;
     const int64_t s2 = 2 * (int64_t)h;  // from one eliminated front to the next
-    if (u) {
-      hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)c * ub * ub, 256)), dim3(256), 0, st, C.Uc, (int64_t)c * ub * ub);
-      LAUNCH_OK("chol cyclic clear");
-    }
     Batch B;
     B.F = {nullptr, C.crec[u], C.Cf + (h - 1) * C.csize, C.Dc + (h - 1) * C.dcsize, C.Uc, s2 * C.csize, s2 * C.dcsize,
-           (int64_t)ub * ub, C.dev.stop};
+           (int64_t)ub * ub, C.dev.stop, 1};
     B.rec = C.crec + u;
     B.n = 1;
     B.nt = c;
@@ -1720,14 +1748,14 @@ int factor_cyclic(CholInst& C, double tol, double repl, int32_t* npert, hipStrea
   return OPF_OK;
 }
 
-int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double repl, int32_t* npert,
+int factor_inst(opf_chol* F, CholInst& C, bool first, const double* kv, double tol, double repl, int32_t* npert,
                 hipStream_t st) {
   const CholPlan& P = C.plan;
   const InstHost& I = *C.I;
   const int T = P.T, G = P.G;
-  hipLaunchKernelGGL(k_fill, dim3(grid_for(P.lsize * T, 256)), dim3(256), 0, st, C.Lf, P.lsize * T);
-  hipLaunchKernelGGL(k_fill, dim3(grid_for(C.csize * T, 256)), dim3(256), 0, st, C.Cf, C.csize * T);
-  LAUNCH_OK("chol fill");
+  hipLaunchKernelGGL(k_clear, dim3(grid_for(std::max(P.lsize, C.csize) * T, 256)), dim3(256), 0, st, C.Lf, P.lsize * T,
+                     C.Cf, C.csize * T, first ? npert : (int32_t*)nullptr);
+  LAUNCH_OK("chol clear");
   // every ramp pair up front: they land in the pg front of the period
   // before, which the chain stream may be factoring while a later chunk's
   // interior runs
@@ -1769,21 +1797,17 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
   const int64_t gg = (int64_t)G * G;
   // front t's incoming chain update (from t-1 on the left, t+1 on the
   // right) into its pivot block
-  auto add_in = [&](int t, const double* Ub) -> int {
-    hipLaunchKernelGGL(k_add_chain, dim3(grid_for(gg, 256)), dim3(256), 0, F->cs, Ub, G, C.Cf + (int64_t)t * C.csize);
+  auto add_in = [&](int t, const double* Ub, int n = 1, int t2 = 0) -> int {
+    hipLaunchKernelGGL(k_add_chain, dim3(grid_for(gg, 256), n), dim3(256), 0, F->cs, Ub, gg, G,
+                       C.Cf + (int64_t)t * C.csize, n > 1 ? (t2 - t) * C.csize : 0);
     LAUNCH_OK("chol chain add");
-    return OPF_OK;
-  };
-  auto clear = [&](double* Ub, int64_t n) -> int {
-    hipLaunchKernelGGL(k_fill, dim3(grid_for(n, 256)), dim3(256), 0, F->cs, Ub, n);
-    LAUNCH_OK("chol chain clear");
     return OPF_OK;
   };
   // nt = 2: fronts kl and kr in one batch (period stride kr - kl)
   auto chain_front = [&](int t, int nt, int t2, int u, double* Ub) -> int {
     Batch B;
     B.F = {nullptr, C.crec[u ? 1 : 0], C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, Ub,
-           (int64_t)(t2 - t) * C.csize, (int64_t)(t2 - t) * C.dcsize, gg, C.dev.stop};
+           (int64_t)(t2 - t) * C.csize, (int64_t)(t2 - t) * C.dcsize, gg, C.dev.stop, 1};
     B.rec = C.crec + (u ? 1 : 0);
     B.n = 1;
     B.nt = nt;
@@ -1793,20 +1817,21 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
     for (;;) {
       const bool l = kl < m && ready[kl], r = kr > m && ready[kr];
       if (l && r) {
-        if (kl >= 1) CHK(add_in(kl, UsL));
-        if (kr <= T - 2) CHK(add_in(kr, UsR));
-        CHK(clear(F->Us, 2 * gg));
+        if (kl >= 1 && kr <= T - 2) {
+          CHK(add_in(kl, UsL, 2, kr));
+        } else {
+          if (kl >= 1) CHK(add_in(kl, UsL));
+          if (kr <= T - 2) CHK(add_in(kr, UsR));
+        }
         CHK(chain_front(kl, 2, kr, G, UsL));
         ++kl;
         --kr;
       } else if (l && (kr <= m || all)) {
         if (kl >= 1) CHK(add_in(kl, UsL));
-        CHK(clear(UsL, gg));
         CHK(chain_front(kl, 1, kl, G, UsL));
         ++kl;
       } else if (r && (kl >= m || all)) {
         if (kr <= T - 2) CHK(add_in(kr, UsR));
-        CHK(clear(UsR, gg));
         CHK(chain_front(kr, 1, kr, G, UsR));
         --kr;
       } else {
@@ -1840,7 +1865,7 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
       if (q1 > q0) {
         Batch B;
         B.F = {C.d_rec + q0, FrontRec(), C.Lf + (int64_t)t0 * P.lsize, C.Df + (int64_t)t0 * C.dsize, C.Ar, P.lsize, C.dsize, P.usize,
-               C.dev.stop};
+               C.dev.stop, 0};
         B.rec = C.rec.data() + q0;
         B.n = (int)(q1 - q0);
         B.nt = nt;
@@ -1873,7 +1898,8 @@ int factor_inst(opf_chol* F, CholInst& C, const double* kv, double tol, double r
 // falling order of p), see k_fwd_panel / k_bwd_panel: y is the
 // right-hand side in, z the forward solution; the backward pass reads z and
 // leaves x in y.
-int fwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, int chunk, double* next, int64_t sn, hipStream_t st) {
+int fwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, int chunk, double* next, int64_t sn, int pass,
+            hipStream_t st) {
   for (int k0 = 0; n > 0; k0 += kSolve) {
     int below = 1;
     for (int i = 0; i < n; ++i) below = std::max(below, rec[i].p + rec[i].u - std::min(k0 + kSolve, rec[i].p));
@@ -1882,10 +1908,10 @@ int fwd_tri(const Tri& A, const FrontRec* rec, int n, int nb, int chunk, double*
     // the launch's triangles
     if ((int64_t)(below + 63) / 64 * nb * n <= 512)
       hipLaunchKernelGGL(k_fwd_panel<64>, dim3((below + 63) / 64, nb, n), dim3(kInner + 64 + 128), 0, st, A, k0, chunk,
-                         next, sn);
+                         next, sn, pass);
     else
       hipLaunchKernelGGL(k_fwd_panel<192>, dim3((below + 191) / 192, nb, n), dim3(kInner + 192 + 128), 0, st, A, k0,
-                         chunk, next, sn);
+                         chunk, next, sn, pass);
     while (n > 0 && rec[n - 1].p <= k0 + kSolve) --n;
   }
   LAUNCH_OK("chol forward panel");
@@ -1922,7 +1948,7 @@ int solve_cyclic(CholInst& C, hipStream_t st) {
     const int n = T / h, c = (n + 1) / 2, u = c > 1 ? 2 : (n > 1 ? 1 : 0);
     top = h;
     const Tri A = level(h, u);
-    CHK(fwd_tri(A, C.crec + u, 1, c, kAll, nullptr, 0, st));
+    CHK(fwd_tri(A, C.crec + u, 1, c, kAll, nullptr, 0, 0, st));
     if (n == c) break;
     hipLaunchKernelGGL(k_cyc_pull, dim3((G + 255) / 256, n - c), dim3(256), 0, st, (const double*)A.w, A.sw, c, G,
                        C.Y + (2 * (int64_t)h - 1) * np + o, A.sy);
@@ -1963,7 +1989,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     const int nl = (int)(P.lvl_large_ptr[h + 1] - q0);
     if (nl > 0) {
       hipLaunchKernelGGL(k_fwd_pull, dim3(T, 1, nl), dim3(256), 0, st, C.dev, C.d_rec + q0, C.Y, C.W);
-      CHK(fwd_tri(tree(q0), C.rec.data() + q0, nl, T, 0, nullptr, 0, st));
+      CHK(fwd_tri(tree(q0), C.rec.data() + q0, nl, T, 0, nullptr, 0, 0, st));
     }
   }
   hipLaunchKernelGGL(k_fwd_root_pull, dim3(T), dim3(256), 0, st, C.dev, C.d_roots, (int32_t)P.roots.size(), C.Y,
@@ -1980,14 +2006,6 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     return Tri{nullptr, C.crec[t == m ? 0 : 1], C.Cf + (int64_t)t * C.csize, C.Dc + (int64_t)t * C.dcsize, C.Y + off(t),
                C.Z + off(t), C.Wc + (int64_t)t * G, C.Gp, d * C.csize, d * C.dcsize, d * np, d * G, G};
   };
-  // front m collects its two neighbours' updates (Wc), left then right; the
-  // others take theirs from the last panel of the neighbour before them
-  auto pull_to = [&](int t, int s) -> int {
-    hipLaunchKernelGGL(k_sub, dim3((G + 255) / 256), dim3(256), 0, st, C.Y + off(t),
-                       (const double*)(C.Wc + (int64_t)s * G), G);
-    LAUNCH_OK("chol forward chain");
-    return OPF_OK;
-  };
   if (C.cyclic) {
     CHK(solve_cyclic(C, st));
   } else {
@@ -1995,21 +2013,24 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     while (kl < m || kr > m) {
       const bool l = kl < m, r = kr > m;
       const int t = l ? kl : kr, nb = l && r ? 2 : 1;
-      // the two sides reach front m in different steps unless both end there
+      // each side's last panel passes its update on, except to front m, which
+      // collects its two neighbours' (Wc), left then right
       const int nl = kl + 1, nr = kr - 1;
-      double* next = (l && nl == m) || (r && nr == m) ? nullptr : C.Y + off(l ? nl : nr);
-      CHK(fwd_tri(chain(t, nb, kr), C.crec + 1, 1, nb, kChainCols, next, nb > 1 ? (int64_t)(nr - nl) * np : 0, st));
-      if (!next) {
-        // one side may still have a neighbour other than m to pass on to
-        if (l && nl != m) CHK(pull_to(nl, kl));
-        if (r && nr != m) CHK(pull_to(nr, kr));
-      }
+      int pass = 0;
+      if (l && nl != m) pass |= 1;
+      if (r && nr != m) pass |= nb > 1 ? 2 : 1;
+      CHK(fwd_tri(chain(t, nb, kr), C.crec + 1, 1, nb, kChainCols, C.Y + off(l ? nl : nr),
+                  nb > 1 ? (int64_t)(nr - nl) * np : 0, pass, st));
       if (l) ++kl;
       if (r) --kr;
     }
-    if (m >= 1) CHK(pull_to(m, m - 1));
-    if (m + 1 <= T - 1) CHK(pull_to(m, m + 1));
-    CHK(fwd_tri(chain(m, 1, m), C.crec, 1, 1, kChainCols, nullptr, 0, st));
+    if (T > 1) {
+      hipLaunchKernelGGL(k_sub, dim3((G + 255) / 256), dim3(256), 0, st, C.Y + off(m),
+                         (const double*)(m >= 1 ? C.Wc + (int64_t)(m - 1) * G : nullptr),
+                         (const double*)(m + 1 < T ? C.Wc + (int64_t)(m + 1) * G : nullptr), G);
+      LAUNCH_OK("chol forward chain");
+    }
+    CHK(fwd_tri(chain(m, 1, m), C.crec, 1, 1, kChainCols, nullptr, 0, 0, st));
   }
   // backward along the pg chain: front m, then outwards (each front reads
   // its chain neighbour's solution, held in Y)
@@ -2196,10 +2217,9 @@ int opf_chol_factor(opf_chol* F, const double* kvals, double pivot_tol, double p
   if (std::isnan(pivot_tol)) return api_fail(OPF_EINVAL, "pivot_tol is NaN");
   if (hipSetDevice(F->device) != hipSuccess) return api_fail(OPF_EHIP, "hipSetDevice failed");
   hipStream_t st = model_stream(F->model);
-  if (hipMemsetAsync(npert, 0, sizeof(int32_t), st) != hipSuccess) return api_fail(OPF_EHIP, "clearing npert");
   for (auto& C : F->inst) {
     C.dev.stop = F->stop_on_pivot ? npert : nullptr;
-    CHK(factor_inst(F, C, kvals, pivot_tol, pivot_repl, npert, st));
+    CHK(factor_inst(F, C, &C == F->inst.data(), kvals, pivot_tol, pivot_repl, npert, st));
   }
   return OPF_OK;
 }
