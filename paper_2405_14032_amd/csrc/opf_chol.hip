@@ -37,12 +37,14 @@
 namespace opf {
 namespace {
 
-constexpr int kSmall = 64;   // largest front factored in LDS by one wavefront
+constexpr int kSmall = 64;   // largest front of one wavefront, a row per lane
 constexpr int kNB = 64;      // panel width of the blocked fronts
 constexpr int kTile = 64;    // trailing-update tile
 constexpr int kChainCols = 128;  // columns summed together in the chain's L21 z (a multiple of kNB)
 constexpr int kStep = 1024;      // columns per trailing update of a blocked front
 constexpr int kWide = 256;       // columns whose panels update each other within their launches
+constexpr int kTreeT = 512;      // threads of k_fwd_tree, k_bwd_tree: eight fronts at a time
+constexpr int kTreeFronts = 16;  // levels of at most this many fronts share their launch (two per wavefront)
 constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 ones (one block per CU)
 // The pg chain by cyclic reduction (see k_cyc_add) from kCycT periods, up to
 // fronts of kCycG: factor + solve, from both ends against by reduction, 54
@@ -69,7 +71,7 @@ struct CDev {
   const int32_t* col;
   const longlong2* con;
   // per child, in kid_ptr's order: where its update matrix and its inverse map
-  // start, its rows
+  // start, its rows, where its update vector starts
   const longlong4* kid;
   int64_t col_root;
   int64_t lsize, usize, wsize;
@@ -81,10 +83,10 @@ struct CDev {
 // its parts start in a period's storage: factor block ((p+u) x p, leading
 // dimension ld), diagonal
 // blocks (see diag_size), update block (u x u), update vector of the solves,
-// row list; its first elimination position and its node.
+// row list; its first elimination position and its children (CDev::kid).
 struct FrontRec {
   int64_t L, D, U, W, R;
-  int32_t p, u, ld, f, s;
+  int32_t p, u, ld, f, k0, k1;
 };
 
 // Front z of a batch: rec's, or the one given by value where rec is NULL (no
@@ -321,17 +323,17 @@ __device__ __forceinline__ bool is_odd(double d, double tol) {
 // always the column to eliminate, so that the steps are a loop of one body:
 // unrolled over the columns they spilled some 400 scalar registers.
 template <int FM>
-__device__ __forceinline__ void small_front(const CDev& D, int s, int p, int u, double* __restrict__ L,
+__device__ __forceinline__ void small_front(const CDev& D, const FrontRec& F, double* __restrict__ L,
                                             double* __restrict__ Ut, const PivotRule& R, int& low) {
-  const int f = p + u, i = (int)threadIdx.x;
+  const int p = F.p, u = F.u, f = p + u, i = (int)threadIdx.x & 63;
   double a[FM];
 #pragma unroll
   for (int j = 0; j < FM; ++j) a[j] = j < p && i >= j && i < f ? L[j * f + i] : 0.0;
   // the next child's map is on its way while one is added
-  const int64_t q0 = D.kid_ptr[s], q1 = D.kid_ptr[s + 1];
+  const int q0 = F.k0, q1 = F.k1;
   const int at = min(i, f - 1);
   int icn = q0 < q1 ? D.inv[D.kid[q0].y + at] : -1;
-  for (int64_t q = q0; q < q1; ++q) {
+  for (int q = q0; q < q1; ++q) {
     const longlong4 kd = D.kid[q];
     const int uc = (int)kd.z, ic = i < f ? icn : -1;
     const double* Uc = Ut + kd.x;
@@ -361,37 +363,41 @@ __device__ __forceinline__ void small_front(const CDev& D, int s, int p, int u, 
     for (int j = 1; j < FM; ++j) a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
     a[FM - 1] = 0.0;
   }
-  double* U = Ut + D.node_uoff[s];
+  double* U = Ut + F.U;
 #pragma unroll
   for (int j = 0; j < FM; ++j)
     if (j < u && i >= p + j && i < f) U[j * u + (i - p)] = a[j];
+}
+
+template <bool BIG>
+__device__ __forceinline__ void small_any(const CDev& D, const FrontRec& F, double* __restrict__ L,
+                                          double* __restrict__ Ut, const PivotRule& R, int& low) {
+  const int f = F.p + F.u;
+  if (BIG) {
+    if (f <= 48) small_front<48>(D, F, L, Ut, R, low);
+    else small_front<64>(D, F, L, Ut, R, low);
+  } else {
+    if (f <= 16) small_front<16>(D, F, L, Ut, R, low);
+    else if (f <= 24) small_front<24>(D, F, L, Ut, R, low);
+    else small_front<32>(D, F, L, Ut, R, low);
+  }
 }
 
 // The small fronts of one level, one wavefront per (front, period); those of
 // more than 32 rows in launches of their own (BIG), which need twice the
 // registers.
 template <bool BIG>
-__global__ void __launch_bounds__(64) k_factor_small(CDev D, const int32_t* __restrict__ list, int64_t l0, int32_t t0,
+__global__ void __launch_bounds__(64) k_factor_small(CDev D, const FrontRec* __restrict__ rec, int32_t t0,
                                                      double* __restrict__ Lf, double* __restrict__ Ar, double tol,
                                                      double repl, int32_t* __restrict__ npert) {
   if (stopped(D.stop)) return;
-  const int tt = (int)blockIdx.y, s = list[l0 + blockIdx.x];
-  const int p = D.node_p[s], u = D.node_u[s];
-  double* L = Lf + (int64_t)(t0 + tt) * D.lsize + D.node_loff[s];
-  double* Ut = Ar + (int64_t)tt * D.usize;
+  const int tt = (int)blockIdx.y;
+  const FrontRec F = rec[blockIdx.x];
   PivotRule R;
   R.tol = tol;
   sqrt_recip(repl, R.s_repl, R.r_repl);
   int low = 0;
-  const int f = p + u;
-  if (BIG) {
-    if (f <= 48) small_front<48>(D, s, p, u, L, Ut, R, low);
-    else small_front<64>(D, s, p, u, L, Ut, R, low);
-  } else {
-    if (f <= 16) small_front<16>(D, s, p, u, L, Ut, R, low);
-    else if (f <= 24) small_front<24>(D, s, p, u, L, Ut, R, low);
-    else small_front<32>(D, s, p, u, L, Ut, R, low);
-  }
+  small_any<BIG>(D, F, Lf + (int64_t)(t0 + tt) * D.lsize + F.L, Ar + (int64_t)tt * D.usize, R, low);
   if (low && threadIdx.x == 0) atomicAdd(npert, low);
 }
 
@@ -886,47 +892,72 @@ __global__ void k_scatter_out(const double* __restrict__ Y, int32_t n_p, int32_t
   }
 }
 
-// Forward, small fronts: v = b(pivots) - children's pivot-row updates,
-// children's other rows summed into this front's update vector, then
-// L11 z = v and w += L21 z.  W holds, per front, what its subtree
-// subtracts from the right-hand side at the front's update rows.
-__global__ void __launch_bounds__(64) k_fwd_small(CDev D, const int32_t* __restrict__ list, int64_t l0,
+// Forward, a small front by one wavefront, lane i its row i: v = b(pivots) -
+// the children's pivot-row updates, their other rows summed into this front's
+// update vector (gathered through the inverse maps, child after child), then
+// L11 z = v and w += L21 z, 8 columns of L in flight.  W holds, per front, what
+// its subtree subtracts from the right-hand side at the front's update rows.
+__device__ __forceinline__ void fwd_small(const CDev& D, const FrontRec& F, const double* __restrict__ Lt,
+                                          double* __restrict__ Yt, double* __restrict__ Wt, int i) {
+  const int p = F.p, f = p + F.u, fs = F.f, at = min(i, f - 1);
+  const double* L = Lt + F.L;
+  const double d = L[(i < p ? i : 0) * f + (i < p ? i : 0)];
+  double v = i < p ? Yt[fs + i] : 0.0;
+  const int q0 = F.k0, q1 = F.k1;
+  int icn = q0 < q1 ? D.inv[D.kid[q0].y + at] : -1;
+  for (int q = q0; q < q1; ++q) {
+    const int ic = i < f ? icn : -1;
+    const double w = Wt[D.kid[q].w + max(ic, 0)];
+    if (q + 1 < q1) icn = D.inv[D.kid[q + 1].y + at];
+    v = ic >= 0 ? (i < p ? v - w : v + w) : v;
+  }
+  for (int k0 = 0; k0 < p; k0 += 8) {
+    double t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = L[min(k0 + j, p - 1) * f + at];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = k0 + j;
+      if (k >= p) break;
+      const double x = lane_bcast(v / d, k);
+      const double z = x * t[j];
+      v = i == k ? x : (i > k ? (i < p ? v - z : v + z) : v);
+    }
+  }
+  if (i < p) Yt[fs + i] = v;
+  else if (i < f) Wt[F.W + i - p] = v;
+}
+
+// The small fronts of one level, a wavefront each (k_fwd_small); and
+// consecutive levels of at most kTreeFronts fronts, all small, in one launch,
+// a block per period, the levels separated by barriers (k_fwd_tree; ptr: the
+// levels' starts in rec).  Four such levels of a 57-bus network are 13.7 us
+// against 4 x 7 (backward 12.3 against 4 x 6): what a launch waits for is the
+// latency of its one chain, and a barrier costs less than a launch.  With more
+// fronts than two per wavefront a level's launch has the chip to spread over.
+// The factorization's levels stay apart: held together they took 78 us against
+// 4 x 15, every front size's code in one kernel spilling its scalars.
+__global__ void __launch_bounds__(64) k_fwd_small(CDev D, const FrontRec* __restrict__ rec,
                                                   const double* __restrict__ Lf, double* __restrict__ Y,
                                                   double* __restrict__ W) {
-  __shared__ double v[kSmall];
   const int t = (int)blockIdx.y;
-  const int s = list[l0 + blockIdx.x];
-  const int p = D.node_p[s], u = D.node_u[s], f = p + u, fs = D.node_f[s];
-  const int i = (int)threadIdx.x;
-  const double* L = Lf + (int64_t)t * D.lsize + D.node_loff[s];
-  double* Yt = Y + (int64_t)t * D.n_p;
-  double* Wt = W + (int64_t)t * D.wsize;
-  if (i < f) v[i] = i < p ? Yt[fs + i] : 0.0;
-  __syncthreads();
-  for (int64_t q = D.kid_ptr[s]; q < D.kid_ptr[s + 1]; ++q) {
-    const int c = D.kids[q];
-    const int uc = D.node_u[c];
-    const int32_t* rel = D.rel + D.row_ptr[c];
-    const double* Wc = Wt + D.node_woff[c];
-    for (int a = i; a < uc; a += (int)blockDim.x) {
-      const int r = rel[a];
-      if (r < p) v[r] -= Wc[a];
-      else v[r] += Wc[a];
+  const FrontRec F = rec[blockIdx.x];
+  fwd_small(D, F, Lf + (int64_t)t * D.lsize, Y + (int64_t)t * D.n_p, W + (int64_t)t * D.wsize,
+            (int)threadIdx.x);
+}
+__global__ void __launch_bounds__(kTreeT) k_fwd_tree(CDev D, const FrontRec* __restrict__ rec,
+                                                     const int64_t* __restrict__ ptr, int32_t h0, int32_t h1,
+                                                     const double* __restrict__ Lf, double* __restrict__ Y,
+                                                     double* __restrict__ W) {
+  const int t = (int)blockIdx.x, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  for (int h = h0; h < h1; ++h) {
+    for (int q = (int)ptr[h] + wv; q < (int)ptr[h + 1]; q += kTreeT / 64) {
+      const FrontRec F = rec[q];
+      fwd_small(D, F, Lf + (int64_t)t * D.lsize, Y + (int64_t)t * D.n_p, W + (int64_t)t * D.wsize,
+                (int)threadIdx.x & 63);
     }
     __syncthreads();
   }
-  for (int k = 0; k < p; ++k) {
-    if (i == k) v[k] /= L[(int64_t)k * f + k];
-    __syncthreads();
-    if (i > k && i < f) {
-      const double z = v[k] * L[(int64_t)k * f + i];
-      if (i < p) v[i] -= z;
-      else v[i] += z;
-    }
-    __syncthreads();
-  }
-  if (i < p) Yt[fs + i] = v[i];
-  else if (i < f) Wt[D.node_woff[s] + i - p] = v[i];
 }
 
 // Forward, large fronts of one level, step 1: pull the children's update
@@ -941,7 +972,7 @@ __global__ void __launch_bounds__(256) k_fwd_pull(CDev D, const FrontRec* __rest
   double* Ws = Wt + f.W;
   for (int a = (int)threadIdx.x; a < f.u; a += (int)blockDim.x) Ws[a] = 0.0;
   __syncthreads();
-  for (int64_t q = D.kid_ptr[f.s]; q < D.kid_ptr[f.s + 1]; ++q) {
+  for (int q = f.k0; q < f.k1; ++q) {
     const int c = D.kids[q];
     const int uc = D.node_u[c];
     const int32_t* rel = D.rel + D.row_ptr[c];
@@ -1325,33 +1356,59 @@ __global__ void __launch_bounds__(kBwdT) k_bwd_panel(Tri A, int32_t q, int32_t c
   }
 }
 
-// Backward, small fronts: gather x at the update rows, v = y - L21^T x_u,
-// then L11^T x = v.
-__global__ void __launch_bounds__(64) k_bwd_small(CDev D, const int32_t* __restrict__ list, int64_t l0,
+// Backward, a small front by one wavefront, lane i its pivot column i: gather x
+// at the update rows, v = y - L21^T x_u, then L11^T x = v, 8 rows of L in
+// flight.
+__device__ __forceinline__ void bwd_small(const CDev& D, const FrontRec& F, const double* __restrict__ Lt,
+                                          double* __restrict__ Yt, int i) {
+  const int p = F.p, u = F.u, f = p + u, fs = F.f;
+  const int at = min(i, p - 1);
+  const double* col = Lt + F.L + at * f;
+  const double d = col[at];
+  const double xu = i < u ? Yt[D.rows[F.R + i]] : 0.0;
+  double v = i < p ? Yt[fs + i] : 0.0;
+  for (int a0 = 0; a0 < u; a0 += 8) {
+    double t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = col[min(p + a0 + j, f - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (a0 + j >= u) break;
+      v -= t[j] * lane_bcast(xu, a0 + j);
+    }
+  }
+  for (int k0 = p - 1; k0 >= 0; k0 -= 8) {
+    double t[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t[j] = col[max(k0 - j, 0)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = k0 - j;
+      if (k < 0) break;
+      const double x = lane_bcast(v / d, k);
+      const double w = v - t[j] * x;
+      v = i == k ? x : (i < k ? w : v);
+    }
+  }
+  if (i < p) Yt[fs + i] = v;
+}
+__global__ void __launch_bounds__(64) k_bwd_small(CDev D, const FrontRec* __restrict__ rec,
                                                   const double* __restrict__ Lf, double* __restrict__ Y) {
-  __shared__ double v[kSmall], xu[kSmall];
   const int t = (int)blockIdx.y;
-  const int s = list[l0 + blockIdx.x];
-  const int p = D.node_p[s], u = D.node_u[s], f = p + u, fs = D.node_f[s];
-  const int i = (int)threadIdx.x;
-  const double* L = Lf + (int64_t)t * D.lsize + D.node_loff[s];
-  double* Yt = Y + (int64_t)t * D.n_p;
-  const int32_t* rows = D.rows + D.row_ptr[s];
-  if (i < u) xu[i] = Yt[rows[i]];
-  __syncthreads();
-  if (i < p) {
-    double acc = Yt[fs + i];
-    for (int a = 0; a < u; ++a) acc -= L[(int64_t)i * f + p + a] * xu[a];
-    v[i] = acc;
-  }
-  __syncthreads();
-  for (int k = p - 1; k >= 0; --k) {
-    if (i == k) v[k] /= L[(int64_t)k * f + k];
-    __syncthreads();
-    if (i < k) v[i] -= L[(int64_t)i * f + k] * v[k];
+  const FrontRec F = rec[blockIdx.x];
+  bwd_small(D, F, Lf + (int64_t)t * D.lsize, Y + (int64_t)t * D.n_p, (int)threadIdx.x);
+}
+__global__ void __launch_bounds__(kTreeT) k_bwd_tree(CDev D, const FrontRec* __restrict__ rec,
+                                                     const int64_t* __restrict__ ptr, int32_t h0, int32_t h1,
+                                                     const double* __restrict__ Lf, double* __restrict__ Y) {
+  const int t = (int)blockIdx.x, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  for (int h = h1 - 1; h >= h0; --h) {
+    for (int q = (int)ptr[h] + wv; q < (int)ptr[h + 1]; q += kTreeT / 64) {
+      const FrontRec F = rec[q];
+      bwd_small(D, F, Lf + (int64_t)t * D.lsize, Y + (int64_t)t * D.n_p, (int)threadIdx.x & 63);
+    }
     __syncthreads();
   }
-  if (i < p) Yt[fs + i] = v[i];
 }
 
 int grid_for(int64_t n, int block) {
@@ -1372,9 +1429,10 @@ struct CholInst {
   const InstHost* I = nullptr;
   CDev dev{};
   int32_t *d_node_f = nullptr, *d_node_p = nullptr, *d_node_u = nullptr, *d_rel = nullptr, *d_kids = nullptr,
-          *d_rows = nullptr, *d_perm = nullptr, *d_items = nullptr, *d_small = nullptr, *d_roots = nullptr,
+          *d_rows = nullptr, *d_perm = nullptr, *d_items = nullptr, *d_roots = nullptr,
           *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr, *d_inv = nullptr, *d_col = nullptr;
-  int64_t* d_coloff = nullptr;
+  int64_t *d_coloff = nullptr, *d_smallptr = nullptr;
+  std::vector<int32_t> run_end;  // per level: the end of the run of small levels it starts or continues, else itself
   longlong2* d_con = nullptr;
   longlong4* d_kid = nullptr;
   std::vector<int64_t> lvl_item, lvl_big;  // per level: extend-add items; the first small front of more than 32 rows
@@ -1387,7 +1445,7 @@ struct CholInst {
   bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends
   int32_t cld = 0;            // their leading dimension: 2 G or 3 G
   double* Uc = nullptr;       // cyclic reduction: a level's update blocks
-  FrontRec* d_rec = nullptr;
+  FrontRec *d_rec = nullptr, *d_srec = nullptr;  // large fronts; small ones, by level
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
 };
@@ -1488,7 +1546,7 @@ void release(opf_chol* F) {
   } while (0)
 
 // The extend-add's tables (see CDev and k_extend) and the small fronts' lists.
-int setup_extend(opf_chol* F, CholInst& C) {
+int setup_extend(opf_chol* F, CholInst& C, const std::vector<int64_t>& woff) {
   const CholPlan& P = C.plan;
   auto order = [&](int32_t s) { return P.node_p[s] + P.node_u[s]; };
   std::vector<int32_t> inv, col, items, small;
@@ -1525,7 +1583,7 @@ int setup_extend(opf_chol* F, CholInst& C) {
   }
   for (int32_t c : P.roots) invert(c, P.G);
   std::vector<longlong4> kid;
-  for (int32_t c : P.kids) kid.push_back(make_longlong4(P.node_uoff[c], inv_off[c], P.node_u[c], 0));
+  for (int32_t c : P.kids) kid.push_back(make_longlong4(P.node_uoff[c], inv_off[c], P.node_u[c], woff[c]));
   C.dev.col_root = columns(P.G, P.roots.data(), P.roots.data() + P.roots.size());
   for (int32_t h = 0; h < P.nlevels; ++h) {
     for (int64_t q = P.lvl_large_ptr[h]; q < P.lvl_large_ptr[h + 1]; ++q) {
@@ -1542,8 +1600,20 @@ int setup_extend(opf_chol* F, CholInst& C) {
         if ((order(P.lvl_small[q]) > 32) == (big == 1)) small.push_back(P.lvl_small[q]);
     }
   }
+  // levels with at most kTreeFronts fronts, all small, in runs of two or more
+  C.run_end.resize(P.nlevels);
+  for (int32_t h = P.nlevels - 1; h >= 0; --h) {
+    const bool fit = P.lvl_large_ptr[h] == P.lvl_large_ptr[h + 1] &&
+                     P.lvl_small_ptr[h + 1] - P.lvl_small_ptr[h] <= kTreeFronts;
+    C.run_end[h] = !fit ? h : (h + 1 < P.nlevels && C.run_end[h + 1] > h + 1 ? C.run_end[h + 1] : h + 1);
+  }
+  CHK(upload(F, P.lvl_small_ptr, &C.d_smallptr));
   CHK(upload(F, items, &C.d_items));
-  CHK(upload(F, small, &C.d_small));
+  std::vector<FrontRec> srec;
+  for (int32_t s : small)
+    srec.push_back({P.node_loff[s], 0, P.node_uoff[s], woff[s], P.row_ptr[s], P.node_p[s], P.node_u[s], order(s),
+                    P.node_f[s], (int32_t)P.kid_ptr[s], (int32_t)P.kid_ptr[s + 1]});
+  CHK(upload(F, srec, &C.d_srec));
   CHK(upload(F, inv, &C.d_inv));
   CHK(upload(F, col, &C.d_col));
   CHK(upload(F, col_off, &C.d_coloff));
@@ -1572,14 +1642,14 @@ int setup_device(opf_chol* F, CholInst& C) {
     std::stable_sort(v.begin(), v.end(), [&](int32_t x, int32_t y) { return P.node_p[x] > P.node_p[y]; });
     for (int32_t s : v) {
       C.rec.push_back({P.node_loff[s], C.dsize, P.node_uoff[s], woff[s], P.row_ptr[s], P.node_p[s], P.node_u[s],
-                       P.node_p[s] + P.node_u[s], P.node_f[s], s});
+                       P.node_p[s] + P.node_u[s], P.node_f[s], (int32_t)P.kid_ptr[s], (int32_t)P.kid_ptr[s + 1]});
       C.dsize += diag_size(P.node_p[s]);
     }
   }
   C.dcsize = diag_size(P.G);
   C.cyclic = P.T >= kCycT && P.G <= kCycG;
   C.cld = (C.cyclic ? 3 : 2) * P.G;
-  for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0};
+  for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
   CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
@@ -1588,7 +1658,7 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(upload(F, P.kids, &C.d_kids));
   CHK(upload(F, P.rows, &C.d_rows));
   CHK(upload(F, P.perm, &C.d_perm));
-  CHK(setup_extend(F, C));
+  CHK(setup_extend(F, C, woff));
   CHK(upload(F, P.roots, &C.d_roots));
   CHK(upload(F, P.kpos0, &C.d_kpos0));
   CHK(upload(F, P.kpos1, &C.d_kpos1));
@@ -1855,10 +1925,10 @@ int factor_inst(opf_chol* F, CholInst& C, bool first, const double* kv, double t
       }
       const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1], sb = C.lvl_big[h];
       if (sb > s0)
-        hipLaunchKernelGGL(k_factor_small<false>, dim3((unsigned)(sb - s0), nt), dim3(64), 0, st, C.dev, C.d_small, s0,
+        hipLaunchKernelGGL(k_factor_small<false>, dim3((unsigned)(sb - s0), nt), dim3(64), 0, st, C.dev, C.d_srec + s0,
                            t0, C.Lf, C.Ar, tol, repl, npert);
       if (s1 > sb)
-        hipLaunchKernelGGL(k_factor_small<true>, dim3((unsigned)(s1 - sb), nt), dim3(64), 0, st, C.dev, C.d_small, sb,
+        hipLaunchKernelGGL(k_factor_small<true>, dim3((unsigned)(s1 - sb), nt), dim3(64), 0, st, C.dev, C.d_srec + sb,
                            t0, C.Lf, C.Ar, tol, repl, npert);
       LAUNCH_OK("chol small fronts");
       const int64_t q0 = P.lvl_large_ptr[h], q1 = P.lvl_large_ptr[h + 1];
@@ -1979,9 +2049,16 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   // forward through the interior trees, all periods at once (small fronts
   // leave their forward solution in Y, large ones in Z)
   for (int h = 0; h < P.nlevels; ++h) {
+    if (C.run_end[h] > h + 1) {
+      hipLaunchKernelGGL(k_fwd_tree, dim3(T), dim3(kTreeT), 0, st, C.dev, C.d_srec, C.d_smallptr, h, C.run_end[h], C.Lf,
+                         C.Y, C.W);
+      LAUNCH_OK("chol forward small levels");
+      h = C.run_end[h] - 1;
+      continue;
+    }
     const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1];
     if (s1 > s0) {
-      hipLaunchKernelGGL(k_fwd_small, dim3((unsigned)(s1 - s0), T), dim3(64), 0, st, C.dev, C.d_small, s0, C.Lf,
+      hipLaunchKernelGGL(k_fwd_small, dim3((unsigned)(s1 - s0), T), dim3(64), 0, st, C.dev, C.d_srec + s0, C.Lf,
                          C.Y, C.W);
       LAUNCH_OK("chol forward small");
     }
@@ -2051,6 +2128,15 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   }
   // backward through the interior trees, top down
   for (int h = P.nlevels - 1; h >= 0; --h) {
+    // a run of small levels, from its first one on
+    int h0 = h;
+    while (h0 > 0 && C.run_end[h] == h + 1 && C.run_end[h0 - 1] == h + 1) --h0;
+    if (h0 < h) {
+      hipLaunchKernelGGL(k_bwd_tree, dim3(T), dim3(kTreeT), 0, st, C.dev, C.d_srec, C.d_smallptr, h0, h + 1, C.Lf, C.Y);
+      LAUNCH_OK("chol backward small levels");
+      h = h0;
+      continue;
+    }
     const int64_t q0 = P.lvl_large_ptr[h];
     const int nl = (int)(P.lvl_large_ptr[h + 1] - q0);
     if (nl > 0) {
@@ -2062,7 +2148,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
     }
     const int64_t s0 = P.lvl_small_ptr[h], s1 = P.lvl_small_ptr[h + 1];
     if (s1 > s0) {
-      hipLaunchKernelGGL(k_bwd_small, dim3((unsigned)(s1 - s0), T), dim3(64), 0, st, C.dev, C.d_small, s0, C.Lf,
+      hipLaunchKernelGGL(k_bwd_small, dim3((unsigned)(s1 - s0), T), dim3(64), 0, st, C.dev, C.d_srec + s0, C.Lf,
                          C.Y);
       LAUNCH_OK("chol backward small");
     }
