@@ -577,24 +577,29 @@ int build_fused(opf_model* M) {
 
 // The default shape of an op, or narrower tiles when a tile's K rows do
 // not fit the LDS budget (buses of high degree).  256 elements and one period
-// per tile, except in the whole sweep:
-//   * the bus pass has blocks of one wavefront (nothing its wavefronts share is
-//     worth waiting for each other: 0-8 % at every size measured);
-//   * the line pass, where the model has few wavefronts of lines and generators
-//     for the chip's 1024 SIMDs, too: with at most one per SIMD one period each
-//     (1000 buses x 8 periods 27.6 -> 23.8 us a sweep, 300 x 24 26.8 -> 24.3),
-//     up to three per SIMD two periods, the second one's loads behind the first
-//     (2000 x 24 44.1 -> 40.2, 2000 x 48 70 -> 64); beyond, blocks of 256 share
-//     their K rows' writes better (6000 x 24 82.6 us against 86.6, 2000 x 168
-//     159 against 182).
+// per tile, except in the whole sweep of a model that has few wavefronts for
+// the chip's 1024 SIMDs: blocks of one wavefront there, which spread over more
+// CUs and wait for nobody, unless a period is one block of 256 anyhow.
+//   * line pass (wavefronts of lines and generators), one period each up to one
+//     per SIMD: 1000 buses x 8 periods 27.6 -> 23.8 us a sweep, 300 x 24 26.8 ->
+//     24.3, 150 (210 lines) x 24 25.2 -> 23.1; 140 lines the same, 85 and fewer
+//     21.6 -> 21.7.  Up to 1.5 per SIMD two periods, the second one's loads
+//     behind the first: 2000 x 24 44.1 -> 40.2.  Beyond, blocks of 256 share
+//     their K rows' writes better: 1500 x 50 52.7 us against 56.1, 6000 x 24
+//     82.6 against 86.6, 2000 x 168 159 against 182.
+//   * bus pass: 300 buses x 6 26.1 -> 25.3 us, 2000 x 40 57.7 -> 56.3, but 100 x
+//     168 25.5 -> 26.5 and 1500 x 70 67.3 -> 68.6.
 int set_default_shape(opf_model* M, int op) {
   Shape s;
-  if (op == OP_SWB) s.block = 64;
-  if (op == OP_SWA) {
-    int64_t waves = 0;
-    for (const auto& I : M->inst) waves += (int64_t)I.T * ((I.B + 63) / 64 + (I.G + 63) / 64);
-    if (waves <= 3 * 1024) s.block = 64;
-    if (waves > 1024 && waves <= 3 * 1024) s.ppt = 2;
+  int64_t waves = 0;
+  int32_t most = 0;
+  for (const auto& I : M->inst) {
+    waves += op == OP_SWB ? (int64_t)I.T * ((I.N + 63) / 64) : (int64_t)I.T * ((I.B + 63) / 64 + (I.G + 63) / 64);
+    most = std::max(most, op == OP_SWB ? I.N : I.B);
+  }
+  if (waves <= 1536 && ((op == OP_SWA && most > 128) || (op == OP_SWB && most > 256))) {
+    s.block = 64;
+    if (op == OP_SWA && waves > 1024) s.ppt = 2;
   }
   int rc = set_shape(M, op, s);
   for (int blk = s.block / 2; rc == OPF_EINVAL && blk >= 64; blk /= 2) {
