@@ -55,6 +55,14 @@ constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 
 // iterate shows a changed elimination order at 1e-8, and small grids keep
 // theirs bit for bit.
 constexpr int kCycT = 64, kCycG = 1536;
+// The pg chain by two wavefronts (see k_chain_wave, k_chain_wave_solve) over
+// horizons of fewer than kCycT periods, up to this many generators in the
+// factorization and in the solves.  Factorization, launched front by front
+// against one launch: 5 generators x 4 periods (14 buses) 140 / 83 us, 7 x 63
+// (57 buses) 763 / 357, 16 x 24 (60 buses) 511 / 465, 17 x 24 574 / 623 (a front
+// of more than 32 rows spills).  Solve: 68 / 48 us, 405 / 145, 213 / 110, 32 x 48
+// (90 buses) 394 / 240, 32 x 6 141 / 115.
+constexpr int kWaveG = 16, kWaveSolveG = 32;
 constexpr int kBwdCols = 32;     // earlier columns updated per block of a backward launch, at least
 
 // Device view of one instance's plan.
@@ -81,9 +89,8 @@ struct CDev {
 
 // One front as the blocked kernels see it: p pivots, u update rows and where
 // its parts start in a period's storage: factor block ((p+u) x p, leading
-// dimension ld), diagonal
-// blocks (see diag_size), update block (u x u), update vector of the solves,
-// row list; its first elimination position and its children (CDev::kid).
+// dimension ld), diagonal blocks (see diag_size), update block (u x u), update
+// vector of the solves, row list; its first elimination position and its children (CDev::kid).
 struct FrontRec {
   int64_t L, D, U, W, R;
   int32_t p, u, ld, f, k0, k1;
@@ -806,6 +813,94 @@ __global__ void k_add_chain(const double* __restrict__ Us, int64_t sU, int32_t G
   }
 }
 
+// ---- the pg chain of few generators
+//
+// The pg chain of G <= FM / 2 generators by one block: one wavefront eliminates
+// the left fronts, one the right ones, front by front in step, a front's row
+// per lane as in small_front, its update block handed to the next front
+// through LDS; then the first one eliminates front m.  Launched front by front
+// such a chain spends three launches of 6 to 17 us on an elimination of G
+// dependent pivots, about 0.1 us each.  Arithmetic as in k_panel, k_update and
+// k_add_chain.  sC: from one front to the next; the ramp rows' part of the
+// factor stays in place, the diagonal blocks go to Dc (mirrored).
+template <int FM>
+__global__ void __launch_bounds__(128) k_chain_wave(int32_t G, int32_t T, double* __restrict__ Cf, int64_t sC,
+                                                    double* __restrict__ Dc, int64_t sD,
+                                                    const int32_t* __restrict__ stop, double tol, double repl,
+                                                    int32_t* __restrict__ npert) {
+  constexpr int H = FM / 2;
+  __shared__ double U[2][H * H];
+  __shared__ int32_t bad[2][2];
+  if (stopped(stop)) return;
+  const int i = (int)threadIdx.x & 63, side = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int m = (T - 1) / 2, ld = 2 * G;
+  PivotRule R;
+  R.tol = tol;
+  sqrt_recip(repl, R.s_repl, R.r_repl);
+  int low = 0;
+  double a[FM], nx[H];
+  // the pivot columns of a front of n rows
+  auto load = [&](int t, int n) {
+    const double* C = Cf + (int64_t)t * sC;
+#pragma unroll
+    for (int j = 0; j < H; ++j) nx[j] = j < G && i >= j && i < n ? C[j * ld + i] : 0.0;
+  };
+  // plus what the front before on side q leaves
+  auto take = [&](int q) {
+#pragma unroll
+    for (int j = 0; j < H; ++j)
+      if (j < G && i >= j && i < G) a[j] += U[q][j * H + i];
+  };
+  auto begin = [&]() {
+#pragma unroll
+    for (int j = 0; j < FM; ++j) a[j] = j < H ? nx[j] : 0.0;
+  };
+  auto eliminate = [&](int t, int n) {
+    double *C = Cf + (int64_t)t * sC, *D = Dc + (int64_t)t * sD;
+    for (int k = 0; k < G; ++k) {
+      double sq, r;
+      odd_pivot(lane_bcast(a[0], k), R, true, sq, r, low);
+      const double l = i == k ? sq : a[0] * r;
+      if (i >= G && i < n) C[k * ld + i] = l;
+      if (i >= k && i < G) {
+        D[k * G + i] = l;
+        D[i * G + k] = l;
+      }
+#pragma unroll
+      for (int j = 1; j < FM; ++j) a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
+      a[FM - 1] = 0.0;
+    }
+  };
+  const int steps = T - 1 - m;  // the right side's fronts, as many as the left's or one more
+  if (side == 1 ? steps > 0 : m > 0) load(side ? T - 1 : 0, 2 * G);
+  for (int s = 0; s < steps; ++s) {
+    const bool on = side || s < m;
+    if (on) {
+      begin();
+      if (s > 0) take(side);
+      if (s + 1 < (side ? steps : m)) load(side ? T - 2 - s : s + 1, 2 * G);
+      eliminate(side ? T - 1 - s : s, 2 * G);
+#pragma unroll
+      for (int j = 0; j < H; ++j)
+        if (j < G && i >= G + j && i < 2 * G) U[side][j * H + i - G] = a[j];
+    }
+    if (i == 0) bad[s & 1][side] = low;
+    __syncthreads();
+    if (stop && bad[s & 1][0] + bad[s & 1][1] > 0) {
+      if (i == 0 && low) atomicAdd(npert, low);
+      return;
+    }
+  }
+  if (side == 0) {
+    load(m, G);
+    begin();
+    if (m > 0) take(0);
+    if (steps > 0) take(1);
+    eliminate(m, G);
+  }
+  if (i == 0 && low) atomicAdd(npert, low);
+}
+
 // ---- cyclic reduction of the pg chain
 //
 // At level k (h = 2^k) the fronts h - 1 + j h, j < n = T / h, are left; the
@@ -1014,35 +1109,37 @@ struct Tri {
   int64_t sL, sD, sy, sw, sv;
 };
 
-// The 64 x 64 triangle of a panel, solved by one wavefront: lane i holds row i
+// The 64 x 64 triangle of a panel (or a smaller front's N x N one, N a multiple
+// of 16), solved by one wavefront: lane i holds row i
 // of the symmetric diagonal block in registers (forward: its entries left of
 // the diagonal, backward those right of it, which are column i below the
 // diagonal; 0 elsewhere), its entry v of the right-hand side and its pivot's
 // reciprocal.  Step k: every lane's product v r, of which lane k's is entry k
 // of the solution, broadcast, and one update -- four instructions, and 64 of
 // these steps are what a solve launch waits for.  Lanes past kb hold zeros.
+template <int N = 64>
 struct Triangle {
-  double t[64], r;
+  double t[N], r;
 };
-template <bool FWD>
-__device__ __forceinline__ void load64(Triangle& T, const double* __restrict__ D, int kb, int lane) {
+template <bool FWD, int N>
+__device__ __forceinline__ void load_triangle(Triangle<N>& T, const double* __restrict__ D, int kb, int lane) {
   const int at = min(lane, kb - 1);
 #pragma unroll
-  for (int k = 0; k < 64; ++k) T.t[k] = D[min(k, kb - 1) * kb + at];
+  for (int k = 0; k < N; ++k) T.t[k] = D[min(k, kb - 1) * kb + at];
   const double d = D[at * kb + at];
   int ln = lane < kb ? lane : (FWD ? 0 : 64);
   // the masks below are taken when they are needed (kept over a front's
   // panels they would fill the scalar registers four times over)
   asm volatile("" : "+v"(ln));
 #pragma unroll
-  for (int k = 0; k < 64; ++k) T.t[k] = (FWD ? k < ln : k > ln) ? T.t[k] : 0.0;
+  for (int k = 0; k < N; ++k) T.t[k] = (FWD ? k < ln : k > ln) ? T.t[k] : 0.0;
   T.r = lane < kb ? 1.0 / d : 0.0;
 }
-template <bool FWD>
-__device__ __forceinline__ double solve64(const Triangle& T, int kb, double v) {
+template <bool FWD, int N>
+__device__ __forceinline__ double solve_triangle(const Triangle<N>& T, int kb, double v) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int b = FWD ? q : 3 - q;
+  for (int q = 0; q < N / 16; ++q) {
+    const int b = FWD ? q : N / 16 - 1 - q;
     if (b * 16 >= kb) continue;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
@@ -1096,7 +1193,7 @@ __device__ __forceinline__ void wave_sum(double (&v)[N]) {
 // below them of the largest front, at least one; batch; fronts).  The launches
 // of a front follow one another, so a launch goes as far as one block can
 // alone: the columns' 64-column panels one after the other, each one's triangle
-// by one of two wavefronts in turn (solve64; the other loads the next), while
+// by one of two wavefronts in turn (solve_triangle; the other loads the next), while
 // the others load their rows of the panel -- the rows of the later panels,
 // which every block repeats, and the block's own ROWS.  (A launch per panel
 // took 8 us, most of it the way to the first loads and back; four panels in
@@ -1128,9 +1225,9 @@ __global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_
   double* z = A.z + (int64_t)blockIdx.y * A.sy + f.f;
   if (tid >= kInner + ROWS) {
     const int lane = tid & 63, odd = (tid - kInner - ROWS) >> 6;
-    Triangle T;
+    Triangle<> T;
     auto load = [&](int k) {
-      if (k < kend) load64<true>(T, D + (int64_t)k * kNB, min(kNB, kend - k), lane);
+      if (k < kend) load_triangle<true>(T, D + (int64_t)k * kNB, min(kNB, kend - k), lane);
     };
     double v = lane < kend - k0 ? y[k0 + lane] : 0.0;
     load(k0 + odd * kNB);
@@ -1138,7 +1235,7 @@ __global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_
       const int kb = min(kNB, kend - k);
       const bool mine = (q & 1) == odd;
       if (mine) {
-        const double x = solve64<true>(T, kb, v);
+        const double x = solve_triangle<true>(T, kb, v);
         xs[lane] = x;
         if (blockIdx.x == 0 && lane < kb) z[k + lane] = x;
       }
@@ -1305,16 +1402,16 @@ __global__ void __launch_bounds__(kBwdT) k_bwd_panel(Tri A, int32_t q, int32_t c
   constexpr int NW = kBwdT / 64 - 2, UN = 4;
   if (wv >= NW) {
     const int odd = wv - NW;
-    Triangle T;
+    Triangle<> T;
     auto load = [&](int k) {
-      if (k >= k0) load64<false>(T, D + (int64_t)k * kNB, min(kNB, f.p - k), lane);
+      if (k >= k0) load_triangle<false>(T, D + (int64_t)k * kNB, min(kNB, f.p - k), lane);
     };
     load((pe - 1 - odd) * kNB);
     for (int k = (pe - 1) * kNB, c = 0; k >= k0; k -= kNB, ++c) {
       const int kb = min(kNB, f.p - k);
       const bool mine = (c & 1) == odd;
       if (mine) {
-        const double x = solve64<false>(T, kb, lane < kb ? zs[k - k0 + lane] : 0.0);
+        const double x = solve_triangle<false>(T, kb, lane < kb ? zs[k - k0 + lane] : 0.0);
         xs[lane] = x;
         if (blockIdx.x == 0 && lane < kb) y[k + lane] = x;
       }
@@ -1353,6 +1450,83 @@ __global__ void __launch_bounds__(kBwdT) k_bwd_panel(Tri A, int32_t q, int32_t c
       }
     }
     __syncthreads();
+  }
+}
+
+// Both solves along a chain factored by k_chain_wave, in one block of two
+// wavefronts: the left and the right fronts' forward solves, front m's two, the
+// backward solves outwards, the next front's factor loaded meanwhile.  Y, Z:
+// the pg right-hand side / solution and forward solution of period 0, sy from
+// one period to the next.  Sums as in k_fwd_panel, k_sub, k_bwd_gemv (whose
+// butterfly over the lanes is a tree over a column's entries here) and
+// k_bwd_panel.
+template <int N>
+__global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, const double* __restrict__ Cf,
+                                                          int64_t sC, const double* __restrict__ Dc, int64_t sD,
+                                                          double* __restrict__ Y, double* __restrict__ Z, int64_t sy) {
+  __shared__ double sh[2][64], xm[64];
+  const int i = (int)threadIdx.x & 63, side = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int m = (T - 1) / 2, ld = 2 * G, g = min(i, G - 1);
+  const int n = side ? T - 1 - m : m;  // the side's fronts
+  auto front = [&](int s) { return side ? T - 1 - s : s; };
+  struct Front {
+    Triangle<N> T;
+    double l[N], y;
+  } A, B;
+  // forward: lane i its ramp row's entries; backward: its column's
+  auto load = [&](Front& F, int s, auto fwd) {
+    const int t = front(s);
+    const double *C = Cf + (int64_t)t * sC + G, *v = (fwd() ? Y : Z) + (int64_t)t * sy;
+    load_triangle<fwd()>(F.T, Dc + (int64_t)t * sD, G, i);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const double e = fwd() ? C[min(k, G - 1) * ld + g] : C[g * ld + min(k, G - 1)];
+      F.l[k] = k < G ? e : 0.0;
+    }
+    F.y = i < G ? v[i] : 0.0;
+  };
+  constexpr std::true_type fwd;
+  constexpr std::false_type bwd;
+  double sum = 0.0;
+  if (n > 0) load(A, 0, fwd);
+  for (int s = 0; s < n; ++s) {
+    if (s + 1 < n) load(B, s + 1, fwd);
+    const double z = solve_triangle<true>(A.T, G, s > 0 && i < G ? A.y - sum : A.y);
+    if (i < G) Z[(int64_t)front(s) * sy + i] = z;
+    sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) sum += A.l[k] * lane_bcast(z, k);
+    A = B;
+  }
+  if (n > 0) load(B, n - 1, bwd);
+  sh[side][i] = sum;
+  __syncthreads();
+  if (side == 0) {
+    double v = i < G ? Y[(int64_t)m * sy + i] : 0.0;
+    if (m > 0 && i < G) v -= sh[0][i];
+    if (T > 1 && i < G) v -= sh[1][i];
+    Triangle<N> M;
+    load_triangle<true>(M, Dc + (int64_t)m * sD, G, i);
+    v = solve_triangle<true>(M, G, v);
+    load_triangle<false>(M, Dc + (int64_t)m * sD, G, i);
+    v = solve_triangle<false>(M, G, v);
+    if (i < G) Y[(int64_t)m * sy + i] = v;
+    xm[i] = v;
+  }
+  __syncthreads();
+  double x = xm[i];
+  for (int s = n - 1; s >= 0; --s) {
+    A = B;
+    if (s > 0) load(B, s - 1, bwd);
+    double w[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = A.l[k] * lane_bcast(x, k);
+#pragma unroll
+    for (int d = N / 2; d > 0; d /= 2)
+#pragma unroll
+      for (int k = 0; k < d; ++k) w[k] += w[k + d];
+    x = solve_triangle<false>(A.T, G, i < G ? A.y - w[0] : 0.0);
+    if (i < G) Y[(int64_t)front(s) * sy + i] = x;
   }
 }
 
@@ -1442,7 +1616,8 @@ struct CholInst {
   double* Gp = nullptr;  // running sums of the chain's L21 z (a step's fronts)
   std::vector<FrontRec> rec;  // the large fronts, by level
   FrontRec crec[3];           // the pg fronts: with no, G and 2 G update rows
-  bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends
+  bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends:
+  bool wave = false, wave_solve = false;  // by two wavefronts
   int32_t cld = 0;            // their leading dimension: 2 G or 3 G
   double* Uc = nullptr;       // cyclic reduction: a level's update blocks
   FrontRec *d_rec = nullptr, *d_srec = nullptr;  // large fronts; small ones, by level
@@ -1648,6 +1823,8 @@ int setup_device(opf_chol* F, CholInst& C) {
   }
   C.dcsize = diag_size(P.G);
   C.cyclic = P.T >= kCycT && P.G <= kCycG;
+  C.wave = P.T < kCycT && P.G >= 1 && P.G <= kWaveG;
+  C.wave_solve = P.T < kCycT && P.G >= 1 && P.G <= kWaveSolveG;
   C.cld = (C.cyclic ? 3 : 2) * P.G;
   for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
@@ -1859,7 +2036,7 @@ int factor_inst(opf_chol* F, CholInst& C, bool first, const double* kv, double t
     if (b > a) chunks.push_back({a, b - a});
   }
   const int nchunk = (int)chunks.size();
-  if (!C.cyclic && nchunk + 1 > (int)F->evs.size()) return api_fail(OPF_EINVAL, "chol: more period chunks than events");
+  if (!C.cyclic && !C.wave && nchunk + 1 > (int)F->evs.size()) return api_fail(OPF_EINVAL, "chol: more period chunks than events");
   std::vector<char> ready(T, 0);
   int kl = 0, kr = T - 1;
   double* UsL = F->Us;
@@ -1945,7 +2122,7 @@ int factor_inst(opf_chol* F, CholInst& C, bool first, const double* kv, double t
     hipLaunchKernelGGL(k_extend_root, dim3((G + 3) / 4, nt), dim3(256), 0, st, C.dev, t0, C.Cf, C.csize,
                        (int64_t)C.cld, C.Ar);
     LAUNCH_OK("chol pg front assembly");
-    if (C.cyclic) continue;
+    if (C.cyclic || C.wave) continue;
     // the chain steps this chunk makes ready, on the chain stream
     if (hipEventRecord(F->evs[chunk_id], st) != hipSuccess || hipStreamWaitEvent(F->cs, F->evs[chunk_id], 0) != hipSuccess)
       return api_fail(OPF_EHIP, "chol: chain stream ordering");
@@ -1953,6 +2130,16 @@ int factor_inst(opf_chol* F, CholInst& C, bool first, const double* kv, double t
     CHK(chain_steps(chunk_id + 1 == nchunk));
   }
   if (C.cyclic) return factor_cyclic(C, tol, repl, npert, st);
+  if (C.wave) {
+    auto go = [&](auto k) {
+      hipLaunchKernelGGL(k, dim3(1), dim3(128), 0, st, (int32_t)G, (int32_t)T, C.Cf, C.csize, C.Dc, C.dcsize, C.dev.stop,
+                         tol, repl, npert);
+    };
+    if (G <= 8) go(k_chain_wave<16>);
+    else go(k_chain_wave<32>);
+    LAUNCH_OK("chol chain by wavefronts");
+    return OPF_OK;
+  }
   // front m: both sides' last updates, no update rows
   if (m >= 1) CHK(add_in(m, UsL));
   if (m + 1 <= T - 1) CHK(add_in(m, UsR));
@@ -2085,6 +2272,14 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   };
   if (C.cyclic) {
     CHK(solve_cyclic(C, st));
+  } else if (C.wave_solve) {
+    auto go = [&](auto k) {
+      hipLaunchKernelGGL(k, dim3(1), dim3(128), 0, st, (int32_t)G, (int32_t)T, (const double*)C.Cf, C.csize,
+                         (const double*)C.Dc, C.dcsize, C.Y + P.n_int, C.Z + P.n_int, np);
+    };
+    if (G <= 16) go(k_chain_wave_solve<16>);
+    else go(k_chain_wave_solve<32>);
+    LAUNCH_OK("chol chain solve by wavefronts");
   } else {
     int kl = 0, kr = T - 1;
     while (kl < m || kr > m) {
@@ -2111,7 +2306,7 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
   }
   // backward along the pg chain: front m, then outwards (each front reads
   // its chain neighbour's solution, held in Y)
-  if (!C.cyclic) {
+  if (!C.cyclic && !C.wave_solve) {
     CHK(bwd_tri(chain(m, 1, m), C.crec, 1, 1, st));
     int kl = m - 1, kr = m + 1;
     while (kl >= 0 || kr <= T - 1) {

@@ -130,3 +130,31 @@ def test_pivots_of_extreme_size(dev):  # noqa: F811
     assert got[pg] == 0.0 and np.all(np.isfinite(got))
     F.close()
     M.close()
+
+
+# either side of the chain's forms by wavefronts (8 / 9, 16 / 17, 32 / 33
+# generators; horizons with none, one and more fronts on a side, and the last
+# one before cyclic reduction)
+@pytest.mark.parametrize("G", [1, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 63])
+def test_chain_by_wavefronts(G, T, dev):  # noqa: F811
+    """Against the oracle, and the static pivots' count the same with and
+    without a second factorization in between."""
+    import torch
+    from paper_2405_14032_amd import capi
+    nets = [synth.make_network(40, 56, G, T, 71)]
+    print(f"chain by wavefronts: G={G} T={T}", flush=True)
+    M = capi.Model(nets, device=0)
+    M.use_current_torch_stream()
+    F = capi.Chol(M)
+    inps = _inputs(nets, "well", 19)
+    bad = [dict(inps[0], diag_x=np.where(np.arange(len(inps[0]["diag_x"])) % 3 == 0, -1e6, inps[0]["diag_x"]))]
+    _, full = _gpu_solve(M, F, bad, torch, dev)
+    x, npert = _gpu_solve(M, F, inps, torch, dev, repeat=2)
+    _, again = _gpu_solve(M, F, bad, torch, dev)
+    F.set_stop_on_pivot(True)
+    _, part = _gpu_solve(M, F, bad, torch, dev)
+    F.close()
+    M.close()
+    assert npert == 0 and full == again and full >= 1 and 1 <= part <= full
+    _check(nets, inps, x, "well", f"chain by wavefronts G={G} T={T}")
