@@ -58,8 +58,8 @@ constexpr int kCycT = 64, kCycG = 1536;
 // The pg chain by two wavefronts (see k_chain_wave, k_chain_wave_solve) over
 // horizons of fewer than kCycT periods, up to this many generators in the
 // factorization and in the solves.  Factorization, launched front by front
-// against one launch: 5 generators x 4 periods (14 buses) 140 / 83 us, 7 x 63
-// (57 buses) 763 / 357, 16 x 24 (60 buses) 511 / 465, 17 x 24 574 / 623 (a front
+// against one launch: 5 generators x 4 periods (14 buses) 140 / 72 us, 7 x 63
+// (57 buses) 763 / 313, 16 x 24 (60 buses) 511 / 395, 17 x 24 574 / 623 (a front
 // of more than 32 rows spills).  Solve: 68 / 48 us, 405 / 145, 213 / 110, 32 x 48
 // (90 buses) 394 / 240, 32 x 6 141 / 115.
 constexpr int kWaveG = 16, kWaveSolveG = 32;
@@ -322,6 +322,61 @@ __device__ __forceinline__ bool is_odd(double d, double tol) {
   return hi - 0x20c00000u > 0x5f200000u - 0x20c00000u || !(d > tol);
 }
 
+// One step of an elimination held a row per lane, a[0] the column eliminated
+// (l its factored entries, lane k its pivot's row): the columns behind it take
+// their update and move one to the left.  The new a[0] comes first, and its
+// pivot's square root and reciprocal (s, r), the serial chain of the whole
+// elimination, run between the updates of the others, an eighth of them after
+// each of its dependent instructions; the empty asm statements hold that order.
+// (One after the other: 37.5 us for a launch of fronts of 48 rows, now 32.6; 13.2
+// and 11.0 for up to 32 rows.)
+template <int FM>
+__device__ __forceinline__ void next_column(double (&a)[FM], double l, int k, bool count, const PivotRule& R,
+                                            double& s, double& r, int& low) {
+  a[0] = fma(-l, lane_bcast(l, (k + 1) & 63), a[1]);
+  const double d = lane_bcast(a[0], (k + 1) & 63);
+  auto fill = [&](auto eighth) {
+    constexpr int q = decltype(eighth)::value, j0 = 2 + (FM - 2) * q / 8, j1 = 2 + (FM - 2) * (q + 1) / 8;
+#pragma unroll
+    for (int j = j0; j < j1; ++j) {
+      a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
+      asm volatile("" : "+v"(a[j - 1]));
+    }
+  };
+  double y = __builtin_amdgcn_rsq(d);
+  asm volatile("" : "+v"(y));
+  fill(std::integral_constant<int, 0>());
+  double g = d * y, h = 0.5 * y;
+  asm volatile("" : "+v"(g), "+v"(h));
+  fill(std::integral_constant<int, 1>());
+  double e = fma(-h, g, 0.5);
+  asm volatile("" : "+v"(e));
+  fill(std::integral_constant<int, 2>());
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  asm volatile("" : "+v"(g), "+v"(h));
+  fill(std::integral_constant<int, 3>());
+  e = fma(-h, g, 0.5);
+  asm volatile("" : "+v"(e));
+  fill(std::integral_constant<int, 4>());
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  asm volatile("" : "+v"(g), "+v"(h));
+  fill(std::integral_constant<int, 5>());
+  e = fma(-g, g, d);
+  asm volatile("" : "+v"(e));
+  fill(std::integral_constant<int, 6>());
+  g = fma(e, h, g);
+  h = h + h;
+  asm volatile("" : "+v"(g), "+v"(h));
+  fill(std::integral_constant<int, 7>());
+  a[FM - 1] = 0.0;
+  e = fma(-g, h, 1.0);
+  s = g;
+  r = fma(e, h, h);
+  if (is_odd(d, R.tol)) odd_pivot(d, R, count, s, r, low);
+}
+
 // A small front (p + u = f <= FM <= 64) by one wavefront: lane i owns row i in
 // registers (entries above the diagonal are scratch that no valid entry ever
 // reads, so the updates run unmasked).  The children's update matrices are
@@ -361,14 +416,12 @@ __device__ __forceinline__ void small_front(const CDev& D, const FrontRec& F, do
       for (int j = 0; j < 8; ++j) a[j0 + j] = ok[j] ? a[j0 + j] + w[j] : a[j0 + j];
     }
   }
+  double s, r;
+  odd_pivot(lane_bcast(a[0], 0), R, p > 0, s, r, low);
   for (int k = 0; k < p; ++k) {
-    double sq, r;
-    odd_pivot(lane_bcast(a[0], k), R, true, sq, r, low);
-    const double l = i == k ? sq : a[0] * r;
+    const double l = i == k ? s : a[0] * r;
     if (i >= k && i < f) L[k * f + i] = l;
-#pragma unroll
-    for (int j = 1; j < FM; ++j) a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
-    a[FM - 1] = 0.0;
+    next_column(a, l, k, k + 1 < p, R, s, r, low);
   }
   double* U = Ut + F.U;
 #pragma unroll
@@ -857,18 +910,16 @@ __global__ void __launch_bounds__(128) k_chain_wave(int32_t G, int32_t T, double
   };
   auto eliminate = [&](int t, int n) {
     double *C = Cf + (int64_t)t * sC, *D = Dc + (int64_t)t * sD;
+    double s, r;
+    odd_pivot(lane_bcast(a[0], 0), R, true, s, r, low);
     for (int k = 0; k < G; ++k) {
-      double sq, r;
-      odd_pivot(lane_bcast(a[0], k), R, true, sq, r, low);
-      const double l = i == k ? sq : a[0] * r;
+      const double l = i == k ? s : a[0] * r;
       if (i >= G && i < n) C[k * ld + i] = l;
       if (i >= k && i < G) {
         D[k * G + i] = l;
         D[i * G + k] = l;
       }
-#pragma unroll
-      for (int j = 1; j < FM; ++j) a[j - 1] = fma(-l, lane_bcast(l, (k + j) & 63), a[j]);
-      a[FM - 1] = 0.0;
+      next_column(a, l, k, k + 1 < G, R, s, r, low);
     }
   };
   const int steps = T - 1 - m;  // the right side's fronts, as many as the left's or one more
