@@ -11,11 +11,10 @@
 namespace opf {
 
 struct CholOptions {
-  int32_t small_max = 64;     // fronts of at most this order are factored in LDS
+  int32_t small_max = 64;     // fronts of at most this order are factored by one wavefront
   int32_t amalg_small = 16;   // merged pivot blocks up to this size: relaxed merge
   double amalg_frac = 0.05;   // otherwise merge while its zeros <= frac of the front
   int32_t max_pivots = 4096;  // no merge beyond this many pivots
-  int32_t col_block = 32;     // columns per extend-add work item
 };
 
 // Local indices: "old" = position in the period block of x (the canonical
@@ -41,9 +40,6 @@ struct CholPlan {
   // level schedule
   std::vector<int32_t> lvl_small, lvl_large;
   std::vector<int64_t> lvl_small_ptr, lvl_large_ptr;
-  std::vector<int32_t> items;        // (node, first column) pairs
-  std::vector<int64_t> lvl_items_ptr;
-  std::vector<int32_t> root_items;   // first columns of the pg front's items
   // K template slot -> destination (see chol_plan_build), K positions
   std::vector<int64_t> slot_dst;
   std::vector<int32_t> kpos0, kpos1, ramp_pos;

@@ -578,7 +578,7 @@ int chol_plan_build(const InstHost& I, const CholOptions& opt, CholPlan& P, std:
     }
     P.usize = std::max<int64_t>(peak, 1);
   }
-  // level lists: small fronts (LDS kernels) and large ones (blocked)
+  // level lists: small fronts (a wavefront each) and large ones (blocked)
   P.lvl_small_ptr.assign(H + 1, 0);
   P.lvl_large_ptr.assign(H + 1, 0);
   {
@@ -594,23 +594,6 @@ int chol_plan_build(const InstHost& I, const CholOptions& opt, CholPlan& P, std:
       P.lvl_large_ptr[h + 1] = (int64_t)P.lvl_large.size();
     }
   }
-  // extend-add work items per level: (node, first column) in blocks of
-  // opt.col_block columns of the node's front
-  P.lvl_items_ptr.assign(H + 1, 0);
-  for (int32_t h = 0; h < H; ++h) {
-    for (int32_t s = 0; s < ns; ++s) {
-      if (P.node_level[s] != h) continue;
-      const int32_t f = P.node_p[s] + P.node_u[s];
-      for (int32_t c0 = 0; c0 < f; c0 += opt.col_block) {
-        P.items.push_back(s);
-        P.items.push_back(c0);
-      }
-    }
-    P.lvl_items_ptr[h + 1] = (int64_t)P.items.size() / 2;
-  }
-  // the pg front of a period collects its tree roots: items over its G
-  // columns
-  for (int32_t c0 = 0; c0 < G; c0 += opt.col_block) P.root_items.push_back(c0);
   // destinations of the K template slots: >= 0 an interior factor offset,
   // < 0 the pg front, -1 - (col * 2G + row)
   P.slot_dst.resize(I.krow[np]);
