@@ -9,14 +9,15 @@
 //   * K's entries are written straight into the factor blocks; each front
 //     then pulls its children's update matrices (extend-add, no atomics: a
 //     work item owns a set of the parent's columns), is factored in place
-//     (small fronts in LDS by one wavefront, large ones by blocked panel +
-//     trailing-update kernels), batched over the periods of a chunk;
+//     (small fronts in registers by one wavefront, large ones by blocked panel
+//     + trailing-update kernels), batched over the periods of a chunk;
 //   * the pg front of period t (G pivots) collects the period's tree roots
 //     and its chain neighbour's update: a chain over t, eliminated from both
 //     ends at once (fronts t < m carry update rows pg_{t+1}, fronts t > m
 //     update rows pg_{t-1}, front m closes it; m = (T - 1) / 2), one front of
 //     each side per launch; over long horizons by cyclic reduction instead
-//     (every other front at once, see k_cyc_add).
+//     (every other front at once, see k_cyc_add), with few generators by one
+//     launch (k_chain_wave).
 // Solves run the same tree forward (update vectors pulled by the parent)
 // and backward (gathers of the ancestors' solution), batched over periods.
 #include <hip/hip_runtime.h>
@@ -53,8 +54,10 @@ constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 
 // third of the work it adds outgrows the steps it saves.  Short horizons gain
 // less (400 x 24: 11.2 / 8.9 ms) and stay with the chain: an interior-point
 // iterate shows a changed elimination order at 1e-8, and small grids keep
-// theirs bit for bit.
+// theirs bit for bit.  The memory it takes beyond the chain's (G^2 per period
+// for the pg fronts, 2 G^2 for a level's update blocks) is held to kCycBytes.
 constexpr int kCycT = 64, kCycG = 1536;
+constexpr int64_t kCycBytes = 16LL << 30;
 // The pg chain by two wavefronts (see k_chain_wave, k_chain_wave_solve) over
 // horizons of fewer than kCycT periods, up to this many generators in the
 // factorization and in the solves.  Factorization, launched front by front
@@ -1873,7 +1876,7 @@ int setup_device(opf_chol* F, CholInst& C) {
     }
   }
   C.dcsize = diag_size(P.G);
-  C.cyclic = P.T >= kCycT && P.G <= kCycG;
+  C.cyclic = P.T >= kCycT && P.G <= kCycG && 24LL * P.G * P.G * P.T <= kCycBytes;
   C.wave = P.T < kCycT && P.G >= 1 && P.G <= kWaveG;
   C.wave_solve = P.T < kCycT && P.G >= 1 && P.G <= kWaveSolveG;
   C.cld = (C.cyclic ? 3 : 2) * P.G;
