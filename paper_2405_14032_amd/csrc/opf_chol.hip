@@ -64,8 +64,9 @@ constexpr int64_t kCycBytes = 16LL << 30;
 // against one launch: 5 generators x 4 periods (14 buses) 140 / 72 us, 7 x 63
 // (57 buses) 763 / 313, 16 x 24 (60 buses) 511 / 395, 17 x 24 574 / 623 (a front
 // of more than 32 rows spills).  Solve: 68 / 48 us, 405 / 145, 213 / 110, 32 x 48
-// (90 buses) 394 / 240, 32 x 6 141 / 115.
-constexpr int kWaveG = 16, kWaveSolveG = 32;
+// (90 buses) 391 / 224, 48 x 24 283 / 210, 54 x 24 (118 buses) 327 / 298, 64 x 24
+// 301 / 290.
+constexpr int kWaveG = 16, kWaveSolveG = 64;
 constexpr int kBwdCols = 32;     // earlier columns updated per block of a backward launch, at least
 
 // Device view of one instance's plan.
@@ -1518,6 +1519,7 @@ template <int N>
 __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, const double* __restrict__ Cf,
                                                           int64_t sC, const double* __restrict__ Dc, int64_t sD,
                                                           double* __restrict__ Y, double* __restrict__ Z, int64_t sy) {
+  constexpr bool kAhead = N <= 32;  // two fronts of more do not fit the registers
   __shared__ double sh[2][64], xm[64];
   const int i = (int)threadIdx.x & 63, side = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int m = (T - 1) / 2, ld = 2 * G, g = min(i, G - 1);
@@ -1542,17 +1544,18 @@ __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, 
   constexpr std::true_type fwd;
   constexpr std::false_type bwd;
   double sum = 0.0;
-  if (n > 0) load(A, 0, fwd);
+  if (kAhead && n > 0) load(A, 0, fwd);
   for (int s = 0; s < n; ++s) {
-    if (s + 1 < n) load(B, s + 1, fwd);
+    if (!kAhead) load(A, s, fwd);
+    else if (s + 1 < n) load(B, s + 1, fwd);
     const double z = solve_triangle<true>(A.T, G, s > 0 && i < G ? A.y - sum : A.y);
     if (i < G) Z[(int64_t)front(s) * sy + i] = z;
     sum = 0.0;
 #pragma unroll
     for (int k = 0; k < N; ++k) sum += A.l[k] * lane_bcast(z, k);
-    A = B;
+    if (kAhead) A = B;
   }
-  if (n > 0) load(B, n - 1, bwd);
+  if (kAhead && n > 0) load(B, n - 1, bwd);
   sh[side][i] = sum;
   __syncthreads();
   if (side == 0) {
@@ -1570,15 +1573,16 @@ __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, 
   __syncthreads();
   double x = xm[i];
   for (int s = n - 1; s >= 0; --s) {
-    A = B;
-    if (s > 0) load(B, s - 1, bwd);
+    if (kAhead) A = B;
+    if (!kAhead) load(A, s, bwd);
+    else if (s > 0) load(B, s - 1, bwd);
     double w[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) w[k] = A.l[k] * lane_bcast(x, k);
 #pragma unroll
-    for (int d = N / 2; d > 0; d /= 2)
+    for (int d = N > 32 ? 32 : N / 2; d > 0; d /= 2)
 #pragma unroll
-      for (int k = 0; k < d; ++k) w[k] += w[k + d];
+      for (int k = 0; k < d && k + d < N; ++k) w[k] += w[k + d];
     x = solve_triangle<false>(A.T, G, i < G ? A.y - w[0] : 0.0);
     if (i < G) Y[(int64_t)front(s) * sy + i] = x;
   }
@@ -2332,7 +2336,9 @@ int solve_inst(CholInst& C, const double* b, double* x, hipStream_t st) {
                          (const double*)C.Dc, C.dcsize, C.Y + P.n_int, C.Z + P.n_int, np);
     };
     if (G <= 16) go(k_chain_wave_solve<16>);
-    else go(k_chain_wave_solve<32>);
+    else if (G <= 32) go(k_chain_wave_solve<32>);
+    else if (G <= 48) go(k_chain_wave_solve<48>);
+    else go(k_chain_wave_solve<64>);
     LAUNCH_OK("chol chain solve by wavefronts");
   } else {
     int kl = 0, kr = T - 1;

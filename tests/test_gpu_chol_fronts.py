@@ -132,17 +132,17 @@ def test_pivots_of_extreme_size(dev):  # noqa: F811
     M.close()
 
 
-# either side of the chain's forms by wavefronts (8 / 9, 16 / 17, 32 / 33
-# generators; horizons with none, one and more fronts on a side, and the last
+# either side of the chain's forms by wavefronts (8 / 9, 16 / 17, 32 / 33,
+# 48 / 49, 64 / 65 generators; horizons with none, one and more fronts on a side, and the last
 # one before cyclic reduction)
-@pytest.mark.parametrize("G", [1, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("G", [1, 8, 9, 16, 17, 32, 33, 48, 49, 64, 65])
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 63])
 def test_chain_by_wavefronts(G, T, dev):  # noqa: F811
     """Against the oracle, and the static pivots' count the same with and
     without a second factorization in between."""
     import torch
     from paper_2405_14032_amd import capi
-    nets = [synth.make_network(40, 56, G, T, 71)]
+    nets = [synth.make_network(max(40, G), max(56, int(1.4 * G)), G, T, 71)]
     print(f"chain by wavefronts: G={G} T={T}", flush=True)
     M = capi.Model(nets, device=0)
     M.use_current_torch_stream()
