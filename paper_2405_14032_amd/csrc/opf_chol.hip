@@ -876,8 +876,8 @@ __global__ void k_add_chain(const double* __restrict__ Us, int64_t sU, int32_t G
 // the left fronts, one the right ones, front by front in step, a front's row
 // per lane as in small_front, its update block handed to the next front
 // through LDS; then the first one eliminates front m.  Launched front by front
-// such a chain spends three launches of 6 to 17 us on an elimination of G
-// dependent pivots, about 0.1 us each.  Arithmetic as in k_panel, k_update and
+// such a chain spends three launches of 3 to 12 us on an elimination of G
+// dependent pivots, about 0.5 us each (6 generators x 24 periods: 44 us in all).  Arithmetic as in k_panel, k_update and
 // k_add_chain.  sC: from one front to the next; the ramp rows' part of the
 // factor stays in place, the diagonal blocks go to Dc (mirrored).
 template <int FM>
