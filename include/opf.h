@@ -365,7 +365,12 @@ typedef struct {
  * OPF_ENOMEM (host or device allocation), OPF_EHIP.  The update-matrix
  * workspace holds the fronts of as many periods as fit in 16 GiB (the
  * environment variable OPF_CHOL_ARENA_BYTES, read here, overrides the
- * budget); those periods are factored together. */
+ * budget); those periods are factored together.  Cyclic reduction of the pg
+ * chain (from 64 periods, up to 1536 generators) takes at most 16 GiB more
+ * than the chain from both ends, over all instances together
+ * (OPF_CHOL_CYCLIC_BYTES, read here, overrides that; 0: never); an instance
+ * beyond that, and every instance if the allocation fails, takes the chain
+ * from both ends. */
 int opf_chol_analyze(opf_model *model, opf_chol **out);
 void opf_chol_destroy(opf_chol *chol); /* NULL is a no-op */
 int opf_chol_get_info(const opf_chol *chol, opf_chol_info *info);

@@ -55,7 +55,8 @@ constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 
 // less (400 x 24: 11.2 / 8.9 ms) and stay with the chain: an interior-point
 // iterate shows a changed elimination order at 1e-8, and small grids keep
 // theirs bit for bit.  The memory it takes beyond the chain's (G^2 per period
-// for the pg fronts, 2 G^2 for a level's update blocks) is held to kCycBytes.
+// for the pg fronts, 2 G^2 for a level's update blocks, which the instances of
+// a batch share) is held to kCycBytes over all instances together.
 constexpr int kCycT = 64, kCycG = 1536;
 constexpr int64_t kCycBytes = 16LL << 30;
 // The pg chain by two wavefronts (see k_chain_wave, k_chain_wave_solve) over
@@ -1677,7 +1678,7 @@ struct CholInst {
   bool cyclic = false;        // pg fronts by cyclic reduction, else from both ends:
   bool wave = false, wave_solve = false;  // by two wavefronts
   int32_t cld = 0;            // their leading dimension: 2 G or 3 G
-  double* Uc = nullptr;       // cyclic reduction: a level's update blocks
+  double* Uc = nullptr;       // cyclic reduction: a level's update blocks (in Ar, or opf_chol::Uc)
   FrontRec *d_rec = nullptr, *d_srec = nullptr;  // large fronts; small ones, by level
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
   int32_t chunk = 1, nlarge = 0;
@@ -1690,6 +1691,7 @@ struct opf_chol {
   int device = -1;
   std::vector<CholInst> inst;
   double* Us = nullptr;  // two G x G update blocks of the pg chain, one per end (largest G)
+  double* Uc = nullptr;  // cyclic reduction's update blocks, where an instance's Ar does not hold them (largest level)
   // the pg chain runs on a stream of its own, chunk by chunk, behind the
   // interior fronts of the next chunk (events order the two)
   hipStream_t cs = nullptr;
@@ -1742,6 +1744,20 @@ int64_t arena_budget() {
   return kArenaBudget;
 }
 
+// Budget of cyclic reduction's additional memory: OPF_CHOL_CYCLIC_BYTES (bytes,
+// 0: the chain from both ends at every size) overrides the default.
+int64_t cyclic_budget() {
+  const char* e = std::getenv("OPF_CHOL_CYCLIC_BYTES");
+  if (e && *e) {
+    const long long v = std::atoll(e);
+    if (v >= 0) return (int64_t)v;
+  }
+  return kCycBytes;
+}
+
+// Update blocks of cyclic reduction, in doubles: the first level has the most.
+int64_t cyclic_blocks(const CholPlan& P) { return (P.T + 1) / 2 * 4LL * P.G * P.G; }
+
 template <class T>
 int upload(opf_chol* F, const std::vector<T>& h, T** d) {
   const size_t bytes = std::max<size_t>(1, h.size()) * sizeof(T);
@@ -1762,6 +1778,7 @@ int dalloc(opf_chol* F, int64_t n, double** d) {
 void release(opf_chol* F) {
   for (void* p : F->allocs) (void)hipFree(p);
   F->allocs.clear();
+  F->Us = F->Uc = nullptr;
   if (F->work) (void)hipFree(F->work);
   F->work = nullptr;
 }
@@ -1880,7 +1897,6 @@ int setup_device(opf_chol* F, CholInst& C) {
     }
   }
   C.dcsize = diag_size(P.G);
-  C.cyclic = P.T >= kCycT && P.G <= kCycG && 24LL * P.G * P.G * P.T <= kCycBytes;
   C.wave = P.T < kCycT && P.G >= 1 && P.G <= kWaveG;
   C.wave_solve = P.T < kCycT && P.G >= 1 && P.G <= kWaveSolveG;
   C.cld = (C.cyclic ? 3 : 2) * P.G;
@@ -1921,11 +1937,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Y));
   CHK(dalloc(F, (int64_t)P.n_p * T, &C.Z));
   CHK(dalloc(F, C.cyclic ? (T + 1) / 2 * 2 * G : 2 * G, &C.Gp));
-  // a level's update blocks: the first level has the most, and the interior
-  // fronts' workspace is free by then
-  const int64_t nuc = C.cyclic ? (T + 1) / 2 * 4 * G * G : 0;
-  if (nuc <= P.usize * C.chunk) C.Uc = C.Ar;
-  else CHK(dalloc(F, nuc, &C.Uc));
   CHK(dalloc(F, C.wsize * T, &C.V));
   CDev& D = C.dev;
   D.node_f = C.d_node_f;
@@ -1945,6 +1956,43 @@ int setup_device(opf_chol* F, CholInst& C) {
   D.n_p = P.n_p;
   D.n_int = P.n_int;
   D.G = P.G;
+  return OPF_OK;
+}
+
+// The instances' forms, device tables and storage; cyc: what cyclic reduction
+// may add to the chain's memory, all instances together.
+int setup_instances(opf_chol* F, int64_t cyc) {
+  int64_t fronts = 0, blocks = 0, uc = 0, maxG = 0;
+  bool any = false;
+  for (auto& C : F->inst) {
+    const CholPlan& P = C.plan;
+    const int64_t f = fronts + (int64_t)P.G * P.G * P.T, b = std::max(blocks, cyclic_blocks(P));
+    C.cyclic = P.T >= kCycT && P.G <= kCycG && 8 * (f + b) <= cyc;
+    if (C.cyclic) {
+      fronts = f;
+      blocks = b;
+      any = true;
+    }
+    maxG = std::max<int64_t>(maxG, P.G);
+  }
+  F->arena_entries = 0;
+  for (auto& C : F->inst) {
+    CHK(setup_device(F, C));
+    const int64_t ar = C.plan.usize * C.chunk;
+    F->arena_entries += ar;
+    // the interior fronts' workspace is free when the reduction starts, and
+    // the instances are factored one after another
+    if (C.cyclic && cyclic_blocks(C.plan) <= ar) C.Uc = C.Ar;
+    else if (C.cyclic) uc = std::max(uc, cyclic_blocks(C.plan));
+  }
+  if (uc > 0) CHK(dalloc(F, uc, &F->Uc));
+  F->arena_entries += uc;
+  for (auto& C : F->inst)
+    if (C.cyclic && !C.Uc) C.Uc = F->Uc;
+  CHK(dalloc(F, 2 * maxG * maxG, &F->Us));
+  const char* inj = std::getenv("OPF_TEST_FAIL_ALLOC");
+  if (any && inj && std::strcmp(inj, "cyclic") == 0)
+    return api_fail(OPF_ENOMEM, "allocation failure injected by OPF_TEST_FAIL_ALLOC");
   return OPF_OK;
 }
 
@@ -2431,7 +2479,6 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
     const auto& insts = model_insts(model);
     F->inst.resize(insts.size());
     CholOptions opt;
-    int32_t maxG = 0;
     for (size_t k = 0; k < insts.size(); ++k) {
       CholInst& C = F->inst[k];
       C.I = &insts[k];
@@ -2443,7 +2490,6 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
       }
       const CholPlan& P = C.plan;
       C.nlarge = (int32_t)P.lvl_large.size();
-      maxG = std::max(maxG, P.G);
       F->flops += P.flops_period * P.T + P.flops_chain;
       F->flops_int += P.flops_period * P.T;
       F->factor_entries += P.lsize * P.T + 2LL * P.G * P.G * P.T;
@@ -2453,16 +2499,20 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
         delete F;
         return api_fail(OPF_EHIP, "chol: hipSetDevice failed");
       }
-      for (auto& C : F->inst) {
-        const int rc = setup_device(F, C);
-        if (rc != OPF_OK) {
-          release(F);
-          delete F;
-          return rc;
+      int rc = setup_instances(F, cyclic_budget());
+      // what the chain from both ends leaves room for is not refused
+      if (rc == OPF_ENOMEM && std::any_of(F->inst.begin(), F->inst.end(), [](const CholInst& C) { return C.cyclic; })) {
+        release(F);
+        (void)hipGetLastError();  // the failed allocation's
+        for (auto& C : F->inst) {
+          CholInst fresh;
+          fresh.plan = std::move(C.plan);
+          fresh.I = C.I;
+          fresh.nlarge = C.nlarge;
+          C = std::move(fresh);
         }
-        F->arena_entries += C.plan.usize * C.chunk;
+        rc = setup_instances(F, 0);
       }
-      const int rc = dalloc(F, 2 * (int64_t)maxG * maxG, &F->Us);
       if (rc != OPF_OK) {
         release(F);
         delete F;
