@@ -343,11 +343,14 @@ int opf_autotune(opf_model *model, const char *cache_path);
 typedef struct opf_chol opf_chol;
 
 typedef struct {
-  int64_t factor_entries; /* factor doubles, all instances and periods          */
+  int64_t factor_entries; /* stored factor doubles, all instances and periods,
+                             the blocked fronts' diagonal blocks (kept apart)
+                             among them                                       */
   int64_t arena_entries;  /* update-matrix workspace doubles                  */
-  double flops;           /* factorization flops (multiply-add = 2); both for
-                             the chain from both ends, cyclic reduction stores
-                             and computes more                                */
+  double flops;           /* factorization flops (multiply-add = 2).  These
+                             three are of the pg chain's form in use; on a
+                             host-only model nothing is stored: entries of the
+                             fronts themselves, chain from both ends          */
   double flops_interior;  /* of which in the per-period interior fronts       */
   int32_t nodes;          /* interior fronts per period, summed over instances */
   int32_t levels;         /* largest interior tree height                      */

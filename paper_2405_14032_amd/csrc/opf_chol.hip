@@ -1758,6 +1758,18 @@ int64_t cyclic_budget() {
 // Update blocks of cyclic reduction, in doubles: the first level has the most.
 int64_t cyclic_blocks(const CholPlan& P) { return (P.T + 1) / 2 * 4LL * P.G * P.G; }
 
+// Flops of cyclic reduction (p^3 / 3 + p^2 u + p u^2 a front, counted as the
+// plan counts the chain's), level by level.
+double cyclic_flops(const CholPlan& P) {
+  const double G = P.G;
+  double f = 0.0;
+  for (int64_t h = 1; h <= P.T; h *= 2) {
+    const int64_t n = P.T / h, c = (n + 1) / 2;
+    f += (double)c * G * G * G * (c > 1 ? 19.0 : (n > 1 ? 7.0 : 1.0)) / 3.0;
+  }
+  return f;
+}
+
 template <class T>
 int upload(opf_chol* F, const std::vector<T>& h, T** d) {
   const size_t bytes = std::max<size_t>(1, h.size()) * sizeof(T);
@@ -1975,11 +1987,14 @@ int setup_instances(opf_chol* F, int64_t cyc) {
     }
     maxG = std::max<int64_t>(maxG, P.G);
   }
-  F->arena_entries = 0;
+  F->arena_entries = F->factor_entries = 0;
+  F->flops = F->flops_int;
   for (auto& C : F->inst) {
     CHK(setup_device(F, C));
     const int64_t ar = C.plan.usize * C.chunk;
     F->arena_entries += ar;
+    F->factor_entries += (C.plan.lsize + C.csize + C.dsize + C.dcsize) * C.plan.T;
+    F->flops += C.cyclic ? cyclic_flops(C.plan) : C.plan.flops_chain;
     // the interior fronts' workspace is free when the reduction starts, and
     // the instances are factored one after another
     if (C.cyclic && cyclic_blocks(C.plan) <= ar) C.Uc = C.Ar;

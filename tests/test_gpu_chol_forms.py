@@ -65,3 +65,65 @@ def test_failed_allocation_takes_the_chain(dev, monkeypatch):  # noqa: F811
     got = _solve(nets, inps, torch, dev)
     assert np.array_equal(got, chain)
     _check(nets, inps, got, "well", "failed allocation")
+
+
+def _counts(net, tr, cyclic):
+    """Stored factor doubles and flops of an instance by enumeration: the
+    interior fronts of its tree, then the pg fronts one by one."""
+    p = tr["npiv"].astype(np.int64)
+    u = np.diff(tr["rowptr"]).astype(np.int64)
+    G, T = net.G, net.T
+
+    def diag(k):  # 64 x 64 diagonal blocks, the last one as it is
+        return sum(min(64, k - j) ** 2 for j in range(0, k, 64))
+
+    def work(a, b):
+        return a ** 3 / 3 + a * a * b + a * b * b
+
+    ent = int(np.sum((p + u) * p)) + sum(diag(int(k)) for k, v in zip(p, u) if k + v > 64)
+    flops = float(sum(work(float(k), float(v)) for k, v in zip(p, u))) * T
+    ent = (ent + (3 if cyclic else 2) * G * G + diag(G)) * T
+    if not cyclic:
+        return ent, flops + (T - 1) * work(G, G) + work(G, 0)
+    left = list(range(T))  # every other one of the fronts left, from the first
+    while left:
+        gone, stay = left[::2], left[1::2]
+        for _ in gone:
+            flops += work(G, 2 * G if len(gone) > 1 else (G if stay else 0))
+        left = stay
+    return ent, flops
+
+
+@pytest.mark.parametrize("T,cyclic", [(63, False), (64, True), (70, True), (70, False)])
+def test_info_counts_the_form_in_use(T, cyclic, dev, monkeypatch):  # noqa: F811
+    from paper_2405_14032_amd import capi
+    nets = [synth.make_network(90, 130, 70, T, 8), synth.make_network(31, 45, 7, 6, 4)]
+    if T >= 64 and not cyclic:
+        monkeypatch.setenv("OPF_CHOL_CYCLIC_BYTES", "0")
+    host, M = capi.Model(nets, device=-1), capi.Model(nets, device=0)
+    H, F = capi.Chol(host), capi.Chol(M)
+    want = [_counts(k, F.tree(i), cyclic and i == 0) for i, k in enumerate(nets)]
+    info, plan = F.info(), H.info()
+    assert info["factor_entries"] == sum(w[0] for w in want)
+    assert abs(info["flops"] - sum(w[1] for w in want)) <= 1e-12 * info["flops"]
+    assert info["arena_entries"] >= plan["arena_entries"]
+    assert info["flops"] >= plan["flops"] and info["factor_entries"] > plan["factor_entries"]
+    for o in (F, H, M, host):
+        o.close()
+
+
+def test_info_counts_separate_update_blocks(dev, monkeypatch):  # noqa: F811
+    """With a workspace of one period per chunk the reduction's update blocks
+    do not fit it: one block for both instances, counted with the workspace."""
+    from paper_2405_14032_amd import capi
+    nets = [synth.make_network(40, 56, 9, 70, 3), synth.make_network(31, 45, 7, 66, 4)]
+    monkeypatch.setenv("OPF_CHOL_ARENA_BYTES", "1")
+    M = capi.Model(nets, device=0)
+    F = capi.Chol(M)
+    both = F.info()["arena_entries"]
+    F.close()
+    monkeypatch.setenv("OPF_CHOL_CYCLIC_BYTES", "0")
+    F = capi.Chol(M)
+    assert both - F.info()["arena_entries"] == max(_added(k)[1] for k in nets) // 8
+    F.close()
+    M.close()
