@@ -1169,8 +1169,9 @@ struct Tri {
 // of 16), solved by one wavefront: lane i holds row i
 // of the symmetric diagonal block in registers (forward: its entries left of
 // the diagonal, backward those right of it, which are column i below the
-// diagonal; 0 elsewhere), its entry v of the right-hand side and its pivot's
-// reciprocal.  Step k: every lane's product v r, of which lane k's is entry k
+// diagonal; 0 elsewhere, or finite past kb, where the steps multiply by 0: never
+// the diagonal, which may be infinite), its entry v of the right-hand side and
+// its pivot's reciprocal.  Step k: every lane's product v r, of which lane k's is entry k
 // of the solution, broadcast, and one update -- four instructions, and 64 of
 // these steps are what a solve launch waits for.  Lanes past kb hold zeros.
 template <int N = 64>
@@ -1183,7 +1184,8 @@ __device__ __forceinline__ void load_triangle(Triangle<N>& T, const double* __re
 #pragma unroll
   for (int k = 0; k < N; ++k) T.t[k] = D[min(k, kb - 1) * kb + at];
   const double d = D[at * kb + at];
-  int ln = lane < kb ? lane : (FWD ? 0 : 64);
+  // (backward, the last row has no entries; past kb it would meet its diagonal)
+  int ln = FWD ? (lane < kb ? lane : 0) : (lane < kb - 1 ? lane : 64);
   // the masks below are taken when they are needed (kept over a front's
   // panels they would fill the scalar registers four times over)
   asm volatile("" : "+v"(ln));

@@ -127,3 +127,48 @@ def test_info_counts_separate_update_blocks(dev, monkeypatch):  # noqa: F811
     assert both - F.info()["arena_entries"] == max(_added(k)[1] for k in nets) // 8
     F.close()
     M.close()
+
+
+
+@pytest.mark.parametrize("G,T", [(1, 1), (5, 3), (16, 4), (17, 3), (20, 1), (33, 2), (54, 3), (64, 1), (65, 3), (70, 1),
+                                 (130, 2), (257, 1), (17, 64), (70, 65), (5, 64)])
+def test_infinite_pivots_anywhere_in_a_panel(G, T, dev):  # noqa: F811
+    """A generator held fixed by an infinite diagonal entry gets 0 wherever its
+    pivot lies in the pg front, the last of a part-filled panel included, and
+    the others the solution without it (well conditioned family, 1e-8)."""
+    import torch
+    from oracle import opf_oracle as O
+    from paper_2405_14032_amd import capi
+    from test_gpu_chol import _oracle_k
+    net = synth.make_network(max(14, G), int(1.4 * max(14, G)), G, T, 9)
+    M = capi.Model([net], device=0)
+    M.use_current_torch_stream()
+    F = capi.Chol(M)
+    inp = _inputs([net], "well", 37)[0]
+    t = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+    e = lambda k: torch.empty(k, dtype=torch.float64, device=dev)
+    jv, hv, kv, x = e(M.nnz_jac), e(M.nnz_hess), e(M.nnz_kkt), e(M.n)
+    M.eval_jhk(t(inp["x"]), t(inp["lam"]), 1.0, t(inp["diag_x"]), t(inp["dcon"]), jv, hv, kv)
+    rp, ci = torch.empty(M.n + 1, dtype=torch.int64, device=dev), torch.empty(M.nnz_kkt, dtype=torch.int32, device=dev)
+    M.kkt_structure(rp, ci)
+    npert = torch.zeros(1, dtype=torch.int32, device=dev)
+    n, orp, oci, okv = _oracle_k(net, inp)
+    K = O.kkt_full(n, orp, oci, okv).tocsc()
+    import scipy.sparse.linalg as sla
+    np_ = M.n // T
+    for g in sorted({0, G // 2, max(0, G - 2), G - 1}):
+        for tt in sorted({0, T // 2, T - 1}):
+            at = tt * np_ + 2 * net.N + g
+            k2 = kv.clone()
+            k2[rp[at + 1] - 1] = float("inf")
+            F.factor(k2, 0.0, 1.0, npert)
+            F.solve(t(inp["b"]), x)
+            torch.cuda.synchronize()
+            got = x.cpu().numpy()
+            keep = np.arange(n) != at
+            ref = np.zeros(n)
+            ref[keep] = sla.spsolve(K[keep][:, keep].tocsc(), inp["b"][keep])
+            assert int(npert.item()) == 0 and got[at] == 0.0, (g, tt)
+            assert np.max(np.abs(got - ref)) <= 1e-8 * np.max(np.abs(ref)), (g, tt)
+    F.close()
+    M.close()
