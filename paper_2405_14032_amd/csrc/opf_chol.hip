@@ -1174,6 +1174,9 @@ struct Tri {
 // its pivot's reciprocal.  Step k: every lane's product v r, of which lane k's is entry k
 // of the solution, broadcast, and one update -- four instructions, and 64 of
 // these steps are what a solve launch waits for.  Lanes past kb hold zeros.
+// Every step runs in every lane, with a zero where there is no entry, so an
+// entry that is infinite or NaN makes all lanes NaN, the last one broadcast too:
+// then the steps run once more, from memory, each in the lanes it belongs to.
 template <int N = 64>
 struct Triangle {
   double t[N], r;
@@ -1194,7 +1197,9 @@ __device__ __forceinline__ void load_triangle(Triangle<N>& T, const double* __re
   T.r = lane < kb ? 1.0 / d : 0.0;
 }
 template <bool FWD, int N>
-__device__ __forceinline__ double solve_triangle(const Triangle<N>& T, int kb, double v) {
+__device__ __forceinline__ double solve_triangle(const Triangle<N>& T, const double* __restrict__ D, int kb, int lane,
+                                                 double y) {
+  double v = y, x = 0.0;
 #pragma unroll
   for (int q = 0; q < N / 16; ++q) {
     const int b = FWD ? q : N / 16 - 1 - q;
@@ -1202,7 +1207,18 @@ __device__ __forceinline__ double solve_triangle(const Triangle<N>& T, int kb, d
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int k = b * 16 + (FWD ? j : 15 - j);
-      v = fma(-T.t[k], lane_bcast(v * T.r, k), v);
+      x = lane_bcast(v * T.r, k);
+      v = fma(-T.t[k], x, v);
+    }
+  }
+  const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32) & 0x7ff00000u;
+  if (__builtin_expect(hi == 0x7ff00000u, 0)) {
+    v = y;
+#pragma unroll 1
+    for (int q = 0; q < kb; ++q) {
+      const int k = FWD ? q : kb - 1 - q;
+      x = lane_bcast(v * T.r, k);
+      if (lane < kb && (FWD ? k < lane : k > lane)) v = fma(-D[k * kb + lane], x, v);
     }
   }
   return v * T.r;
@@ -1293,7 +1309,7 @@ __global__ void __launch_bounds__(kInner + ROWS + 128) k_fwd_panel(Tri A, int32_
       const int kb = min(kNB, kend - k);
       const bool mine = (q & 1) == odd;
       if (mine) {
-        const double x = solve_triangle<true>(T, kb, v);
+        const double x = solve_triangle<true>(T, D + (int64_t)k * kNB, kb, lane, v);
         xs[lane] = x;
         if (blockIdx.x == 0 && lane < kb) z[k + lane] = x;
       }
@@ -1469,7 +1485,8 @@ __global__ void __launch_bounds__(kBwdT) k_bwd_panel(Tri A, int32_t q, int32_t c
       const int kb = min(kNB, f.p - k);
       const bool mine = (c & 1) == odd;
       if (mine) {
-        const double x = solve_triangle<false>(T, kb, lane < kb ? zs[k - k0 + lane] : 0.0);
+        const double x = solve_triangle<false>(T, D + (int64_t)k * kNB, kb, lane,
+                                               lane < kb ? zs[k - k0 + lane] : 0.0);
         xs[lane] = x;
         if (blockIdx.x == 0 && lane < kb) y[k + lane] = x;
       }
@@ -1551,7 +1568,8 @@ __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, 
   for (int s = 0; s < n; ++s) {
     if (!kAhead) load(A, s, fwd);
     else if (s + 1 < n) load(B, s + 1, fwd);
-    const double z = solve_triangle<true>(A.T, G, s > 0 && i < G ? A.y - sum : A.y);
+    const double z = solve_triangle<true>(A.T, Dc + (int64_t)front(s) * sD, G, i,
+                                          s > 0 && i < G ? A.y - sum : A.y);
     if (i < G) Z[(int64_t)front(s) * sy + i] = z;
     sum = 0.0;
 #pragma unroll
@@ -1567,9 +1585,9 @@ __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, 
     if (T > 1 && i < G) v -= sh[1][i];
     Triangle<N> M;
     load_triangle<true>(M, Dc + (int64_t)m * sD, G, i);
-    v = solve_triangle<true>(M, G, v);
+    v = solve_triangle<true>(M, Dc + (int64_t)m * sD, G, i, v);
     load_triangle<false>(M, Dc + (int64_t)m * sD, G, i);
-    v = solve_triangle<false>(M, G, v);
+    v = solve_triangle<false>(M, Dc + (int64_t)m * sD, G, i, v);
     if (i < G) Y[(int64_t)m * sy + i] = v;
     xm[i] = v;
   }
@@ -1586,7 +1604,7 @@ __global__ void __launch_bounds__(128) k_chain_wave_solve(int32_t G, int32_t T, 
     for (int d = N > 32 ? 32 : N / 2; d > 0; d /= 2)
 #pragma unroll
       for (int k = 0; k < d && k + d < N; ++k) w[k] += w[k + d];
-    x = solve_triangle<false>(A.T, G, i < G ? A.y - w[0] : 0.0);
+    x = solve_triangle<false>(A.T, Dc + (int64_t)front(s) * sD, G, i, i < G ? A.y - w[0] : 0.0);
     if (i < G) Y[(int64_t)front(s) * sy + i] = x;
   }
 }

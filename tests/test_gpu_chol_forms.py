@@ -172,3 +172,35 @@ def test_infinite_pivots_anywhere_in_a_panel(G, T, dev):  # noqa: F811
             assert np.max(np.abs(got - ref)) <= 1e-8 * np.max(np.abs(ref)), (g, tt)
     F.close()
     M.close()
+
+
+@pytest.mark.parametrize("G,T", [(1, 1), (5, 1), (17, 1), (33, 1), (64, 1), (65, 1), (257, 1), (5, 2), (70, 2)])
+def test_infinite_right_hand_side_stays_in_its_place(G, T, dev):  # noqa: F811
+    """A diagonal K and an infinite entry at the variable eliminated last: it
+    comes out infinite, not NaN (nothing is taken from it afterwards), no
+    entry that is coupled to it finite, and the other instance of the batch is
+    not touched."""
+    import torch
+    from paper_2405_14032_amd import capi
+    net, other = synth.make_network(max(14, G), int(1.4 * max(14, G)), G, T, 9), synth.make_network(14, 20, 5, 2, 10)
+    M = capi.Model([net, other], device=0)
+    M.use_current_torch_stream()
+    F = capi.Chol(M)
+    rp, ci = torch.empty(M.n + 1, dtype=torch.int64, device=dev), torch.empty(M.nnz_kkt, dtype=torch.int32, device=dev)
+    M.kkt_structure(rp, ci)
+    kv = torch.zeros(M.nnz_kkt, dtype=torch.float64, device=dev)
+    kv[rp[1:] - 1] = 4.0
+    last = 2 * net.N + G - 1  # the last pg variable of the chain's middle period, (T - 1) / 2 = 0
+    b, x = torch.ones(M.n, dtype=torch.float64, device=dev), torch.empty(M.n, dtype=torch.float64, device=dev)
+    npert = torch.zeros(1, dtype=torch.int32, device=dev)
+    F.factor(kv, 0.0, 1.0, npert)
+    for v in (np.inf, -np.inf):
+        b[last] = v
+        F.solve(b, x)
+        torch.cuda.synchronize()
+        got = x.cpu().numpy()
+        assert int(npert.item()) == 0 and got[last] == v
+        assert not np.any(np.isfinite(got[2 * net.N:2 * net.N + G]))
+        assert np.array_equal(got[net.n:], np.full(M.n - net.n, 0.25))
+    F.close()
+    M.close()
