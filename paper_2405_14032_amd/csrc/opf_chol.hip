@@ -280,9 +280,11 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
 // (Goldschmidt) steps and a last correction each, where the two functions one
 // after the other are a dependent chain about three times as long -- and a
 // front's pivots are one serial chain.  d outside [2^-500, 2^500] is scaled
-// by a power of four first; an infinite d keeps inf and 0.
+// by a power of four first; an infinite d keeps inf and 0, a zero one 0 and inf.
 __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   const bool lo = d < 0x1p-500, hi = d > 0x1p500;
+  const bool end = __builtin_amdgcn_class(d, 0x260);  // +-0 or infinity
+  const double at_end = hi ? 0.0 : copysign(INFINITY, d);
   const double x = d * (lo ? 0x1p400 : (hi ? 0x1p-400 : 1.0));
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -298,9 +300,8 @@ __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   g *= lo ? 0x1p-200 : (hi ? 0x1p200 : 1.0);
   h *= lo ? 0x1p200 : (hi ? 0x1p-200 : 1.0);
   asm("" : "+v"(g), "+v"(h));  // selects, not a branch around the above
-  const bool inf = d == INFINITY;
-  s = inf ? d : g;
-  r = inf ? 0.0 : h;
+  s = end ? d : g;
+  r = end ? at_end : h;
 }
 
 // The static pivot rule as the elimination uses it: the threshold, the square

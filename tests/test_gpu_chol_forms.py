@@ -204,3 +204,40 @@ def test_infinite_right_hand_side_stays_in_its_place(G, T, dev):  # noqa: F811
         assert np.array_equal(got[net.n:], np.full(M.n - net.n, 0.25))
     F.close()
     M.close()
+
+
+@pytest.mark.parametrize("G", [1, 5, 17, 33, 64, 65, 70])
+def test_zero_pivot_below_a_negative_threshold(G, dev):  # noqa: F811
+    """A threshold below 0 lets a zero pivot stand: not counted, its root 0 and
+    the reciprocal infinite, as sqrt(0) and 1 / 0 round, so the last variable
+    eliminated comes out infinite (a diagonal K); another instance of the batch
+    is not touched."""
+    import torch
+    from paper_2405_14032_amd import capi
+    net, other = synth.make_network(max(14, G), int(1.4 * max(14, G)), G, 1, 9), synth.make_network(14, 20, 5, 2, 10)
+    M = capi.Model([net, other], device=0)
+    M.use_current_torch_stream()
+    F = capi.Chol(M)
+    rp, ci = torch.empty(M.n + 1, dtype=torch.int64, device=dev), torch.empty(M.nnz_kkt, dtype=torch.int32, device=dev)
+    M.kkt_structure(rp, ci)
+    kv = torch.zeros(M.nnz_kkt, dtype=torch.float64, device=dev)
+    kv[rp[1:] - 1] = 4.0
+    last = 2 * net.N + G - 1  # the last pg variable
+    kv[rp[last + 1] - 1] = 0.0
+    b, x = torch.ones(M.n, dtype=torch.float64, device=dev), torch.empty(M.n, dtype=torch.float64, device=dev)
+    b[last] = -1.0
+    npert = torch.full((1,), -7, dtype=torch.int32, device=dev)
+    F.factor(kv, -1.0, 1.0, npert)
+    F.solve(b, x)
+    torch.cuda.synchronize()
+    got = x.cpu().numpy()
+    assert int(npert.item()) == 0 and got[last] == -np.inf
+    assert np.array_equal(got[net.n:], np.full(M.n - net.n, 0.25))
+    F.factor(kv, 0.0, 2.0, npert)  # counted and replaced where the threshold is not below it
+    F.solve(b, x)
+    torch.cuda.synchronize()
+    want = np.full(M.n, 0.25)
+    want[last] = -0.5
+    assert int(npert.item()) == 1 and np.max(np.abs(x.cpu().numpy() - want)) <= 1e-15
+    F.close()
+    M.close()
