@@ -19,8 +19,9 @@ const std::vector<InstHost>& model_insts(const opf_model* M);
 int64_t model_n(const opf_model* M);
 int64_t model_nnzk(const opf_model* M);
 const opf_model* chol_model(const opf_chol* F);  // the model F was analysed from
-// Device memory of the factor object for a caller's work vectors: at least
-// bytes, uninitialised, valid until the next call on F or until F is destroyed.
-// Grown when a call asks for more, otherwise the same block again.
+// Device memory of the factor object for the work vectors of its model's
+// interior-point loop: bytes (the model's dimensions give them: the same at
+// every call), uninitialised, allocated by the first call and the same block
+// again by the later ones, until F is destroyed.
 int chol_workspace(opf_chol* F, size_t bytes, void** out);
 }  // namespace opf

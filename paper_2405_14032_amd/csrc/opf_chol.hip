@@ -72,8 +72,8 @@ constexpr int kBwdCols = 32;     // earlier columns updated per block of a backw
 
 // Device view of one instance's plan.
 struct CDev {
-  const int32_t *node_f, *node_p, *node_u, *rel, *kids, *rows;
-  const int64_t *node_loff, *node_uoff, *node_woff, *row_ptr, *kid_ptr;
+  const int32_t *node_p, *node_u, *rel, *kids, *rows;
+  const int64_t *node_loff, *node_uoff, *node_woff, *row_ptr;
   // extend-add: per node its rows by position in its parent's front (inv, -1:
   // none); per column of a large front (col_off) or of the pg front (from
   // col_root) the children with an entry there in their order, con[col[q]] ..
@@ -1682,7 +1682,7 @@ struct CholInst {
   CholPlan plan;
   const InstHost* I = nullptr;
   CDev dev{};
-  int32_t *d_node_f = nullptr, *d_node_p = nullptr, *d_node_u = nullptr, *d_rel = nullptr, *d_kids = nullptr,
+  int32_t *d_node_p = nullptr, *d_node_u = nullptr, *d_rel = nullptr, *d_kids = nullptr,
           *d_rows = nullptr, *d_perm = nullptr, *d_items = nullptr, *d_roots = nullptr,
           *d_kpos0 = nullptr, *d_kpos1 = nullptr, *d_ramp = nullptr, *d_inv = nullptr, *d_col = nullptr;
   int64_t *d_coloff = nullptr, *d_smallptr = nullptr;
@@ -1690,8 +1690,7 @@ struct CholInst {
   longlong2* d_con = nullptr;
   longlong4* d_kid = nullptr;
   std::vector<int64_t> lvl_item, lvl_big;  // per level: extend-add items; the first small front of more than 32 rows
-  int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_kidptr = nullptr,
-          *d_slot = nullptr;
+  int64_t *d_loff = nullptr, *d_uoff = nullptr, *d_woff = nullptr, *d_rowptr = nullptr, *d_slot = nullptr;
   double *Lf = nullptr, *Cf = nullptr, *Df = nullptr, *Dc = nullptr, *Ar = nullptr, *W = nullptr, *V = nullptr, *Wc = nullptr, *Y = nullptr, *Z = nullptr;
   double* Gp = nullptr;  // running sums of the chain's L21 z (a step's fronts)
   std::vector<FrontRec> rec;  // the large fronts, by level
@@ -1702,7 +1701,7 @@ struct CholInst {
   double* Uc = nullptr;       // cyclic reduction: a level's update blocks (in Ar, or opf_chol::Uc)
   FrontRec *d_rec = nullptr, *d_srec = nullptr;  // large fronts; small ones, by level
   int64_t csize = 0, wsize = 0, dsize = 0, dcsize = 0;
-  int32_t chunk = 1, nlarge = 0;
+  int32_t chunk = 1;
 };
 
 }  // namespace
@@ -1727,7 +1726,6 @@ struct opf_chol {
   bool stop_on_pivot = false;  // skip the rest of a factorization after its first static pivot
   std::vector<void*> allocs;
   void* work = nullptr;  // chol_workspace
-  size_t work_bytes = 0;
   double flops = 0.0, flops_int = 0.0;
   int64_t factor_entries = 0, arena_entries = 0;
 };
@@ -1735,13 +1733,9 @@ struct opf_chol {
 const opf_model* opf::chol_model(const opf_chol* F) { return F ? F->model : nullptr; }
 
 int opf::chol_workspace(opf_chol* F, size_t bytes, void** out) {
-  if (bytes > F->work_bytes) {
-    if (F->work) (void)hipFree(F->work);
+  if (!F->work && hipMalloc(&F->work, bytes) != hipSuccess) {
     F->work = nullptr;
-    F->work_bytes = 0;
-    if (hipMalloc(&F->work, bytes) != hipSuccess)
-      return api_fail(OPF_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
-    F->work_bytes = bytes;
+    return api_fail(OPF_ENOMEM, "device allocation of " + std::to_string(bytes) + " bytes failed");
   }
   *out = F->work;
   return OPF_OK;
@@ -1935,7 +1929,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   C.cld = (C.cyclic ? 3 : 2) * P.G;
   for (int k = 0; k < 3; ++k) C.crec[k] = {0, 0, 0, 0, 0, P.G, k * P.G, C.cld, 0, 0, 0};
   CHK(upload(F, C.rec, &C.d_rec));
-  CHK(upload(F, P.node_f, &C.d_node_f));
   CHK(upload(F, P.node_p, &C.d_node_p));
   CHK(upload(F, P.node_u, &C.d_node_u));
   CHK(upload(F, P.rel, &C.d_rel));
@@ -1951,7 +1944,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(upload(F, P.node_uoff, &C.d_uoff));
   CHK(upload(F, woff, &C.d_woff));
   CHK(upload(F, P.row_ptr, &C.d_rowptr));
-  CHK(upload(F, P.kid_ptr, &C.d_kidptr));
   const int64_t T = P.T, G = P.G;
   // the plan numbers a pg front's entries with leading dimension 2 G
   std::vector<int64_t> slot = P.slot_dst;
@@ -1972,7 +1964,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   CHK(dalloc(F, C.cyclic ? (T + 1) / 2 * 2 * G : 2 * G, &C.Gp));
   CHK(dalloc(F, C.wsize * T, &C.V));
   CDev& D = C.dev;
-  D.node_f = C.d_node_f;
   D.node_p = C.d_node_p;
   D.node_u = C.d_node_u;
   D.rel = C.d_rel;
@@ -1982,7 +1973,6 @@ int setup_device(opf_chol* F, CholInst& C) {
   D.node_uoff = C.d_uoff;
   D.node_woff = C.d_woff;
   D.row_ptr = C.d_rowptr;
-  D.kid_ptr = C.d_kidptr;
   D.lsize = P.lsize;
   D.usize = P.usize;
   D.wsize = C.wsize;
@@ -2525,7 +2515,6 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
         return api_fail(rc, "instance " + std::to_string(k) + ": " + err);
       }
       const CholPlan& P = C.plan;
-      C.nlarge = (int32_t)P.lvl_large.size();
       F->flops += P.flops_period * P.T + P.flops_chain;
       F->flops_int += P.flops_period * P.T;
       F->factor_entries += P.lsize * P.T + 2LL * P.G * P.G * P.T;
@@ -2544,7 +2533,6 @@ int opf_chol_analyze(opf_model* model, opf_chol** out) {
           CholInst fresh;
           fresh.plan = std::move(C.plan);
           fresh.I = C.I;
-          fresh.nlarge = C.nlarge;
           C = std::move(fresh);
         }
         rc = setup_instances(F, 0);
