@@ -241,3 +241,79 @@ def test_zero_pivot_below_a_negative_threshold(G, dev):  # noqa: F811
     assert int(npert.item()) == 1 and np.max(np.abs(x.cpu().numpy() - want)) <= 1e-15
     F.close()
     M.close()
+
+
+# solves of two and more 256-column launches a front, one and two 1024-column
+# steps of the factorization, the last size that is reduced and the next one
+@pytest.mark.parametrize("G,T,reduced", [(257, 64, True), (400, 66, True), (513, 65, True), (1030, 64, True),
+                                         (1536, 64, True), (1537, 64, False)])
+def test_both_forms_on_large_fronts(G, T, reduced, dev, monkeypatch):  # noqa: F811
+    """The same K by cyclic reduction and by the chain: backward error in K of
+    each (1e-11), so two eliminations in different orders that agree to twice
+    the forward tolerance (2e-8); beyond the reduction's sizes both are the
+    chain, bit for bit."""
+    import scipy.sparse as sp
+    import torch
+    from paper_2405_14032_amd import capi
+    net = synth.make_network(G, int(1.3 * G), G, T, 61)
+    print(f"both forms G={G} T={T}", flush=True)
+    inp = _inputs([net], "well", 41)[0]
+    M = capi.Model([net], device=0)
+    M.use_current_torch_stream()
+    t = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=dev)
+    e = lambda k: torch.empty(k, dtype=torch.float64, device=dev)
+    jv, hv, kv, x, b = e(M.nnz_jac), e(M.nnz_hess), e(M.nnz_kkt), e(M.n), t(inp["b"])
+    M.eval_jhk(t(inp["x"]), t(inp["lam"]), 1.0, t(inp["diag_x"]), t(inp["dcon"]), jv, hv, kv)
+    rp, ci = torch.empty(M.n + 1, dtype=torch.int64, device=dev), torch.empty(M.nnz_kkt, dtype=torch.int32, device=dev)
+    M.kkt_structure(rp, ci)
+    npert = torch.zeros(1, dtype=torch.int32, device=dev)
+    got, flops = [], []
+    for budget in (None, "0"):
+        if budget:
+            monkeypatch.setenv("OPF_CHOL_CYCLIC_BYTES", budget)
+        F = capi.Chol(M)
+        flops.append(F.info()["flops"])
+        for _ in range(2):
+            F.factor(kv, 0.0, 1.0, npert)
+            F.solve(b, x)
+        torch.cuda.synchronize()
+        assert int(npert.item()) == 0
+        got.append(x.cpu().numpy().copy())
+        F.close()
+    lower = sp.csr_matrix((kv.cpu().numpy(), ci.cpu().numpy(), rp.cpu().numpy()), shape=(M.n, M.n))
+    M.close()
+    K = (lower + sp.tril(lower, -1).T).tocsr()
+    for v in got:
+        assert np.max(np.abs(K @ v - inp["b"])) <= 1e-11 * (abs(K).max() * np.max(np.abs(v)) + np.max(np.abs(inp["b"])))
+    assert (flops[0] > flops[1]) == reduced
+    if reduced:
+        assert 0.0 < np.max(np.abs(got[0] - got[1])) <= 2e-8 * np.max(np.abs(got[1]))
+    else:
+        assert np.array_equal(got[0], got[1])
+
+
+def test_static_pivots_in_both_forms(dev, monkeypatch):  # noqa: F811
+    """Whether a static pivot is taken is a property of K (indefinite or not):
+    the same answer from both forms with fronts of several panels, full and
+    stopped at the first."""
+    import torch
+    from paper_2405_14032_amd import capi
+    net = synth.make_network(300, 420, 270, 65, 61)
+    inps = _inputs([net], "well", 43)
+    neg = inps[0]["diag_x"].copy()
+    neg.reshape(net.T, -1)[40, 2 * net.N + 269] = -1e6  # one generator of one period
+    M = capi.Model([net], device=0)
+    M.use_current_torch_stream()
+    for budget in (None, "0"):
+        if budget:
+            monkeypatch.setenv("OPF_CHOL_CYCLIC_BYTES", budget)
+        F = capi.Chol(M)
+        assert _gpu_solve(M, F, inps, torch, dev)[1] == 0
+        for stop in (False, True):
+            F.set_stop_on_pivot(stop)
+            assert _gpu_solve(M, F, [dict(inps[0], diag_x=neg)], torch, dev)[1] >= 1
+        x, n = _gpu_solve(M, F, inps, torch, dev)
+        assert n == 0
+        _check([net], inps, x, "backward error only", f"static pivots, budget {budget}")
+        F.close()
+    M.close()
