@@ -579,16 +579,17 @@ int build_fused(opf_model* M) {
 // not fit the LDS budget (buses of high degree).  256 elements and one period
 // per tile, except in the whole sweep of a model that has few wavefronts for
 // the chip's 1024 SIMDs: blocks of one wavefront there, which spread over more
-// CUs and wait for nobody, unless a period is one block of 256 anyhow.
-//   * line pass (wavefronts of lines and generators), one period each up to one
-//     per SIMD: 1000 buses x 8 periods 27.6 -> 23.8 us a sweep, 300 x 24 26.8 ->
-//     24.3, 150 (210 lines) x 24 25.2 -> 23.1; 140 lines the same, 85 and fewer
-//     21.6 -> 21.7.  Up to 1.5 per SIMD two periods, the second one's loads
-//     behind the first: 2000 x 24 44.1 -> 40.2.  Beyond, blocks of 256 share
-//     their K rows' writes better: 1500 x 50 52.7 us against 56.1, 6000 x 24
-//     82.6 against 86.6, 2000 x 168 159 against 182.
-//   * bus pass: 300 buses x 6 26.1 -> 25.3 us, 2000 x 40 57.7 -> 56.3, but 100 x
-//     168 25.5 -> 26.5 and 1500 x 70 67.3 -> 68.6.
+// CUs and wait for nobody, from the sizes on where that was measured to gain.
+//   * line pass (wavefronts of lines and generators), more than 128 lines (three
+//     wavefronts): one period each up to one per SIMD: 1000 buses x 8 periods
+//     27.6 -> 23.8 us a sweep, 300 x 24 26.8 -> 24.3, 150 (210 lines) x 24 25.2 ->
+//     23.1; 140 lines the same, 85 and fewer 21.6 -> 21.7.  Up to 1.5 per SIMD two
+//     periods, the second one's loads behind the first: 2000 x 24 44.1 -> 40.2.
+//     Beyond, blocks of 256 share their K rows' writes better: 1500 x 50 52.7 us
+//     against 56.1, 6000 x 24 82.6 against 86.6, 2000 x 168 159 against 182.
+//   * bus pass, more than 256 buses (one block of 256): 300 buses x 6 26.1 -> 25.3
+//     us, 2000 x 40 57.7 -> 56.3, but 100 x 168 25.5 -> 26.5 and 1500 x 70 67.3 ->
+//     68.6.
 int set_default_shape(opf_model* M, int op) {
   Shape s;
   int64_t waves = 0;

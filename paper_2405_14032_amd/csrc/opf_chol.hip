@@ -49,12 +49,12 @@ constexpr int kTreeFronts = 16;  // levels of at most this many fronts share the
 constexpr int kFewTiles = 256;   // updates of fewer 64 x 64 tiles take 32 x 32 ones (one block per CU)
 // The pg chain by cyclic reduction (see k_cyc_add) from kCycT periods, up to
 // fronts of kCycG: factor + solve, from both ends against by reduction, 54
-// generators x 64 periods 2.44 / 1.12 ms, 400 x 64 25.9 / 18.5, 400 x 168 51 /
-// 43, 1000 x 168 185 / 140, 1400 x 168 314 / 285, but 2000 x 168 675 / 722: the
-// third of the work it adds outgrows the steps it saves.  Short horizons gain
-// less (400 x 24: 11.2 / 8.9 ms) and stay with the chain: an interior-point
-// iterate shows a changed elimination order at 1e-8, and small grids keep
-// theirs bit for bit.  The memory it takes beyond the chain's (G^2 per period
+// generators x 64 periods 2.05 / 0.92 ms, 400 x 64 21.4 / 14.8, 400 x 168 53 /
+// 34, 1000 x 168 110 / 70, 1400 x 168 173 / 138, 1600 x 168 198 / 172, but 2000 x
+// 168 602 / 644: the work it adds outgrows the steps it saves.  The line on the
+// horizon is not one of speed (400 x 24 takes 9.2 / 7.3 ms, 54 x 24 1.10 / 0.74):
+// an interior-point iterate shows a changed elimination order at 1e-8, and
+// short horizons keep theirs bit for bit.  The memory it takes beyond the chain's (G^2 per period
 // for the pg fronts, 2 G^2 for a level's update blocks, which the instances of
 // a batch share) is held to kCycBytes over all instances together.
 constexpr int kCycT = 64, kCycG = 1536;
@@ -470,10 +470,13 @@ __global__ void __launch_bounds__(64) k_factor_small(CDev D, const FrontRec* __r
 // Right-looking elimination of 16 columns, one row per lane, lanes 0-15 the
 // diagonal rows; low counts the static pivots among the first n columns.
 // Column k updates column k + 1 first; then that column's pivot is taken
-// (sqrt_recip without its scaling, step by step, some 15 dependent operations)
-// with the updates of the columns further right in between, one after each
+// (a hardware estimate refined step by step, some 15 dependent operations)
+// with the updates of the columns further right in between, some after each
 // step: one wavefront issues an instruction every 4 cycles at best, so the
 // chain's waits are where the updates belong, and every instruction counts.
+// (Its steps: one coupled refinement, two corrections of the root and one of
+// the reciprocal, where sqrt_recip and next_column refine twice and correct
+// each once.  Either way both round as sqrt() and the division.)
 // The empty asm statements hold that order; left to itself the compiler
 // collects a column's updates in front of its pivot, one dependent chain, and
 // spills the broadcast entries.
@@ -714,7 +717,8 @@ __global__ void __launch_bounds__(kPT) k_panel(Fronts F, int32_t kbeg, int32_t k
 // What bounds a large launch is keeping the matrix cores issued: a block in its
 // first loads or its last read-modify-write has to leave others running.  64 x
 // 64 tiles of 4 wavefronts (32 x 32 each, 63 VGPRs) with 8 panel columns per
-// LDS round (20 KB for both buffers) leave 7 blocks on a CU: 58 TFLOP/s at
+// LDS round (20 KB for both buffers) leave 7 blocks on a CU (its LDS holds no
+// more; the launch bounds only keep the registers to 6 or more): 58 TFLOP/s at
 // 4323 columns x 1024 panel columns x 8 periods, 47 at 4114 x 204 x 8, 55 at
 // 2976 x 1024 x 2; 128 x 128 tiles of 4 wavefronts (2 blocks on a CU) reached
 // 51, 33 and 37, of 8 wavefronts 60, 45 and 43, and twice the time on launches
@@ -966,7 +970,7 @@ __global__ void __launch_bounds__(128) k_chain_wave(int32_t G, int32_t T, double
 // rows, in this order (a missing neighbour's rows are zero; a level of one
 // front has no left rows).  Its update block links the two.  T = 168 periods
 // take 8 levels where the two-ended chain takes 84 steps, at 19/3 G^3 instead
-// of 7/3 G^3 multiply-adds for most fronts.
+// of 7/3 G^3 flops (a multiply-add two) for most fronts.
 
 // Front i's updates (2G x 2G blocks Ub, ub rows) into the pivot blocks of the
 // fronts that stay: front s = 2 i + 1 takes its left neighbour's (i, its right
