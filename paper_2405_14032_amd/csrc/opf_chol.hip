@@ -280,11 +280,9 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
 // (Goldschmidt) steps and a last correction each, where the two functions one
 // after the other are a dependent chain about three times as long -- and a
 // front's pivots are one serial chain.  d outside [2^-500, 2^500] is scaled
-// by a power of four first; an infinite d keeps inf and 0, a zero one 0 and inf.
+// by a power of four first; neither zero nor infinite (see odd_pivot).
 __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   const bool lo = d < 0x1p-500, hi = d > 0x1p500;
-  const bool end = __builtin_amdgcn_class(d, 0x260);  // +-0 or infinity
-  const double at_end = hi ? 0.0 : copysign(INFINITY, d);
   const double x = d * (lo ? 0x1p400 : (hi ? 0x1p-400 : 1.0));
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -299,9 +297,8 @@ __device__ __forceinline__ void sqrt_recip(double d, double& s, double& r) {
   h = fma(fma(-g, h, 1.0), h, h);
   g *= lo ? 0x1p-200 : (hi ? 0x1p200 : 1.0);
   h *= lo ? 0x1p200 : (hi ? 0x1p-200 : 1.0);
-  asm("" : "+v"(g), "+v"(h));  // selects, not a branch around the above
-  s = end ? d : g;
-  r = end ? at_end : h;
+  s = g;
+  r = h;
 }
 
 // The static pivot rule as the elimination uses it: the threshold, the square
@@ -310,13 +307,17 @@ struct PivotRule {
   double tol, s_repl, r_repl;
 };
 
-// Square root and reciprocal of a pivot that is static, infinite, NaN or far
-// from 1 in size: rare, kept out of the pivot chain.
+// Square root and reciprocal of a pivot that is static, infinite, NaN, zero
+// (under a threshold below 0) or far from 1 in size: rare, kept out of the pivot
+// chain.  An infinite pivot keeps inf and 0, a zero one 0 and inf.
 __device__ __forceinline__ void odd_pivot(double d, const PivotRule& R, bool count, double& s, double& r, int& low) {
-  const bool bad = !(d > R.tol);
+  const bool bad = !(d > R.tol), end = __builtin_amdgcn_class(d, 0x260);  // +-0 or infinity
+  const double r_end = d > 0.0 ? 0.0 : copysign(INFINITY, d);
+  const double s_not = bad ? R.s_repl : d, r_not = bad ? R.r_repl : r_end;
   sqrt_recip(d, s, r);
-  s = bad ? R.s_repl : s;
-  r = bad ? R.r_repl : r;
+  asm("" : "+v"(s), "+v"(r));  // selects, not a branch around the above
+  s = bad || end ? s_not : s;
+  r = bad || end ? r_not : r;
   low += bad && count;
 }
 
